@@ -101,9 +101,9 @@ typedef struct tang_stats_s {
     uint64_t top1_hits;   /* answer lies in the first predicted tuple */
     uint64_t fallbacks;   /* nothing matched in the predicted tuples */
     uint64_t no_match;    /* packets with no matching rule at all */
-    uint64_t filter_checks;  /* bucket-filter bits read (one per tuple reached) */
-    uint64_t wave_steps;     /* per packet: most filter-passing tuples of a packet in its wave */
-    uint64_t wave_rounds;    /* per packet: filter-sweep batches (8 tuples) of its wave */
+    uint64_t filter_checks;  /* bucket-filter blocks read */
+    uint64_t wave_steps;     /* per 64 packets: 64 x the probe-loop steps of their wave */
+    uint64_t wave_rounds;    /* per packet: filter batches (8 groups) of its wave */
 } tang_stats_t;
 
 typedef struct tang_ruleset_s tang_ruleset_t;
@@ -217,11 +217,6 @@ int tang_model_load_resnet(tang_ruleset_t* rs, const tang_resnet_desc_t* desc,
  * unless stats != NULL (then the counters are copied back and the call synchronises).
  * n = 0 is a no-op. Concurrent classify calls on any streams are allowed while no
  * update is in flight; order updates before classify through the streams.
- * With a BF16 or FP8 model loaded, no stats and n >= 2^22, the batch is processed in
- * chunks of 2^21 headers: each chunk's model runs on `stream` and its search on a stream
- * the ruleset owns (created on first use), overlapping the next chunk's model; `stream`
- * then waits for the last search, so completion is still observed through `stream`.
- * Chunked calls on one ruleset share that stream, so their searches run one after another.
  */
 int tang_classify(tang_ruleset_t* rs, const tang_header_t* d_hdr, uint32_t* d_rule_id,
                   size_t n, void* stream, tang_stats_t* stats);

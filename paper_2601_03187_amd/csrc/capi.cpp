@@ -106,7 +106,7 @@ using namespace tang;
 
 size_t tang_ruleset_s::device_bytes() const {
     if (device == TANG_HOST_ONLY) return 0;
-    return slots.size() * sizeof(Slot) + filter.size() * sizeof(uint32_t) +
+    return slots.size() * sizeof(SlotDev) + (nw == 1 ? (size_t)rec_cap * 4 : 0) + (size_t)filter_blocks * 8 +
            (size_t)rec_cap * sizeof(Rec) + (nw > 1 ? (size_t)rec_cap * nw * 4 : 0) +
            sizeof(TupleTable) +
            kStatCopies * sizeof(StatsDev) + model.bytes;
@@ -130,6 +130,8 @@ static void free_device(tang_ruleset_t* rs) {
     (void)hipSetDevice(rs->device);
     model_free(rs->model);
     if (rs->d_slots) (void)dev_release(rs->d_slots);
+    if (rs->d_back) (void)dev_release(rs->d_back);
+    rs->d_back = nullptr;
     if (rs->d_filter) (void)dev_release(rs->d_filter);
     rs->d_filter = nullptr;
     if (rs->d_recs) (void)dev_release(rs->d_recs);
@@ -137,10 +139,6 @@ static void free_device(tang_ruleset_t* rs) {
     rs->d_cmask = nullptr;
     if (rs->d_tt) (void)dev_release(rs->d_tt);
     if (rs->d_stats) (void)dev_release(rs->d_stats);
-    for (hipEvent_t e : rs->pipe_events) (void)hipEventDestroy(e);
-    rs->pipe_events.clear();
-    if (rs->pipe_stream) (void)hipStreamDestroy(rs->pipe_stream);
-    rs->pipe_stream = nullptr;
     rs->d_slots = nullptr;
     rs->d_recs = nullptr;
     rs->d_tt = nullptr;
@@ -360,65 +358,17 @@ static int run_search(tang_ruleset_t* rs, const tang_header_t* d_hdr, uint32_t* 
     return TANG_OK;
 }
 
-// Large batches with a model: chunk k's model runs on the caller's stream while chunk
-// k-1's search runs on the ruleset's own stream, so the MFMA-bound and the latency-bound
-// kernels overlap (and a chunk's headers are still cached when its search reads them).
-// The caller's stream waits for the last search, so the call completes in stream order.
-// If another thread is enqueueing a chunked call on the same ruleset, this call takes
-// the plain path instead of waiting for the lock.
-static int classify_chunked(tang_ruleset_t* rs, const tang_header_t* d_hdr, uint32_t* out,
-                            size_t n, hipStream_t s, bool* done) {
-    *done = false;
-    std::unique_lock<std::mutex> lk(rs->pipe_mu, std::try_to_lock);
-    if (!lk.owns_lock()) return TANG_OK;
-    if (!rs->pipe_stream) TANG_HIP(hipStreamCreateWithFlags(&rs->pipe_stream, hipStreamNonBlocking));
-    // A half chunk first and last (the first chunk's predictor and the last chunk's search
-    // run with nothing beside them), the rest in equal parts of at most kPipeChunk;
-    // n >= 2 kPipeChunk here.
-    const size_t E = kPipeChunk / 2, M = n - 2 * E;
-    const size_t q = (M + kPipeChunk - 1) / kPipeChunk, part = (M + q - 1) / q;
-    std::vector<size_t> sz{E};
-    for (size_t left = M; left > 0; left -= std::min(part, left)) sz.push_back(std::min(part, left));
-    sz.push_back(E);
-    const size_t K = sz.size();
-    while (rs->pipe_events.size() < K + 1) {
-        hipEvent_t e = nullptr;
-        TANG_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-        rs->pipe_events.push_back(e);
-    }
-    const int kcand = rs->model.topk;
-    size_t base = 0;
-    for (size_t k = 0; k < K; base += sz[k], ++k) {
-        const size_t m = sz[k];
-        TANG_HIP(launch_mlp(rs, d_hdr + base, m, out + base, nullptr, nullptr, s, true));
-        TANG_HIP(hipEventRecord(rs->pipe_events[k], s));
-        TANG_HIP(hipStreamWaitEvent(rs->pipe_stream, rs->pipe_events[k], 0));
-        TANG_HIP(launch_classify(rs, d_hdr + base, out + base, m, kcand, rs->pipe_stream, false));
-    }
-    TANG_HIP(hipEventRecord(rs->pipe_events[K], rs->pipe_stream));
-    TANG_HIP(hipStreamWaitEvent(s, rs->pipe_events[K], 0));
-    *done = true;
-    return TANG_OK;
-}
-
 namespace tang {
 int classify_async(tang_ruleset_t* rs, const tang_header_t* d_hdr, uint32_t* d_rule_id, size_t n,
-                   hipStream_t s, tang_stats_t* stats, bool allow_chunks, const uint32_t* d_live) {
+                   hipStream_t s, tang_stats_t* stats, const uint32_t* d_live) {
     int rc = check_classify(rs, d_hdr, d_rule_id, n);
     if (rc) return rc;
-    if (d_live && (stats || allow_chunks || rs->model.kind != 0))
-        return fail(TANG_EINVAL, "a live-count launch takes no stats, chunks or residual model");
+    if (d_live && (stats || rs->model.kind != 0))
+        return fail(TANG_EINVAL, "a live-count launch takes no stats or residual model");
     if (stats) std::memset(stats, 0, sizeof *stats);
     if (n == 0) return TANG_OK;
     TANG_HIP(hipSetDevice(rs->device));
-    // (an FP32 model's MLP takes several times the search: nothing to overlap)
-    if (allow_chunks && rs->model.loaded && rs->model.prec != TANG_FP32 && !stats &&
-        n >= 2 * kPipeChunk) {
-        bool done = false;
-        rc = classify_chunked(rs, d_hdr, d_rule_id, n, s, &done);
-        if (rc || done) return rc;
-    }
-    if (rs->model.loaded) TANG_HIP(launch_mlp(rs, d_hdr, n, d_rule_id, nullptr, nullptr, s, false, d_live));
+    if (rs->model.loaded) TANG_HIP(launch_mlp(rs, d_hdr, n, d_rule_id, nullptr, nullptr, s, d_live));
     return run_search(rs, d_hdr, d_rule_id, n, s, stats, d_live);
 }
 }  // namespace tang
@@ -428,7 +378,7 @@ extern "C" {
 int tang_classify(tang_ruleset_t* rs, const tang_header_t* d_hdr, uint32_t* d_rule_id, size_t n,
                   void* stream, tang_stats_t* stats) {
     TANG_GUARD_BEGIN
-    return classify_async(rs, d_hdr, d_rule_id, n, (hipStream_t)stream, stats, true);
+    return classify_async(rs, d_hdr, d_rule_id, n, (hipStream_t)stream, stats);
     TANG_GUARD_END
 }
 

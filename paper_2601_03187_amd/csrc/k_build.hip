@@ -88,7 +88,9 @@ template <int NW>
 __global__ __launch_bounds__(256) void k_conflict_update(Rec* __restrict__ recs,
                                                          uint32_t* __restrict__ cmask, uint32_t used,
                                                          const uint32_t* __restrict__ new_pos,
-                                                         uint32_t n_new) {
+                                                         uint32_t n_new,
+                                                         const uint32_t* __restrict__ back,
+                                                         SlotDev* __restrict__ slots) {
     __shared__ BoxDev q[256];
     __shared__ uint32_t qkey_p[256], qkey_i[256], qadd[256][NW];
     const uint32_t p = blockIdx.x * 256u + threadIdx.x;
@@ -141,6 +143,12 @@ __global__ __launch_bounds__(256) void k_conflict_update(Rec* __restrict__ recs,
 #pragma unroll
         for (int w = 0; w < NW; ++w)
             if (add[w]) atomicOr(&row[w], add[w]);
+        if constexpr (NW == 1) {
+            if (add[0]) {
+                const uint32_t b = back[p];
+                if (b) atomicOr(&slots[b - 1u].first.cmask, add[0]);
+            }
+        }
     }
 }
 
@@ -154,10 +162,12 @@ __global__ void k_stage_records(const Rec* __restrict__ recs, const Rec* __restr
 }
 
 __global__ void k_place_records(Rec* __restrict__ recs, const Rec* __restrict__ stage,
-                                const uint32_t* __restrict__ dst, uint32_t n) {
+                                const uint32_t* __restrict__ dst, uint32_t n,
+                                uint32_t* __restrict__ back) {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     recs[dst[i]] = stage[i];
+    if (back) back[dst[i]] = 0u;
 }
 
 __global__ void k_stage_masks(const uint32_t* __restrict__ cmask, uint32_t nw,
@@ -177,10 +187,34 @@ __global__ void k_place_masks(uint32_t* __restrict__ cmask, uint32_t nw,
     cmask[(size_t)dst[i / nw] * nw + i % nw] = stage[i];
 }
 
-__global__ void k_scatter_slots(Slot* __restrict__ slots, const uint32_t* __restrict__ idx,
-                                const Slot* __restrict__ val, uint32_t n) {
+__global__ void k_fill_slots(SlotDev* __restrict__ slots, const uint32_t* __restrict__ idx,
+                             const Slot* __restrict__ val, uint32_t n, const Rec* __restrict__ recs,
+                             uint32_t* __restrict__ back, uint32_t* __restrict__ filter,
+                             const TupleTable* __restrict__ tt) {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) slots[idx[i]] = val[i];
+    if (i >= n) return;
+    const uint32_t at = idx ? idx[i] : i;
+    SlotDev d;
+    d.s = val[i];
+    d.first = Rec{0u, 0u, kDead, 0u, 0u, 0u, kDead, 0u};
+    for (uint32_t& p : d.pad) p = 0u;
+    if (d.s.tl != kEmptyTL && !(d.s.off & kSplit) && (d.s.tl & kMaxBucketLen)) {
+        d.first = recs[d.s.off];
+        if (back) back[d.s.off] = at + 1u;
+    }
+    slots[at] = d;
+    const uint32_t tk = d.s.tl >> kTlShift;
+    if (d.s.tl == kEmptyTL || (tk >> kKindShift)) return;
+    // a main bucket: its two bits in the block its group value picks (tuple (0, 0) has no
+    // group: its one possible key always has a bucket)
+    const TupleGroup g = tt->tg[tk];
+    if (g.gkey == kNoGroup) return;
+    const bool by_dip = (g.gkey & 64u) != 0u;
+    const uint32_t v = by_dip ? d.s.md : d.s.ms, o = by_dip ? d.s.ms : d.s.md;
+    uint32_t* blk = filter + 2u * (filter_block(g.salt, v) & tt->filter_mask);
+    const uint32_t h = filter_hash(filter_salt(tk), o);
+    atomicOr(blk, 0x80000000u >> filter_pos_x(h));
+    atomicOr(blk + 1, 0x80000000u >> filter_pos_y(h));
 }
 
 }  // namespace
@@ -201,28 +235,31 @@ hipError_t launch_conflict_build(const BoxDev* d_boxes, size_t n, Rec* d_recs, u
 }
 
 hipError_t launch_conflict_update(Rec* d_recs, uint32_t* d_cmask, uint32_t nw, uint32_t rec_used,
-                                  const uint32_t* d_new_pos, uint32_t n_new, hipStream_t s) {
+                                  const uint32_t* d_new_pos, uint32_t n_new, const uint32_t* d_back,
+                                  SlotDev* d_slots, hipStream_t s) {
     if (!n_new || !rec_used) return hipSuccess;
     const dim3 g((rec_used + 255) / 256), b(256);
     if (nw == 1)
-        hipLaunchKernelGGL(k_conflict_update<1>, g, b, 0, s, d_recs, d_cmask, rec_used, d_new_pos, n_new);
+        hipLaunchKernelGGL(k_conflict_update<1>, g, b, 0, s, d_recs, d_cmask, rec_used, d_new_pos, n_new,
+                           d_back, d_slots);
     else if (nw == kMaskWords)
         hipLaunchKernelGGL(k_conflict_update<kMaskWords>, g, b, 0, s, d_recs, d_cmask, rec_used,
-                           d_new_pos, n_new);
+                           d_new_pos, n_new, d_back, d_slots);
     else
         hipLaunchKernelGGL(k_conflict_update<kMaxWords>, g, b, 0, s, d_recs, d_cmask, rec_used,
-                           d_new_pos, n_new);
+                           d_new_pos, n_new, d_back, d_slots);
     return hipGetLastError();
 }
 
 hipError_t launch_move_records(Rec* d_recs, const Rec* d_fresh, const uint32_t* d_src,
-                               const uint32_t* d_dst, uint32_t n, Rec* d_stage, hipStream_t s) {
+                               const uint32_t* d_dst, uint32_t n, Rec* d_stage, uint32_t* d_back,
+                               hipStream_t s) {
     if (!n) return hipSuccess;
     const dim3 g((n + 255) / 256), b(256);
     hipLaunchKernelGGL(k_stage_records, g, b, 0, s, d_recs, d_fresh, d_src, n, d_stage);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_place_records, g, b, 0, s, d_recs, d_stage, d_dst, n);
+    hipLaunchKernelGGL(k_place_records, g, b, 0, s, d_recs, d_stage, d_dst, n, d_back);
     return hipGetLastError();
 }
 
@@ -237,11 +274,12 @@ hipError_t launch_move_masks(uint32_t* d_cmask, uint32_t nw, const uint32_t* d_s
     return hipGetLastError();
 }
 
-hipError_t launch_scatter_slots(Slot* d_slots, const uint32_t* d_idx, const Slot* d_val,
-                                uint32_t n, hipStream_t s) {
+hipError_t launch_fill_slots(SlotDev* d_slots, const uint32_t* d_idx, const Slot* d_val, uint32_t n,
+                             const Rec* d_recs, uint32_t* d_back, uint32_t* d_filter,
+                             const TupleTable* d_tt, hipStream_t s) {
     if (!n) return hipSuccess;
-    hipLaunchKernelGGL(k_scatter_slots, dim3((n + 255) / 256), dim3(256), 0, s, d_slots, d_idx,
-                       d_val, n);
+    hipLaunchKernelGGL(k_fill_slots, dim3((n + 255) / 256), dim3(256), 0, s, d_slots, d_idx, d_val, n,
+                       d_recs, d_back, d_filter, d_tt);
     return hipGetLastError();
 }
 

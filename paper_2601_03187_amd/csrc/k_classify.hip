@@ -1,4 +1,4 @@
-// Search stage of the two-stage classification (Sec. 5.1.1), one packet per lane:
+// Search stage of the two-stage classification (Sec. 5.1.1):
 //   1. probe the predicted tuples: truncate SIP/DIP to the tuple's prefix lengths,
 //      hash, walk the open-addressing slots to the bucket, and compare the bucket's
 //      rules one by one in (priority, id) order -- the first match is the bucket's best;
@@ -9,16 +9,15 @@
 // Before any slot walk, a bit of the bucket filter rules out a tuple that has no bucket
 // for the header's masked addresses. The filter is blocked by prefix group (the tuples
 // sharing their longer field's length): one 8-byte block answers every tuple of its
-// group, so certification loads one block per group it needs -- all of them at once,
-// eight independent loads at a time -- and then each lane walks slots only for its own
-// tuples whose bit is set. Random loads are what the search pays for (each one costs
-// an L2 request whatever its width), so the scan also reads only the first half of each
-// record and the second half only when a rule matches.
+// group, so certification loads one block per group, eight independent loads at a time.
+// The headers with tuples left then go through a queue to the wave's lanes, each lane
+// running one header's probes. A slot carries a copy of its list's first record, since
+// random lines are what the search pays for.
 // Candidates come packed in the output word from the MLP (one byte per candidate, 16
 // bits above 256 tuples). Tuple spaces of more than 32 tuples use the same steps over
 // multiword tuple masks (8 words up to 256 tuples, 16 up to 512), with conflict masks in
 // a side array.
-#include <type_traits>
+#include <algorithm>
 
 #include "tang_internal.hpp"
 
@@ -26,137 +25,14 @@ namespace tang {
 namespace {
 
 constexpr uint32_t kNoTuple = 0xFFFFFFFFu;
-
-struct Best {
-    uint32_t prio, id, cmask, tuple, pos;   // pos: record index (for wide conflict masks)
-};
+// Sets of 64 headers per wave, rulesets of at most 32 tuples: four from this many headers on,
+// one below. More sets keep a wave's lanes busy longer, fewer make more waves (100,000
+// rules, one set against four: 131,072 headers 83 against 106 us, 524,288 117 against 126,
+// 1,048,576 185 against 148; 4.2M at 512k rules 389 against 290; with U = 1).
+constexpr uint32_t kQueueFrom = 3u << 18;
 
 __device__ __forceinline__ bool kless(uint32_t p1, uint32_t i1, uint32_t p2, uint32_t i2) {
     return p1 < p2 || (p1 == p2 && i1 < i2);
-}
-
-// Whole 16-byte loads. Copying the structs field by field lets the compiler split them
-// into narrow loads sunk into the branches that use each field: more load instructions
-// per wave and dependent round trips between them. An empty asm that takes all four
-// words keeps each 16-byte load whole and in place.
-__device__ __forceinline__ uint4 load16(const void* p) {
-    uint4 a = *reinterpret_cast<const uint4*>(p);
-    asm volatile("" : "+v"(a.x), "+v"(a.y), "+v"(a.z), "+v"(a.w));
-    return a;
-}
-__device__ __forceinline__ Slot load_slot(const Slot* p) {
-    const uint4 a = load16(p);
-    return Slot{a.x, a.y, a.z, a.w};
-}
-__device__ __forceinline__ uint2 load8(const uint2* p) {
-    uint2 a = *p;
-    asm volatile("" : "+v"(a.x), "+v"(a.y));
-    return a;
-}
-
-// Compares one list of records in (priority, id) order: the first match is its best;
-// the scan stops there or at the first record that cannot beat the current answer.
-// The hot half (ports, priority, protocol/lengths) decides; the cold half (prefixes,
-// id, conflict mask) is read for a priority tie, a rule held by a coarser tuple, and
-// the match.
-template <bool STATS>
-__device__ __forceinline__ void scan_list(uint32_t t, uint32_t off, uint32_t len, uint32_t sip,
-                                          uint32_t dip, uint32_t sp, uint32_t dp, uint32_t proto,
-                                          const Rec* __restrict__ recs, Best& b, uint32_t& n_recs) {
-    for (uint32_t k = 0; k < len; ++k) {
-        const uint4* p = reinterpret_cast<const uint4*>(recs + off + k);
-        const uint4 h = load16(p);  // sp, dp, prio, meta
-        if (STATS) ++n_recs;
-        if (h.z > b.prio) break;
-        const bool ok = ((uint32_t)(sp >= (h.x & 0xFFFFu)) & (uint32_t)(sp <= (h.x >> 16)) &
-                         (uint32_t)(dp >= (h.y & 0xFFFFu)) & (uint32_t)(dp <= (h.y >> 16)) &
-                         ((uint32_t)(meta_exact(h.w) == 0) | (uint32_t)(proto == meta_proto(h.w)))) != 0u;
-        if (!ok && h.z < b.prio) continue;
-        const uint4 c = load16(p + 1);  // sip, dip, id, cmask
-        if (h.z == b.prio && !(c.z < b.id)) break;
-        if (!ok) continue;
-        if (meta_check(h.w)) {
-            const uint32_t sm = pmask(meta_sl(h.w)), dm = pmask(meta_dl(h.w));
-            if (((sip ^ c.x) & sm) | ((dip ^ c.y) & dm)) continue;
-        }
-        b = Best{h.z, c.z, c.w, t, off + k};
-        break;
-    }
-}
-
-// Walks the open-addressing slots from hash h to key (tk, k0, k1); returns the slot, or
-// an empty one. The table is kept at most a third full, so an empty slot ends every
-// walk; the step bound only guards against a corrupted table.
-template <bool STATS>
-__device__ __forceinline__ Slot find_slot(uint64_t h64, uint32_t tk, uint32_t k0, uint32_t k1,
-                                          uint32_t slot_mask, const Slot* __restrict__ slots,
-                                          uint32_t& n_slots) {
-    uint32_t h = slot_of(h64) & slot_mask;
-    for (uint32_t step = 0; step <= slot_mask; ++step) {
-        const Slot s = load_slot(slots + h);
-        if (STATS) ++n_slots;
-        if (s.tl == kEmptyTL || (s.ms == k0 && s.md == k1 && (s.tl >> kTlShift) == tk)) return s;
-        h = (h + 1) & slot_mask;
-    }
-    return Slot{0, 0, kEmptyTL, 0};
-}
-
-// Searches tuple t for this header: the slot walk to the bucket, then the bucket's list,
-// or for a split bucket the sub-lists the header selects.
-template <bool STATS>
-__device__ __forceinline__ void search_tuple(uint32_t t, const TupleDev* s_t, uint32_t sip,
-                                             uint32_t dip, uint32_t sp, uint32_t dp, uint32_t proto,
-                                             uint32_t slot_mask, const Slot* __restrict__ slots,
-                                             const Rec* __restrict__ recs, Best& b,
-                                             uint32_t& n_probe, uint32_t& n_slots, uint32_t& n_recs) {
-    if (STATS) ++n_probe;
-    const uint32_t ms = sip & s_t[t].smask, md = dip & s_t[t].dmask;
-    const Slot s = find_slot<STATS>(key_hash(t, ms, md), t, ms, md, slot_mask, slots, n_slots);
-    if (s.tl == kEmptyTL) return;
-    if (!(s.off & kSplit)) {
-        scan_list<STATS>(t, s.off, s.tl & kMaxBucketLen, sip, dip, sp, dp, proto, recs, b, n_recs);
-        return;
-    }
-    // a split bucket: only the four sub-lists this header's DP, SP and protocol select
-    const uint32_t bi = s.off & ~kSplit;
-    const uint32_t keys[4][2] = {{kSubDp, dp}, {kSubSp, sp}, {kSubProto, proto}, {kSubRest, 0u}};
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const uint32_t tk = t | (keys[q][0] << kKindShift);
-        const Slot u = find_slot<STATS>(key_hash(tk, bi, keys[q][1]), tk, bi, keys[q][1], slot_mask,
-                                        slots, n_slots);
-        if (u.tl != kEmptyTL)
-            scan_list<STATS>(t, u.off, u.tl & kMaxBucketLen, sip, dip, sp, dp, proto, recs, b, n_recs);
-    }
-}
-
-// The filter block of group key gk for this header.
-__device__ __forceinline__ const uint2* block_of(const uint2* __restrict__ filter, uint32_t gk,
-                                                 uint32_t sip, uint32_t dip, uint32_t filter_mask) {
-    const uint32_t len = gk & 63u;
-    const uint32_t v = (gk & 64u ? dip : sip) & pmask(len);
-    return filter + (filter_block(gk, v) & filter_mask);
-}
-
-// Whether tuple t of group key gk may hold a bucket for this header, given its block.
-__device__ __forceinline__ bool block_has(uint2 blk, uint32_t t, uint32_t gk, const TupleDev* s_t,
-                                          uint32_t sip, uint32_t dip) {
-    const uint32_t o = gk & 64u ? (sip & s_t[t].smask) : (dip & s_t[t].dmask);
-    const uint32_t bits = filter_bits(t, o), b1 = bits & 63u, b2 = bits >> 8;
-    return ((b1 & 32u ? blk.y : blk.x) >> (b1 & 31u)) & ((b2 & 32u ? blk.y : blk.x) >> (b2 & 31u)) & 1u;
-}
-
-__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = max(v, (uint32_t)__shfl_xor(v, o, 64));
-    return v;
-}
-
-// OR of a 32-bit mask over the wave, as a wave-uniform value.
-__device__ __forceinline__ uint32_t wave_or(uint32_t v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v |= __shfl_xor(v, o, 64);
-    return __builtin_amdgcn_readfirstlane(v);
 }
 
 __device__ __forceinline__ unsigned long long wave_sum(unsigned long long v) {
@@ -165,14 +41,41 @@ __device__ __forceinline__ unsigned long long wave_sum(unsigned long long v) {
     return v;
 }
 
+// Orders a wave's own LDS accesses: one lane's writes before another lane's reads. The
+// hardware runs a wave's LDS instructions in order; this keeps the compiler from moving them.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Lanes of `m` below this one.
+__device__ __forceinline__ uint32_t lanes_below(unsigned long long m) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// A header's search state in LDS: its best answer so far (cm: the answer's conflict mask,
+// or its record position where masks are in the side array) and the tuples it still has
+// to probe (work: the mask itself, or which words of the wave's `work` rows are not zero).
+struct alignas(16) Entry {
+    uint32_t prio, id, cm, work;
+};
+
 // NW: conflict-mask words (1 for at most 32 tuples, kMaskWords for up to 256, kMaxWords
-// above). Tuple sets are NW-word bit masks (word t / 32, bit t % 32); group sets one
-// word (at most 32 groups) or two (64). The best-key prefixes stay in LDS up to 256
-// tuples; above, the one row a lane needs is read from the tuple table.
-template <bool STATS, int NW>
+// above). Tuple sets are NW-word bit masks (word t / 32, bit t % 32). R: sets of 64 headers
+// per wave. U: records of a list per step: a small batch lasts as long as its longest list
+// scan, so more records in flight pay there, until the registers cost waves.
+//
+// What bounds it (25 tuples, 512k rules, no predictor, 4.2M Zipf headers): random 128-byte
+// lines. The card serves 265 G random accesses/s that hit an L2 and 60 G that miss it, and
+// a header needs about 7.4 and 1.3 of them, together 210 of the kernel's 290 us; vector
+// issue takes about 205 us beside them. One header per lane with a slot table, its records
+// and the filter each on lines of their own (8.6 and 2.0 accesses) took 396 us, 93% of it
+// vector issue: the wave ran its probe loop as long as its busiest lane needed, 25 steps
+// where a header needs 3.3 on average.
+template <bool STATS, int NW, int R, int U>
 __global__ __launch_bounds__(256) void k_classify(const uint4* __restrict__ hdr,
                                                   uint32_t* __restrict__ out, uint32_t n,
-                                                  const Slot* __restrict__ slots,
+                                                  const SlotDev* __restrict__ slots,
                                                   const Rec* __restrict__ recs,
                                                   const uint32_t* __restrict__ cmask_rows,
                                                   const uint2* __restrict__ filter,
@@ -180,357 +83,388 @@ __global__ __launch_bounds__(256) void k_classify(const uint4* __restrict__ hdr,
                                                   StatsDev* __restrict__ st,
                                                   const uint32_t* __restrict__ live) {
     constexpr uint32_t NT = 32u * NW;
-    constexpr int NG = NW == 1 ? 32 : kMaxGroups;   // groups: at most one per tuple
-    constexpr bool PREFIX_LDS = NW <= kMaskWords;
     constexpr uint32_t CB = NW > kMaskWords ? 16u : 8u;   // bits per packed candidate
-    using GMask = typename std::conditional<NW == 1, uint32_t, unsigned long long>::type;
+    constexpr uint32_t NE = 64u * R;                      // entries per wave
     __shared__ TupleDev s_t[NT];
+    __shared__ TupleGroup s_tg[NT];
+    __shared__ uint2 s_after[NT];   // smallest best key from a tuple on
     __shared__ uint2 s_rank[NT];  // best keys in ascending order
-    __shared__ uint32_t s_prefix[PREFIX_LDS ? NT + 1 : 1][NW];
-    __shared__ uint32_t s_all[NW], s_nog[NW];
-    __shared__ uint32_t s_gid[NT];
-    __shared__ uint32_t s_gkey[NG];
-    __shared__ uint32_t s_gmask[NG][NW];
-    __shared__ uint32_t s_misc[4];
-    const int tid = threadIdx.x;
+    __shared__ uint4 s_hdr[4][NE];
+    __shared__ Entry s_ent[4][NE];
+    __shared__ uint16_t s_queue[4][NE];
+    __shared__ uint32_t s_work[4][NW > 1 ? NW : 1][NW > 1 ? NE : 1];
+    __shared__ uint32_t s_prefix[NW == 1 ? NT + 1 : 1];
+    __shared__ uint32_t s_tup[4][STATS ? NE : 1];   // the answer's tuple
+    const uint32_t tid = threadIdx.x, lane = tid & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (live) n = min(n, *live);
-    if (blockIdx.x * 256u >= n) return;   // uniform over the block (a live count below the grid)
-    for (uint32_t k = tid; k < NT; k += 256u) {
+    if (blockIdx.x * 4u * NE >= n) return;   // uniform over the block (a live count below the grid)
+    const uint32_t ntup = ttg->n, ngroups = ttg->ngroups;
+    const uint32_t slot_mask = ttg->slot_mask, filter_mask = ttg->filter_mask;
+    for (uint32_t k = tid; k < ntup; k += 256u) {
         s_t[k] = ttg->t[k];
+        s_tg[k] = ttg->tg[k];
+        s_after[k] = make_uint2(ttg->after_prio[k], ttg->after_id[k]);
         s_rank[k] = make_uint2(ttg->rank_prio[k], ttg->rank_id[k]);
-        s_gid[k] = ttg->gid[k];
     }
-    if constexpr (PREFIX_LDS)
-        for (uint32_t k = tid; k < (NT + 1) * NW; k += 256u) s_prefix[k / NW][k % NW] = ttg->prefix[k / NW][k % NW];
-    for (uint32_t k = tid; k < (uint32_t)NG * NW; k += 256u) s_gmask[k / NW][k % NW] = ttg->gmask[k / NW][k % NW];
-    if (tid < NG) s_gkey[tid] = ttg->gkey[tid];
-    if (tid < NW) {
-        s_all[tid] = ttg->all_mask[tid];
-        s_nog[tid] = ttg->nogroup[tid];
-    }
-    if (tid == 0) {
-        s_misc[0] = ttg->n;
-        s_misc[1] = ttg->ngroups;
-        s_misc[2] = ttg->slot_mask;
-        s_misc[3] = ttg->filter_mask;
-    }
+    if constexpr (NW == 1)
+        if (tid <= NT) s_prefix[tid] = ttg->prefix[tid][0];
     __syncthreads();
-    const uint32_t ntup = s_misc[0], ngroups = s_misc[1], slot_mask = s_misc[2], filter_mask = s_misc[3];
-    const uint32_t i = blockIdx.x * 256u + tid;
-    uint32_t n_probe = 0, n_slots = 0, n_recs = 0, top1 = 0, fb = 0, nm = 0, active = 0;
+    const uint32_t base = (blockIdx.x * 4u + wave) * NE;
+    const uint32_t cnt = base < n ? min(n - base, NE) : 0u;   // this wave's headers
+    uint4* const hd = s_hdr[wave];
+    Entry* const ent = s_ent[wave];
+    uint16_t* const queue = s_queue[wave];
+    uint32_t n_probe = 0, n_slots = 0, n_recs = 0, top1 = 0, fb = 0, nm = 0;
     uint32_t n_filter = 0, n_steps = 0, n_rounds = 0;
-    uint32_t sip = 0, dip = 0, sp = 0, dp = 0, proto = 0, c0 = kNoTuple;
-    uint32_t todo[NW];
+
+    // Pass 0 probes the predicted tuples, pass 1 certifies.
+    for (uint32_t pass = kcand > 0 ? 0u : 1u; pass < 2u; ++pass) {
+        uint32_t qn = 0;   // headers with tuples to probe
+#pragma unroll 1
+        for (uint32_t r = 0; r < (uint32_t)R; ++r) {
+            const uint32_t e = r * 64u + lane;
+            const bool active = e < cnt;
+            uint4 h = make_uint4(0u, 0u, 0u, 0u);
+            if (pass == 0 || kcand == 0) {
+                if (active) h = hdr[base + e];
+                hd[e] = h;
+                if (STATS) s_tup[wave][e] = kNoTuple;
+            } else {
+                h = hd[e];
+            }
+            const uint32_t sip = h.x, dip = h.y;
+            uint32_t cand = 0;
+            if (kcand > 0 && active) cand = out[base + e];
+            uint32_t work = 0;   // NW = 1: tuples to probe; else its words that are not zero
+            if (pass == 0) {
+                if constexpr (NW > 1) {
 #pragma unroll
-    for (int w = 0; w < NW; ++w) todo[w] = 0;
-    Best b{kDead, kDead, 0u, 0u, 0u};
-    // the first candidate's group block, kept for the other tuples of its group
-    uint32_t g0 = kNoGroup;
-    uint2 blk0 = make_uint2(0u, 0u);
-    if (i < n) {
-        active = 1;
-        const uint4 h = hdr[i];
-        sip = h.x;
-        dip = h.y;
-        sp = h.z & 0xFFFFu;
-        dp = h.z >> 16;
-        proto = h.w & 0xFFu;
-        bool found = false;
-        uint32_t probed[NW];
-#pragma unroll
-        for (int w = 0; w < NW; ++w) probed[w] = 0;
-        if (kcand > 0) {
-            const uint32_t cp = out[i];
-            for (int c = 0; c < kcand; ++c) {
-                const uint32_t t = (cp >> (CB * c)) & ((1u << CB) - 1u);
-                if (c == 0) c0 = t;
-                if (t >= ntup) continue;
-                uint32_t& pw = probed[NW == 1 ? 0 : t >> 5];
-                if ((pw >> (t & 31u)) & 1u) continue;
-                pw |= 1u << (t & 31u);
-                if (!kless(s_t[t].best_prio, s_t[t].best_id, b.prio, b.id)) continue;
-                const uint32_t g = s_gid[t];
-                bool pass = true;
-                if (g != kNoGroup) {
-                    const uint32_t gk = s_gkey[g];
-                    uint2 blk;
-                    if (g == g0) {
-                        blk = blk0;
-                    } else {
-                        blk = load8(block_of(filter, gk, sip, dip, filter_mask));
+                    for (int w = 0; w < NW; ++w) s_work[wave][w][e] = 0;
+                }
+                for (int c = 0; c < kcand; ++c) {
+                    const uint32_t t = (cand >> (CB * c)) & ((1u << CB) - 1u);
+                    if (!active || t >= ntup) continue;
+                    const TupleGroup tg = s_tg[t];
+                    bool pass_f = true;
+                    if (tg.gkey != kNoGroup) {
+                        const uint32_t ms = sip & s_t[t].smask, md = dip & s_t[t].dmask;
+                        const bool by_dip = (tg.gkey & 64u) != 0u;   // the group's field
+                        const uint32_t v = by_dip ? md : ms, o = by_dip ? ms : md;
+                        const uint2 blk = filter[filter_block(tg.salt, v) & filter_mask];
+                        pass_f = filter_has(blk, filter_hash(filter_salt(t), o)) >> 31;
                         if (STATS) ++n_filter;
                     }
-                    if (g0 == kNoGroup) {
-                        g0 = g;
-                        blk0 = blk;
+                    if (!pass_f) continue;
+                    if constexpr (NW == 1) {
+                        work |= 1u << t;
+                    } else {
+                        s_work[wave][t >> 5][e] |= 1u << (t & 31u);
+                        work |= 1u << (t >> 5);
                     }
-                    pass = block_has(blk, t, gk, s_t, sip, dip);
                 }
-                if (pass)
-                    search_tuple<STATS>(t, s_t, sip, dip, sp, dp, proto, slot_mask, slots, recs, b,
-                                        n_probe, n_slots, n_recs);
-            }
-            found = b.id != kDead;
-        }
-        if (NW == 1 || !found) {
-#pragma unroll
-            for (int w = 0; w < NW; ++w)
-                todo[w] = (found ? b.cmask : s_all[w]) & ~probed[w] & s_all[w];
-        } else {
-            const uint4* row = reinterpret_cast<const uint4*>(cmask_rows + (size_t)b.pos * NW);
-#pragma unroll
-            for (int q = 0; q < NW / 4; ++q) {
-                const uint4 m = row[q];
-                todo[4 * q] = m.x & ~probed[4 * q];
-                todo[4 * q + 1] = m.y & ~probed[4 * q + 1];
-                todo[4 * q + 2] = m.z & ~probed[4 * q + 2];
-                todo[4 * q + 3] = m.w & ~probed[4 * q + 3];
-            }
-        }
-        if (STATS) fb = found ? 0u : 1u;
-    }
-    // Certification. First drop the tuples whose best key cannot beat the answer: the
-    // tuples in ascending best-key order form a prefix, found by a binary search.
-    {
-        uint32_t any = 0;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) any |= todo[w];
-        if (any) {
-            uint32_t k = 0;
-#pragma unroll
-            for (uint32_t step = NT; step > 0; step >>= 1)
-                if (k + step <= ntup && kless(s_rank[k + step - 1].x, s_rank[k + step - 1].y, b.prio, b.id))
-                    k += step;
-            if constexpr (PREFIX_LDS) {
-#pragma unroll
-                for (int w = 0; w < NW; ++w) todo[w] &= s_prefix[k][w];
+                ent[e] = Entry{kDead, kDead, 0u, work};
             } else {
-                const uint4* row = reinterpret_cast<const uint4*>(ttg->prefix[k]);
+                Entry b{kDead, kDead, 0u, 0u};
+                if (kcand > 0) b = ent[e];
+                const bool found = b.id != kDead;
+                if (STATS) fb += active && !found;
+                // The certification set: the answer's conflict mask, or every tuple after a
+                // miss, without the tuples probed in pass 0 and those whose best key cannot
+                // beat the answer -- in ascending best-key order the tuples that can form a
+                // prefix, found by a binary search.
+                uint32_t k = ntup;
+                if (__ballot(found)) {
+                    k = 0;
 #pragma unroll
-                for (int q = 0; q < NW / 4; ++q) {
-                    const uint4 m = row[q];
-                    todo[4 * q] &= m.x;
-                    todo[4 * q + 1] &= m.y;
-                    todo[4 * q + 2] &= m.z;
-                    todo[4 * q + 3] &= m.w;
+                    for (uint32_t step = NT; step > 0; step >>= 1)
+                        if (k + step <= ntup && kless(s_rank[k + step - 1].x, s_rank[k + step - 1].y, b.prio, b.id))
+                            k += step;
                 }
-            }
-        }
-    }
-    // Phase 1: the groups the remaining tuples need (the first candidate's block is
-    // already here), their blocks eight at a time per lane, then each needed tuple's bit.
-    uint32_t hits[NW];
-    GMask gneed = 0;
+                uint32_t todo[NW];
+                if constexpr (NW == 1) {
+                    todo[0] = active ? (found ? b.cm : ~0u) & s_prefix[k] : 0u;
+                } else {
 #pragma unroll
-    for (int w = 0; w < NW; ++w) hits[w] = todo[w] & s_nog[w];
-    if (g0 != kNoGroup) {
+                    for (int w = 0; w < NW; ++w) todo[w] = active ? ttg->all_mask[w] : 0u;
+                    if (active && found) {
+                        const uint4* row = reinterpret_cast<const uint4*>(cmask_rows + (size_t)b.cm * NW);
+                        const uint4* pre = reinterpret_cast<const uint4*>(ttg->prefix[k]);
 #pragma unroll
-        for (int w = 0; w < NW; ++w) {
-            for (uint32_t m = todo[w] & s_gmask[g0][w]; m; m &= m - 1u) {
-                const uint32_t t = 32u * w + (uint32_t)__builtin_ctz(m);
-                if (block_has(blk0, t, s_gkey[g0], s_t, sip, dip)) hits[w] |= 1u << (t & 31u);
-            }
-        }
-    }
-    {
-        uint32_t any = 0;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) any |= todo[w];
-        if (wave_or(any)) {
-            for (uint32_t g = 0; g < ngroups; ++g) {
-                uint32_t m = 0;
-#pragma unroll
-                for (int w = 0; w < NW; ++w) m |= todo[w] & s_gmask[g][w];
-                if (m && g != g0) gneed |= (GMask)1 << g;
-            }
-        }
-    }
-    for (;;) {
-        if (!wave_or(gneed != 0 ? 1u : 0u)) break;
-        if (STATS) ++n_rounds;
-        uint32_t gq[8];
-        uint2 blk[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            gq[q] = kNoGroup;
-            blk[q] = make_uint2(0u, 0u);
-            if (gneed) {
-                const uint32_t g = NW == 1 ? (uint32_t)__builtin_ctz((uint32_t)gneed)
-                                           : (uint32_t)__builtin_ctzll((unsigned long long)gneed);
-                gneed &= gneed - 1;
-                gq[q] = g;
-                blk[q] = load8(block_of(filter, s_gkey[g], sip, dip, filter_mask));
-                if (STATS) ++n_filter;
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            if (gq[q] == kNoGroup) continue;
-            const uint32_t gk = s_gkey[gq[q]];
-#pragma unroll
-            for (int w = 0; w < NW; ++w) {
-                for (uint32_t m = todo[w] & s_gmask[gq[q]][w]; m; m &= m - 1u) {
-                    const uint32_t t = 32u * w + (uint32_t)__builtin_ctz(m);
-                    if (block_has(blk[q], t, gk, s_t, sip, dip)) hits[w] |= 1u << (t & 31u);
-                }
-            }
-        }
-    }
-    // Phase 2: each lane searches its own passing tuples in tuple order -- tuples are
-    // numbered by first appearance in priority order, so good answers come early --
-    // skipping any whose best key can no longer beat the answer. The probes run as one
-    // flat loop of loads per lane (slot, record first half, record second half; a lane
-    // between probes takes its next tuple at the top of the loop), so a wave takes as
-    // many iterations as its busiest lane issues loads in total. Probe by probe in
-    // lockstep, a wave would wait at every probe for its lane with the longest walk or
-    // bucket scan, and lanes with long scans rarely coincide.
-    uint32_t steps = 0;
-    {
-        enum : uint32_t { P_NEXT = 0, P_SLOT, P_HOT, P_COLD, P_DONE };
-        constexpr uint32_t kMain = 8;   // `sub` while walking to a tuple's main bucket
-        uint32_t ps = active ? P_NEXT : P_DONE;
-        uint32_t ct = 0, tk = 0, k0 = 0, k1 = 0, walk = 0, sub = kMain, bi = 0, left = 0;
-        uint32_t hp = 0, hm = 0, hok = 0;
-        const uint4* ld = reinterpret_cast<const uint4*>(slots);
-        for (;;) {
-            if (ps == P_NEXT) {
-                ps = P_DONE;
-#pragma unroll
-                for (int w = 0; w < NW; ++w) {
-                    while (hits[w]) {
-                        const uint32_t t = 32u * w + (uint32_t)__builtin_ctz(hits[w]);
-                        hits[w] &= hits[w] - 1u;
-                        if (kless(s_t[t].best_prio, s_t[t].best_id, b.prio, b.id)) {
-                            ct = t;
-                            ps = P_SLOT;
-                            break;
+                        for (int q = 0; q < NW / 4; ++q) {
+                            const uint4 m = row[q], p = pre[q];
+                            todo[4 * q] = m.x & p.x;
+                            todo[4 * q + 1] = m.y & p.y;
+                            todo[4 * q + 2] = m.z & p.z;
+                            todo[4 * q + 3] = m.w & p.w;
                         }
                     }
-                    if (ps == P_SLOT) break;
                 }
-                if (ps == P_SLOT) {
-                    if (STATS) ++n_probe;
-                    tk = ct;
-                    k0 = sip & s_t[ct].smask;
-                    k1 = dip & s_t[ct].dmask;
-                    sub = kMain;
-                    walk = 0;
-                    ld = reinterpret_cast<const uint4*>(slots + (slot_of(key_hash(tk, k0, k1)) & slot_mask));
+                for (int c = 0; c < kcand; ++c) {
+                    const uint32_t t = (cand >> (CB * c)) & ((1u << CB) - 1u);
+                    if constexpr (NW == 1) {
+                        if (t < ntup) todo[0] &= ~(1u << t);
+                    } else {
+#pragma unroll
+                        for (int w = 0; w < NW; ++w)
+                            if (t >> 5 == (uint32_t)w) todo[w] &= ~(1u << (t & 31u));
+                    }
+                }
+                // The filter: eight groups at a time, each lane's blocks loaded together, then
+                // each group's tuples. Groups and tuples are the same for every lane, so masks
+                // and salts are scalars and a test is a few vector instructions; a lane that
+                // does not need a group reads block 0 with the others and drops the outcome.
+                uint32_t hits = 0;
+                if constexpr (NW == 1) {
+                    hits = todo[0] & ttg->nogroup[0];
+                } else {
+#pragma unroll
+                    for (int w = 0; w < NW; ++w) s_work[wave][w][e] = todo[w] & ttg->nogroup[w];
+                }
+                for (uint32_t g0 = 0; g0 < ngroups; g0 += 8u) {
+                    uint2 blk[8];
+                    if (STATS) ++n_rounds;
+#pragma unroll
+                    for (uint32_t q = 0; q < 8u; ++q) {
+                        blk[q] = make_uint2(0u, 0u);
+                        if (g0 + q < ngroups) {
+                            const FilterGroup fg = ttg->fg[g0 + q];
+                            uint32_t need = 0;
+#pragma unroll
+                            for (int w = 0; w < NW; ++w) need |= todo[w] & ttg->gmask[g0 + q][w];
+                            const uint32_t v = (fg.dip ? dip : sip) & fg.mask;
+                            const uint32_t at = need ? filter_block(fg.salt, v) & filter_mask : 0u;
+                            blk[q] = filter[at];
+                            if (STATS) n_filter += need != 0;
+                        }
+                    }
+#pragma unroll
+                    for (uint32_t q = 0; q < 8u; ++q) {
+                        if (g0 + q < ngroups) {
+                            const FilterGroup fg = ttg->fg[g0 + q];
+                            const uint32_t ov = fg.dip ? sip : dip;
+                            for (uint32_t k = fg.begin; k < fg.end; ++k) {
+                                const FilterOp op = ttg->fop[k];
+                                const uint32_t has = filter_has(blk[q], filter_hash(op.salt, ov & op.omask));
+                                if constexpr (NW == 1) {
+                                    hits |= (has >> 31) << op.t;
+                                } else {
+                                    if (has >> 31) atomicOr(&s_work[wave][op.t >> 5][e], 1u << (op.t & 31u));
+                                }
+                            }
+                        }
+                    }
+                }
+                if constexpr (NW == 1) {
+                    work = hits & todo[0];
+                } else {
+#pragma unroll
+                    for (int w = 0; w < NW; ++w) {
+                        const uint32_t m = s_work[wave][w][e] & todo[w];
+                        s_work[wave][w][e] = m;
+                        work |= m ? 1u << w : 0u;
+                    }
+                }
+                ent[e] = Entry{b.prio, b.id, b.cm, work};
+            }
+            const unsigned long long has = __ballot(work != 0u);
+            if (work) queue[qn + lanes_below(has)] = (uint16_t)e;
+            qn += (uint32_t)__popcll(has);
+        }
+        wave_sync();
+
+        // The probe loop: each lane runs one header's probes as single steps (a slot with its
+        // bucket's first record, or a further record), its tuples in index order -- tuples are
+        // numbered by first appearance in priority order, so good answers come early --
+        // skipping any whose best key can no longer beat the answer. A lane that is done
+        // takes the next header of the queue, so the wave's lanes stay busy until the queue
+        // is empty.
+        enum : uint32_t { P_IDLE = 0, P_NEXT, P_START, P_SLOT, P_REC };
+        constexpr uint32_t kMain = 8;   // `sub` while walking to a tuple's main bucket
+        uint32_t taken = 0;
+        uint32_t ps = P_IDLE, e = 0, sip = 0, dip = 0, ports = 0, proto = 0;
+        uint32_t bp = kDead, bid = kDead, bcm = 0;   // the lane's header's best
+        uint32_t cur = 0, word = 0, nz = 0;   // tuples left (of mask word `word`), words left
+        uint32_t ct = 0, tk = 0, k0 = 0, k1 = 0, sub = kMain, bi = 0, left = 0;
+        uint32_t at = 0, walk = 0;   // slot or record index; steps of the slot walk
+        for (;;) {
+            const unsigned long long idle = __ballot(ps == P_IDLE);
+            if (idle && taken < qn) {
+                const uint32_t q = taken + lanes_below(idle);
+                if (ps == P_IDLE && q < qn) {
+                    e = queue[q];
+                    const uint4 h = hd[e];
+                    const Entry b = ent[e];
+                    sip = h.x;
+                    dip = h.y;
+                    ports = h.z;
+                    proto = h.w & 0xFFu;
+                    bp = b.prio;
+                    bid = b.id;
+                    bcm = b.cm;
+                    if constexpr (NW == 1) {
+                        cur = b.work;
+                    } else {
+                        cur = 0;
+                        nz = b.work;
+                    }
+                    ps = P_NEXT;
+                }
+                taken = min(qn, taken + (uint32_t)__popcll(idle));
+            }
+            if (ps == P_NEXT) {
+                ps = P_IDLE;
+                for (;;) {
+                    if constexpr (NW > 1) {
+                        if (!cur && nz) {
+                            word = (uint32_t)__builtin_ctz(nz);
+                            nz &= nz - 1u;
+                            cur = s_work[wave][word][e];
+                        }
+                    }
+                    if (!cur) break;
+                    const uint32_t t = 32u * word + (uint32_t)__builtin_ctz(cur);
+                    cur &= cur - 1u;
+                    const uint2 after = s_after[t];
+                    if (!kless(after.x, after.y, bp, bid)) {   // nor any later tuple
+                        cur = 0;
+                        nz = 0;
+                        break;
+                    }
+                    const TupleDev td = s_t[t];
+                    if (kless(td.best_prio, td.best_id, bp, bid)) {
+                        ct = t;
+                        tk = t;
+                        k0 = sip & td.smask;
+                        k1 = dip & td.dmask;
+                        sub = kMain;
+                        ps = P_START;
+                        if (STATS) ++n_probe;
+                        break;
+                    }
+                }
+                if (ps == P_IDLE) ent[e] = Entry{bp, bid, bcm, 0u};   // nothing left to probe
+            }
+            if (!__ballot(ps != P_IDLE)) {
+                if (taken >= qn) break;
+                continue;
+            }
+            if (STATS) ++n_steps;
+            if (ps == P_START) {
+                at = key_hash(tk, k0, k1) & slot_mask;
+                walk = 0;
+                ps = P_SLOT;
+            }
+            // one step's loads: the slot (its key and its bucket's first record share a
+            // 64-byte line) or the next U records of the list
+            uint4 a = make_uint4(0u, 0u, 0u, 0u), b = a, c = a;
+            uint4 xb[U], xc[U];
+            const bool rec = ps == P_REC;
+            if (ps != P_IDLE) {
+                const uint4* p = rec ? reinterpret_cast<const uint4*>(recs + at)
+                                     : reinterpret_cast<const uint4*>(slots + at) + 1;
+                if (!rec) a = p[-1];
+                b = p[0];   // sp, dp, prio, meta
+                c = p[1];   // sip, dip, id, cmask
+                if (rec) {
+#pragma unroll
+                    for (uint32_t j = 1; j < (uint32_t)U; ++j) {
+                        const uint32_t k = min(j, left - 1u);   // the list's last record past its end
+                        xb[j] = p[2u * k];
+                        xc[j] = p[2u * k + 1u];
+                    }
                 }
             }
-            if (!__ballot(ps != P_DONE)) break;
-            if (STATS && ps != P_DONE) ++steps;
-            uint4 v = make_uint4(0u, 0u, 0u, 0u);
-            if (ps != P_DONE) v = load16(ld);
-            bool list_done = false;
+            // Records are in (priority, id) order: the first match is the list's best, and the
+            // list ends at the first record that cannot beat the answer.
+            const uint32_t sp = ports & 0xFFFFu, dp = ports >> 16;
+            auto test = [&](const uint4& b, const uint4& c) {
+                if (STATS) ++n_recs;
+                bool ok = ((uint32_t)(sp >= (b.x & 0xFFFFu)) & (uint32_t)(sp <= (b.x >> 16)) &
+                           (uint32_t)(dp >= (b.y & 0xFFFFu)) & (uint32_t)(dp <= (b.y >> 16)) &
+                           ((uint32_t)(meta_exact(b.w) == 0) | (uint32_t)(proto == meta_proto(b.w)))) != 0u;
+                const bool better = kless(b.z, c.z, bp, bid);
+                if (ok && better && meta_check(b.w))   // held by a coarser tuple: its own prefixes
+                    ok = (((sip ^ c.x) & pmask(meta_sl(b.w))) | ((dip ^ c.y) & pmask(meta_dl(b.w)))) == 0u;
+                if (ok && better) {
+                    bp = b.z;
+                    bid = c.z;
+                    bcm = NW == 1 ? c.w : at;
+                    if (STATS) s_tup[wave][e] = ct;
+                }
+                ++at;
+                --left;
+                return ok || !better || left == 0;
+            };
+            bool first = rec, done = false;
             if (ps == P_SLOT) {
                 if (STATS) ++n_slots;
-                if (v.z == kEmptyTL) {
-                    list_done = true;
-                } else if (v.x == k0 && v.y == k1 && (v.z >> kTlShift) == tk) {
-                    if (sub == kMain && (v.w & kSplit)) {
-                        bi = v.w & ~kSplit;   // a split bucket: the sub-lists the header selects
+                if (a.z == kEmptyTL) {
+                    done = true;
+                } else if (a.x == k0 && a.y == k1 && (a.z >> kTlShift) == tk) {
+                    left = a.z & kMaxBucketLen;
+                    if (a.w & kSplit) {   // a split bucket: the sub-lists the header selects
+                        bi = a.w & ~kSplit;
                         sub = 0;
-                        list_done = true;
-                    } else if ((v.z & kMaxBucketLen) == 0) {
-                        list_done = true;
+                        done = true;
                     } else {
-                        left = (v.z & kMaxBucketLen) - 1u;
-                        ps = P_HOT;
-                        ld = reinterpret_cast<const uint4*>(recs + v.w);
+                        at = a.w;
+                        ps = P_REC;
+                        first = left != 0;
+                        done = !first;
                     }
-                } else if (++walk > slot_mask) {
-                    list_done = true;   // only a corrupted table has no empty slot
                 } else {
-                    const uint32_t h = (uint32_t)(reinterpret_cast<const Slot*>(ld) - slots);
-                    ld = reinterpret_cast<const uint4*>(slots + ((h + 1u) & slot_mask));
-                }
-            } else if (ps == P_HOT) {
-                if (STATS) ++n_recs;
-                if (v.z > b.prio) {
-                    list_done = true;   // this and every later record cannot beat the answer
-                } else {
-                    const bool ok = ((uint32_t)(sp >= (v.x & 0xFFFFu)) & (uint32_t)(sp <= (v.x >> 16)) &
-                                     (uint32_t)(dp >= (v.y & 0xFFFFu)) & (uint32_t)(dp <= (v.y >> 16)) &
-                                     ((uint32_t)(meta_exact(v.w) == 0) |
-                                      (uint32_t)(proto == meta_proto(v.w)))) != 0u;
-                    if (!ok && v.z < b.prio) {
-                        if (left) {
-                            --left;
-                            ld += 2;
-                        } else {
-                            list_done = true;
-                        }
-                    } else {
-                        hp = v.z;
-                        hm = v.w;
-                        hok = ok ? 1u : 0u;
-                        ps = P_COLD;
-                        ld += 1;
-                    }
-                }
-            } else if (ps == P_COLD) {
-                bool next = false;
-                if (hp == b.prio && !(v.z < b.id)) {
-                    list_done = true;
-                } else if (!hok) {
-                    next = true;
-                } else if (meta_check(hm) && ((((sip ^ v.x) & pmask(meta_sl(hm))) |
-                                               ((dip ^ v.y) & pmask(meta_dl(hm)))) != 0u)) {
-                    next = true;
-                } else {
-                    b = Best{hp, v.z, v.w, ct, (uint32_t)(reinterpret_cast<const Rec*>(ld - 1) - recs)};
-                    list_done = true;
-                }
-                if (next) {
-                    if (left) {
-                        --left;
-                        ps = P_HOT;
-                        ld += 1;
-                    } else {
-                        list_done = true;
-                    }
+                    at = (at + 1u) & slot_mask;
+                    done = ++walk > slot_mask;   // only a corrupted table has no empty slot
                 }
             }
-            if (list_done) {
+            if (first) done = test(b, c);
+            if constexpr (U > 1) {
+#pragma unroll
+                for (uint32_t j = 1; j < (uint32_t)U; ++j)
+                    if (rec && !done) done = test(xb[j], xc[j]);
+            }
+            if (done) {
                 if (sub < 4u) {
                     // the next sub-list of a split bucket
                     const uint32_t kind = sub == 0 ? kSubDp : sub == 1 ? kSubSp : sub == 2 ? kSubProto : kSubRest;
-                    const uint32_t val = sub == 0 ? dp : sub == 1 ? sp : sub == 2 ? proto : 0u;
+                    k1 = sub == 0 ? ports >> 16 : sub == 1 ? ports & 0xFFFFu : sub == 2 ? proto : 0u;
                     ++sub;
                     tk = ct | (kind << kKindShift);
                     k0 = bi;
-                    k1 = val;
-                    walk = 0;
-                    ps = P_SLOT;
-                    ld = reinterpret_cast<const uint4*>(slots + (slot_of(key_hash(tk, k0, k1)) & slot_mask));
-                } else {
+                    ps = P_START;
+                } else if (cur | nz) {
                     ps = P_NEXT;
+                } else {
+                    ps = P_IDLE;
+                    ent[e] = Entry{bp, bid, bcm, 0u};
                 }
             }
         }
+        wave_sync();
     }
-    if (STATS) n_steps = wave_max(steps);
-    if (active) {
-        const bool found = b.id != kDead;
-        out[i] = found ? b.id : TANG_NO_MATCH;
+#pragma unroll 1
+    for (uint32_t e = lane; e < cnt; e += 64u) {
+        const uint32_t id = ent[e].id;
         if (STATS) {
-            top1 = (found && b.tuple == c0) ? 1u : 0u;
-            nm = found ? 0u : 1u;
+            nm += id == kDead;
+            if (kcand > 0 && id != kDead) top1 += s_tup[wave][e] == (out[base + e] & ((1u << CB) - 1u));
         }
+        out[base + e] = id == kDead ? TANG_NO_MATCH : id;
     }
     if (STATS) {
         // wave sums -> block sums in LDS -> one set of atomics per block, spread over
-        // kStatCopies counter copies (summed on the host) to avoid one hot address
+        // kStatCopies counter copies (summed on the host) to avoid one hot address.
+        // Steps and rounds are a wave's own counts, shared out over 64 headers.
         constexpr int NS = 10;
         __shared__ unsigned long long s_red[4][NS];
-        unsigned long long v[NS] = {active, n_probe, n_slots, n_recs, top1, fb, nm, n_filter,
-                                    active ? n_steps : 0u, active ? n_rounds : 0u};
+        unsigned long long v[NS] = {lane == 0 ? cnt : 0u, n_probe, n_slots, n_recs, top1, fb, nm, n_filter,
+                                    n_steps, n_rounds};
 #pragma unroll
         for (int q = 0; q < NS; ++q) v[q] = wave_sum(v[q]);
-        if ((tid & 63) == 0)
+        if (lane == 0)
 #pragma unroll
-            for (int q = 0; q < NS; ++q) s_red[tid >> 6][q] = v[q];
+            for (int q = 0; q < NS; ++q) s_red[wave][q] = v[q];
         __syncthreads();
         if (tid < NS) {
             const unsigned long long sum = s_red[0][tid] + s_red[1][tid] + s_red[2][tid] + s_red[3][tid];
@@ -548,22 +482,30 @@ hipError_t launch_classify(const tang_ruleset_t* rs, const tang_header_t* d_hdr,
     if (d_live && n > chunk) return hipErrorInvalidValue;
     for (size_t base = 0; base < n; base += chunk) {
         const uint32_t m = (uint32_t)std::min(chunk, n - base);
-        const dim3 grid((m + 255) / 256), block(256);
         const uint4* h = reinterpret_cast<const uint4*>(d_hdr) + base;
-        auto go = [&](auto kern) {
-            hipLaunchKernelGGL(kern, grid, block, 0, s, h, d_out + base, m, rs->d_slots, rs->d_recs,
-                               rs->d_cmask, reinterpret_cast<const uint2*>(rs->d_filter), rs->d_tt,
-                               kcand, rs->d_stats, d_live);
+        auto go = [&](auto kern, uint32_t sets) {
+            const uint32_t per_block = 256u * sets;
+            hipLaunchKernelGGL(kern, dim3((m + per_block - 1) / per_block), dim3(256), 0, s, h, d_out + base, m,
+                               rs->d_slots, rs->d_recs, rs->d_cmask,
+                               reinterpret_cast<const uint2*>(rs->d_filter), rs->d_tt, kcand, rs->d_stats,
+                               d_live);
         };
+        // Records per step (100,000 rules; U = 1, 2, 4, 8): 65,536 headers 75, 66, 56, 57 us; 5M
+        // with four sets 933 (U = 1) against 900 (2); 144 tuples, 1M 230, 223, 251, 339; 387
+        // tuples, 1M 829, 838, 854, 944.
+        // Wider rulesets take one set: two need 44 and 71 KB of LDS per workgroup, and the
+        // waves lost cost more than the fuller lanes give (144 tuples, 2.1M headers: 387
+        // against 476 us; 387 tuples, 1M: 884 against 977).
         if (rs->nw == 1) {
-            if (stats) go(k_classify<true, 1>);
-            else go(k_classify<false, 1>);
+            if (stats) go(k_classify<true, 1, 4, 2>, 4);
+            else if (m >= kQueueFrom) go(k_classify<false, 1, 4, 2>, 4);
+            else go(k_classify<false, 1, 1, 4>, 1);
         } else if (rs->nw == kMaskWords) {
-            if (stats) go(k_classify<true, kMaskWords>);
-            else go(k_classify<false, kMaskWords>);
+            if (stats) go(k_classify<true, kMaskWords, 1, 2>, 1);
+            else go(k_classify<false, kMaskWords, 1, 2>, 1);
         } else {
-            if (stats) go(k_classify<true, kMaxWords>);
-            else go(k_classify<false, kMaxWords>);
+            if (stats) go(k_classify<true, kMaxWords, 1, 1>, 1);
+            else go(k_classify<false, kMaxWords, 1, 1>, 1);
         }
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;

@@ -67,7 +67,7 @@ extern "C" int tang_classify_host_noalloc(tang_ruleset_t* rs, const tang_header_
         // search, so nothing in the staging area needs clearing between calls. Calls that
         // overlap on one GPU share this area and race.
         TANG_HIP(hipMemcpy(dh, hdr, n * sizeof(tang_header_t), hipMemcpyHostToDevice));
-        rc = classify_async(rs, dh, dout, n, nullptr, stats, false);
+        rc = classify_async(rs, dh, dout, n, nullptr, stats);
         if (rc) return rc;
         TANG_HIP(hipMemcpy(rule_id, dout, n * sizeof(uint32_t), hipMemcpyDeviceToHost));
         return TANG_OK;

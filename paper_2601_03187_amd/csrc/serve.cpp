@@ -362,14 +362,14 @@ int tang_server_s::graph_for(uint32_t tag, tang_ruleset_t* rs, uint32_t cls, uin
 int tang_server_s::run_batch(tang_ruleset_t* rs, StreamSlot& s, size_t cap, bool live_count,
                              bool staged) {
     // a copy-engine batch's graph is the classification alone (its copies are issued around it)
-    if (!staged) return classify_async(rs, s.d_hdr(), s.d_out, cap, s.stream, nullptr, false, s.d_live());
+    if (!staged) return classify_async(rs, s.d_hdr(), s.d_out, cap, s.stream, nullptr, s.d_live());
     const uint32_t c = (uint32_t)cap;   // cap <= max_batch, a 32-bit value
     constexpr uint32_t in_blk = kInPerThread * kStageThreads, out_blk = kOutPerThread * kStageThreads;
     hipLaunchKernelGGL(k_stage_in, dim3((c + in_blk - 1) / in_blk), dim3(kStageThreads),
                        0, s.stream, reinterpret_cast<const uint4*>(s.dh_buf),
                        reinterpret_cast<uint4*>(s.d_buf), c);
     TANG_HIP(hipGetLastError());
-    int rc = classify_async(rs, s.d_hdr(), s.d_out, cap, s.stream, nullptr, false,
+    int rc = classify_async(rs, s.d_hdr(), s.d_out, cap, s.stream, nullptr,
                             live_count ? s.d_live() : nullptr);
     if (rc) return rc;
     hipLaunchKernelGGL(k_stage_out, dim3((c + out_blk - 1) / out_blk),
@@ -433,7 +433,7 @@ bool tang_server_s::prepare(uint32_t tag, tang_ruleset_t* rs, bool warm) {
     if (!cfg.use_graphs || rs->model.kind != 0) return true;
     StreamSlot& s0 = slots[0];
     if (!warm) {
-        if (classify_async(rs, s0.d_hdr(), s0.d_out, 32, s0.stream, nullptr, false) != TANG_OK) return true;
+        if (classify_async(rs, s0.d_hdr(), s0.d_out, 32, s0.stream, nullptr) != TANG_OK) return true;
         if (hipStreamSynchronize(s0.stream) != hipSuccess) return true;
         std::lock_guard<std::mutex> g(mu);
         warmed[tag] = 1;

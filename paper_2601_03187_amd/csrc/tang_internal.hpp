@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cstddef>
 #include <cstdint>
 #include <cstring>
 #include <memory>
@@ -82,6 +83,16 @@ struct alignas(16) Rec {
 };
 constexpr uint32_t kDead = 0xFFFFFFFFu;
 
+// A slot on the device (64 B): the slot and a copy of its list's first record, so that a
+// probe costs one line where it took one for the slot and one for the record. Most lists
+// hold one rule. The copy is refreshed whenever the slot, the record or (rulesets of at
+// most 32 tuples) the record's conflict mask changes.
+struct alignas(64) SlotDev {
+    Slot s;
+    Rec first;
+    uint32_t pad[4];
+};
+
 __host__ __device__ inline uint32_t meta_pack(uint32_t sl, uint32_t dl, uint32_t proto,
                                               uint32_t exact, uint32_t tuple, uint32_t check) {
     return proto | (exact << 8) | (check << 9) | (sl << 10) | (dl << 16) | (tuple << 22);
@@ -108,44 +119,58 @@ struct TupleDev {
 // possible key always has a bucket, has none. At most 64 groups (32 lengths per field).
 constexpr int kMaxGroups = 64;
 constexpr uint32_t kNoGroup = 0xFFu;
+// A group and its tuples as the filter reads them (one scalar load each): the group's own
+// field (dip: 0 SIP, 1 DIP) and its mask and salt, and its range of FilterOps; a tuple's
+// mask on the other field and its salt.
+struct alignas(32) FilterGroup {
+    uint32_t dip, mask, salt, begin, end, pad[3];
+};
+struct alignas(16) FilterOp {
+    uint32_t omask, salt, t, pad;
+};
+// A tuple's group for a lane that tests one tuple of its own: key (kNoGroup: none) and salt.
+struct alignas(8) TupleGroup {
+    uint32_t gkey, salt;
+};
 struct TupleTable {
     TupleDev t[TANG_MAX_TUPLES];
-    uint16_t order[TANG_MAX_TUPLES]; // tuple indices by ascending best key
     uint32_t rank_prio[TANG_MAX_TUPLES], rank_id[TANG_MAX_TUPLES];  // best keys in that order
-    // prefix[k]: the k tuples of lowest best key, as mask words
-    uint32_t prefix[TANG_MAX_TUPLES + 1][kMaxWords];
     uint32_t n;                       // number of tuples
     uint32_t all_mask[kMaxWords];     // bits of all tuples
     uint32_t slot_mask;               // slots - 1
     uint32_t filter_mask;             // filter blocks - 1
     uint32_t nw;                      // mask words of this ruleset (1, kMaskWords or kMaxWords)
-    uint8_t gid[TANG_MAX_TUPLES];     // filter group of each tuple (kNoGroup: none)
+    TupleGroup tg[TANG_MAX_TUPLES];
+    // smallest best key among tuples t, t + 1, ...: a probe in tuple order stops there once
+    // its answer is better
+    uint32_t after_prio[TANG_MAX_TUPLES], after_id[TANG_MAX_TUPLES];
     uint32_t ngroups;
     uint32_t gkey[kMaxGroups];        // side (bit 6: 1 = DIP) | prefix length (bits 0-5)
     uint32_t gmask[kMaxGroups][kMaxWords];  // tuples of each group
     uint32_t nogroup[kMaxWords];      // tuples without a group (always pass)
+    FilterGroup fg[kMaxGroups];
+    FilterOp fop[TANG_MAX_TUPLES];
+    // prefix[k]: the k tuples of lowest best key, as mask words; rows past n are not copied
+    // to the device
+    uint32_t prefix[TANG_MAX_TUPLES + 1][kMaxWords];
 };
+inline size_t tuple_table_bytes(const TupleTable& tt) {
+    return offsetof(TupleTable, prefix) + (tt.n + 1) * sizeof tt.prefix[0];
+}
 
-// Key hash: two chained MurmurHash3 32-bit finalisers (fmix32, Appleby, public domain),
-// first over the masked SIP salted by the tuple index, then over that result xor the
-// masked DIP. Each stage is a bijection, so structured keys (prefixes whose only varying
-// bits are the top byte) do not collapse. The low half of the result picks the slot.
-// The bucket filter uses its own cheaper hashes (filter_block / filter_bits below).
-__host__ __device__ inline uint32_t fmix32(uint32_t h) {
-    h ^= h >> 16;
-    h *= 0x85EBCA6Bu;
-    h ^= h >> 13;
-    h *= 0xC2B2AE35u;
-    h ^= h >> 16;
-    return h;
+// Key hash: the masked SIP salted by the tuple key, multiplied and folded, then the masked
+// DIP, multiplied and folded twice (each stage a bijection, so structured keys -- prefixes
+// whose only varying bits are the top byte -- do not collapse). The low bits pick the slot;
+// the slot stores the full key, so answers never depend on the hash.
+// The bucket filter uses its own hashes (filter_block / filter_hash below).
+__host__ __device__ inline uint32_t key_hash(uint32_t t, uint32_t ms, uint32_t md) {
+    uint32_t x = (ms ^ (t + 1u) * 0x9E3779B9u) * 0x85EBCA6Bu;
+    x ^= x >> 15;
+    x = (x ^ md) * 0xC2B2AE35u;
+    x ^= x >> 15;
+    x *= 0x2C1B3C6Du;
+    return x ^ (x >> 16);
 }
-__host__ __device__ inline uint64_t key_hash(uint32_t t, uint32_t ms, uint32_t md) {
-    const uint32_t h = fmix32(fmix32(ms + (t + 1u) * 0x9E3779B9u) ^ md);
-    uint32_t f = (h ^ (h >> 15)) * 0x2C1B3C6Du;
-    f ^= f >> 12;
-    return ((uint64_t)f << 32) | h;
-}
-__host__ __device__ inline uint32_t slot_of(uint64_t h) { return (uint32_t)h; }
 // Bucket filter, blocked by prefix group. A main bucket (t, ms, md) of a tuple with
 // lengths (ls, ld) belongs to the tuple's filter group: the SIP group of length ls when
 // ls >= ld, else the DIP group of length ld. The group value v (ms or md) picks one
@@ -157,18 +182,24 @@ __host__ __device__ inline uint32_t slot_of(uint64_t h) { return (uint32_t)h; }
 // lengths per field), where a bit per tuple took one load each. A clear bit means no
 // bucket; a set pair may be a collision, which only costs a slot walk. Placement never
 // affects answers.
-__host__ __device__ inline uint32_t filter_block(uint32_t gkey, uint32_t v) {
-    uint32_t x = v ^ ((gkey + 1u) * 0x9E3779B9u);
+__host__ __device__ inline uint32_t filter_block(uint32_t salt, uint32_t v) {
+    uint32_t x = v ^ salt;
     x *= 0x85EBCA6Bu;
     x ^= x >> 15;
     x *= 0xC2B2AE35u;
     x ^= x >> 16;
     return x;
 }
-// The two bit positions (0..63) in bits 0-5 and 8-13.
-__host__ __device__ inline uint32_t filter_bits(uint32_t t, uint32_t o) {
-    const uint32_t h = (o ^ ((t + 1u) * 0x7FEB352Du)) * 0x846CA68Bu;
-    return (h >> 26) | (((h >> 18) & 63u) << 8);
+__host__ __device__ inline uint32_t group_salt(uint32_t gkey) { return (gkey + 1u) * 0x9E3779B9u; }
+__host__ __device__ inline uint32_t filter_salt(uint32_t t) { return (t + 1u) * 0x7FEB352Du; }
+__host__ __device__ inline uint32_t filter_hash(uint32_t salt, uint32_t o) { return (o ^ salt) * 0x846CA68Bu; }
+// One bit in each half of the block, counted from the top: shifting each half left by its
+// position brings the bit to the sign, so a test is two shifts and an AND. Bit 31 of the
+// result: set in both halves.
+__host__ __device__ inline uint32_t filter_pos_x(uint32_t h) { return h >> 27; }
+__host__ __device__ inline uint32_t filter_pos_y(uint32_t h) { return (h >> 22) & 31u; }
+__device__ inline uint32_t filter_has(uint2 blk, uint32_t h) {
+    return (blk.x << filter_pos_x(h)) & (blk.y << filter_pos_y(h));
 }
 __host__ __device__ inline uint32_t group_key_of(uint32_t ls, uint32_t ld) {
     return ls >= ld ? ls : (64u | ld);
@@ -262,12 +293,13 @@ struct tang_ruleset_s {
     std::vector<Bucket> buckets;
     std::unordered_map<BKey, uint32_t, BKeyHash> bucket_of;
     std::vector<tang::Slot> slots;                 // host mirror of the slot table
-    std::vector<uint32_t> filter;                  // host mirror of the bucket filter (2 words per block)
+    uint32_t filter_blocks = 0;                    // size of the bucket filter (device only)
     uint32_t rec_used = 0, rec_cap = 0;
     uint32_t nw = 1;   // conflict-mask words per rule (fixed at build: words_for(tuples))
 
     // device state
-    tang::Slot* d_slots = nullptr;
+    tang::SlotDev* d_slots = nullptr;
+    uint32_t* d_back = nullptr;    // nw = 1: slot index + 1 of a list's first record, else 0
     uint32_t* d_filter = nullptr;
     tang::Rec* d_recs = nullptr;
     uint32_t* d_cmask = nullptr;   // nw > 1: nw words per record position
@@ -277,11 +309,6 @@ struct tang_ruleset_s {
     tang::ModelDev model;
     std::mutex stats_mu;
     mutable std::mutex ws_mu;  // enqueueing of residual-model launches (shared workspace)
-    // Chunked classify: the searches of a large batch run on this stream (created on first
-    // use, default priority), each after its chunk's model on the caller's stream.
-    std::mutex pipe_mu;
-    hipStream_t pipe_stream = nullptr;
-    std::vector<hipEvent_t> pipe_events;
     uint64_t version = 0;   // bumped by every change that captured launches depend on
     bool failed = false;    // an update's device flush failed: host and device disagree
 
@@ -330,32 +357,32 @@ hipError_t launch_classify(const tang_ruleset_t* rs, const tang_header_t* d_hdr,
 hipError_t launch_conflict_build(const BoxDev* d_boxes, size_t n, Rec* d_recs, uint32_t* d_cmask,
                                  uint32_t nw, const uint32_t* all_mask,
                                  hipStream_t s);
+// back, slots (nw = 1): the mask copies in the slots of records that are their list's first.
 hipError_t launch_conflict_update(Rec* d_recs, uint32_t* d_cmask, uint32_t nw, uint32_t rec_used,
-                                  const uint32_t* d_new_pos, uint32_t n_new, hipStream_t s);
+                                  const uint32_t* d_new_pos, uint32_t n_new, const uint32_t* d_back,
+                                  SlotDev* d_slots, hipStream_t s);
+// Clears `back` (nw = 1) at every destination.
 hipError_t launch_move_records(Rec* d_recs, const Rec* d_src_recs, const uint32_t* d_src,
-                               const uint32_t* d_dst, uint32_t n, Rec* d_stage, hipStream_t s);
+                               const uint32_t* d_dst, uint32_t n, Rec* d_stage, uint32_t* d_back,
+                               hipStream_t s);
 // nw > 1: the mask rows move with their records (the same src / dst lists; new sources
 // get zero rows), through a stage of n rows.
 hipError_t launch_move_masks(uint32_t* d_cmask, uint32_t nw, const uint32_t* d_src,
                              const uint32_t* d_dst, uint32_t n, uint32_t* d_stage, hipStream_t s);
-hipError_t launch_scatter_slots(Slot* d_slots, const uint32_t* d_idx, const Slot* d_val,
-                                uint32_t n, hipStream_t s);
-// Batches of at least two chunks of this many headers, with a BF16 or FP8 model and no
-// stats, are classified chunk by chunk with the model and the search on two streams.
-constexpr size_t kPipeChunk = (size_t)1 << 21;
+// Writes slots with their first records and sets `back` (nw = 1) and the filter bits of
+// main buckets: slot d_idx[i] = d_val[i], or slot i without d_idx.
+hipError_t launch_fill_slots(SlotDev* d_slots, const uint32_t* d_idx, const Slot* d_val, uint32_t n,
+                             const Rec* d_recs, uint32_t* d_back, uint32_t* d_filter,
+                             const TupleTable* d_tt, hipStream_t s);
 // Largest batch of tang_classify_host_noalloc (its static staging: 5 MiB per GPU).
 constexpr size_t kNoAllocMaxHeaders = (size_t)1 << 18;
-// tang_classify's body; allow_chunks = false keeps every launch on stream s (for callers
-// that capture the launches into a graph).
+// tang_classify's body; every launch is on stream s (callers may be capturing it).
 // d_live: as for launch_classify (with a plain MLP or no model; not with stats).
 int classify_async(tang_ruleset_t* rs, const tang_header_t* d_hdr, uint32_t* d_rule_id, size_t n,
-                   hipStream_t s, tang_stats_t* stats, bool allow_chunks,
-                   const uint32_t* d_live = nullptr);
-// beside_search: the launch overlaps a search on another stream (the chunked classify),
-// so the predictor leaves room on every SIMD for search waves.
+                   hipStream_t s, tang_stats_t* stats, const uint32_t* d_live = nullptr);
 hipError_t launch_mlp(const tang_ruleset_t* rs, const tang_header_t* d_hdr, size_t n,
                       uint32_t* d_cand_packed, float* d_logits, uint16_t* d_cand16,
-                      hipStream_t s, bool beside_search = false, const uint32_t* d_live = nullptr);
+                      hipStream_t s, const uint32_t* d_live = nullptr);
 int search_host(const tang_ruleset_t* rs, const tang_header_t* hdr, const uint32_t* cand,
                 uint32_t* out, size_t n, uint32_t kcand, uint32_t threads, bool exact,
                 tang_stats_t* stats);

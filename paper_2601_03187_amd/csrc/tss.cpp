@@ -27,7 +27,7 @@ Slot slot_value(const tang_ruleset_t* rs, uint32_t b) {
 // Linear probing from the hash position to the first empty slot.
 uint32_t slot_insert(std::vector<Slot>& slots, const Slot& v) {
     uint32_t mask = (uint32_t)slots.size() - 1;
-    uint32_t h = slot_of(key_hash(v.tl >> kTlShift, v.ms, v.md)) & mask;
+    uint32_t h = key_hash(v.tl >> kTlShift, v.ms, v.md) & mask;
     while (slots[h].tl != kEmptyTL) h = (h + 1) & mask;
     slots[h] = v;
     return h;
@@ -75,28 +75,15 @@ std::vector<uint32_t> split_bucket(tang_ruleset_t* rs, uint32_t b) {
     return touched;
 }
 
-// The filter bit of a main bucket: in the block its group value picks (tuple (0, 0)
-// has no group: its one possible key always has a bucket).
-void filter_add(tang_ruleset_t* rs, const tang_ruleset_t::Bucket& bk) {
-    const uint32_t ls = rs->sigs[bk.t].first, ld = rs->sigs[bk.t].second;
-    if (ls == 0 && ld == 0) return;
-    const uint32_t gk = group_key_of(ls, ld);
-    const uint32_t v = gk & 64u ? bk.md : bk.ms, o = gk & 64u ? bk.ms : bk.md;
-    const uint32_t blocks = (uint32_t)rs->filter.size() / 2;
-    const uint32_t blk = filter_block(gk, v) & (blocks - 1u), bits = filter_bits(bk.t, o);
-    for (uint32_t bit : {bits & 63u, bits >> 8}) rs->filter[2 * blk + (bit >> 5)] |= 1u << (bit & 31u);
-}
-
-// Slot table at load <= 1/4 (short walks) and the bucket filter at >= 32 bits per bucket
-// (blocks of 64 bits).
+// Slot table at load <= 1/4 (short walks) and the size of the bucket filter, >= 32 bits per
+// bucket (blocks of 64 bits); the device sets the filter's bits from the slots.
 void rebuild_slots(tang_ruleset_t* rs) {
     const uint64_t nb = rs->buckets.size();
     rs->slots.assign(next_pow2(std::max<uint64_t>(1024, 4 * nb + 4)), Slot{0, 0, kEmptyTL, 0});
-    rs->filter.assign(2 * (uint64_t)next_pow2(std::max<uint64_t>(1024, (nb + 1) / 2)), 0u);
+    rs->filter_blocks = next_pow2(std::max<uint64_t>(1024, (nb + 1) / 2));
     for (uint32_t b = 0; b < rs->buckets.size(); ++b) {
         auto& bk = rs->buckets[b];
         bk.slot = slot_insert(rs->slots, slot_value(rs, b));
-        if (is_main(bk)) filter_add(rs, bk);
     }
 }
 
@@ -171,12 +158,17 @@ TupleTable make_tuple_table(const tang_ruleset_t* rs) {
         tt.t[t].best_prio = (uint32_t)(rs->tuple_best[t] >> 32);
         tt.t[t].best_id = (uint32_t)rs->tuple_best[t];
     }
+    uint64_t after = ~0ull;
+    for (uint32_t t = n; t-- > 0;) {
+        after = std::min(after, rs->tuple_best[t]);
+        tt.after_prio[t] = (uint32_t)(after >> 32);
+        tt.after_id[t] = (uint32_t)after;
+    }
     std::vector<uint32_t> ord(n);
     std::iota(ord.begin(), ord.end(), 0u);
     std::stable_sort(ord.begin(), ord.end(),
                      [&](uint32_t a, uint32_t b) { return rs->tuple_best[a] < rs->tuple_best[b]; });
     for (uint32_t i = 0; i < n; ++i) {
-        tt.order[i] = (uint16_t)ord[i];
         tt.rank_prio[i] = (uint32_t)(rs->tuple_best[ord[i]] >> 32);
         tt.rank_id[i] = (uint32_t)rs->tuple_best[ord[i]];
         for (int w = 0; w < kMaxWords; ++w) tt.prefix[i + 1][w] = tt.prefix[i][w];
@@ -189,7 +181,7 @@ TupleTable make_tuple_table(const tang_ruleset_t* rs) {
     for (uint32_t t = 0; t < n; ++t) {
         const uint32_t ls = rs->sigs[t].first, ld = rs->sigs[t].second;
         if (ls == 0 && ld == 0) {
-            tt.gid[t] = (uint8_t)kNoGroup;
+            tt.tg[t] = TupleGroup{kNoGroup, 0u};
             tt.nogroup[t >> 5] |= 1u << (t & 31u);
             continue;
         }
@@ -197,11 +189,22 @@ TupleTable make_tuple_table(const tang_ruleset_t* rs) {
         uint32_t g = 0;
         while (g < tt.ngroups && tt.gkey[g] != gk) ++g;
         if (g == tt.ngroups) tt.gkey[tt.ngroups++] = gk;
-        tt.gid[t] = (uint8_t)g;
+        tt.tg[t] = TupleGroup{gk, group_salt(gk)};
         tt.gmask[g][t >> 5] |= 1u << (t & 31u);
     }
+    uint32_t ops = 0;
+    for (uint32_t g = 0; g < tt.ngroups; ++g) {
+        FilterGroup& f = tt.fg[g];
+        f.dip = tt.gkey[g] >> 6;
+        f.mask = pmask(tt.gkey[g] & 63u);
+        f.salt = group_salt(tt.gkey[g]);
+        f.begin = ops;
+        for (uint32_t t = 0; t < n; ++t)
+            if (tt.tg[t].gkey == tt.gkey[g]) tt.fop[ops++] = FilterOp{f.dip ? tt.t[t].smask : tt.t[t].dmask, filter_salt(t), t, 0u};
+        f.end = ops;
+    }
     tt.slot_mask = rs->slots.empty() ? 0 : (uint32_t)rs->slots.size() - 1;
-    tt.filter_mask = rs->filter.empty() ? 0 : (uint32_t)rs->filter.size() / 2u - 1u;
+    tt.filter_mask = rs->filter_blocks ? rs->filter_blocks - 1u : 0u;
     return tt;
 }
 
@@ -272,15 +275,30 @@ int build_host(tang_ruleset_t* rs, const tang_rule_t* rules, size_t n) {
 // ---------------------------------------------------------------------------------------
 // Device upload of a freshly built ruleset, with the conflict masks computed on the GPU.
 
+// Fills the whole device slot table from the host mirror, and the (cleared) filter's bits,
+// through a staging block that the caller releases once the stream is done.
+static hipError_t upload_slots(const tang_ruleset_t* rs, SlotDev* d_slots, uint32_t* d_filter, Slot** d_val,
+                               hipStream_t s) {
+    hipError_t e = dev_alloc(d_val, rs->slots.size() * sizeof(Slot));
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(*d_val, rs->slots.data(), rs->slots.size() * sizeof(Slot), hipMemcpyHostToDevice, s);
+    if (e == hipSuccess)
+        e = launch_fill_slots(d_slots, nullptr, *d_val, (uint32_t)rs->slots.size(), rs->d_recs, rs->d_back,
+                              d_filter, rs->d_tt, s);
+    return e;
+}
+
 int upload_all(tang_ruleset_t* rs) {
     TANG_HIP(hipSetDevice(rs->device));
     hipStream_t s = rs->upd_stream;
-    TANG_HIP(dev_alloc(&rs->d_slots, rs->slots.size() * sizeof(Slot)));
-    TANG_HIP(dev_alloc(&rs->d_filter, rs->filter.size() * sizeof(uint32_t)));
-    TANG_HIP(hipMemcpy(rs->d_filter, rs->filter.data(), rs->filter.size() * sizeof(uint32_t),
-                       hipMemcpyHostToDevice));
+    TANG_HIP(dev_alloc(&rs->d_slots, rs->slots.size() * sizeof(SlotDev)));
+    TANG_HIP(dev_alloc(&rs->d_filter, (size_t)rs->filter_blocks * 8));
+    TANG_HIP(hipMemset(rs->d_filter, 0, (size_t)rs->filter_blocks * 8));
     TANG_HIP(dev_alloc(&rs->d_recs, (size_t)rs->rec_cap * sizeof(Rec)));
-    if (rs->nw > 1) {
+    if (rs->nw == 1) {
+        TANG_HIP(dev_alloc(&rs->d_back, (size_t)rs->rec_cap * sizeof(uint32_t)));
+        TANG_HIP(hipMemset(rs->d_back, 0, (size_t)rs->rec_cap * sizeof(uint32_t)));
+    } else {
         TANG_HIP(dev_alloc(&rs->d_cmask, (size_t)rs->rec_cap * rs->nw * sizeof(uint32_t)));
         TANG_HIP(hipMemset(rs->d_cmask, 0, (size_t)rs->rec_cap * rs->nw * sizeof(uint32_t)));
     }
@@ -291,8 +309,6 @@ int upload_all(tang_ruleset_t* rs) {
     for (uint32_t h = 0; h < rs->rules.size(); ++h)
         if (rs->rules[h].live) recs[rs->rules[h].pos] = make_rec(rs, h);
     TupleTable tt = make_tuple_table(rs);
-    TANG_HIP(hipMemcpy(rs->d_slots, rs->slots.data(), rs->slots.size() * sizeof(Slot),
-                       hipMemcpyHostToDevice));
     TANG_HIP(hipMemcpy(rs->d_recs, recs.data(), recs.size() * sizeof(Rec), hipMemcpyHostToDevice));
     TANG_HIP(hipMemcpy(rs->d_tt, &tt, sizeof tt, hipMemcpyHostToDevice));
 
@@ -327,6 +343,12 @@ int upload_all(tang_ruleset_t* rs) {
         (void)dev_release(d_boxes);
         if (e != hipSuccess) return hip_fail(e, "conflict-mask build");
     }
+    // the slots copy their first records, masks included
+    Slot* d_val = nullptr;
+    hipError_t e = upload_slots(rs, rs->d_slots, rs->d_filter, &d_val, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (d_val) (void)dev_release(d_val);
+    if (e != hipSuccess) return hip_fail(e, "slot table upload");
     return TANG_OK;
 }
 
@@ -341,7 +363,7 @@ namespace {
 // `fresh` are handles of rules not yet on the device. Then the slot entries, tuple
 // table, and the conflict masks of the fresh rules are brought up to date.
 int flush(tang_ruleset_t* rs, const std::vector<uint32_t>& dirty, const std::vector<uint32_t>& fresh,
-          bool rehash, bool filter_dirty) {
+          bool rehash) {
     rs->version++;
     if (rs->device == TANG_HOST_ONLY) return TANG_OK;
     TANG_HIP(hipSetDevice(rs->device));
@@ -379,6 +401,16 @@ int flush(tang_ruleset_t* rs, const std::vector<uint32_t>& dirty, const std::vec
             TANG_HIP(hipStreamSynchronize(s));
             TANG_HIP(dev_release(rs->d_cmask));
             rs->d_cmask = nmask;
+        }
+        if (rs->nw == 1) {
+            uint32_t* nback = nullptr;
+            TANG_HIP(dev_alloc(&nback, (size_t)ncap * sizeof(uint32_t)));
+            TANG_HIP(hipMemsetAsync(nback, 0, (size_t)ncap * sizeof(uint32_t), s));
+            TANG_HIP(hipMemcpyAsync(nback, rs->d_back, (size_t)rs->rec_used * sizeof(uint32_t),
+                                    hipMemcpyDeviceToDevice, s));
+            TANG_HIP(hipStreamSynchronize(s));
+            TANG_HIP(dev_release(rs->d_back));
+            rs->d_back = nback;
         }
         TANG_HIP(hipStreamSynchronize(s));
         TANG_HIP(dev_release(rs->d_recs));
@@ -446,7 +478,7 @@ int flush(tang_ruleset_t* rs, const std::vector<uint32_t>& dirty, const std::vec
         }
         if (e == hipSuccess)
             e = launch_move_records(rs->d_recs, (const Rec*)d_new, (const uint32_t*)d_src,
-                                    (const uint32_t*)d_dst, (uint32_t)dst.size(), (Rec*)d_stage, s);
+                                    (const uint32_t*)d_dst, (uint32_t)dst.size(), (Rec*)d_stage, rs->d_back, s);
         if (e == hipSuccess && rs->nw > 1) {
             void* d_mstage = nullptr;
             e = dev_alloc(&d_mstage, dst.size() * rs->nw * sizeof(uint32_t));
@@ -457,21 +489,31 @@ int flush(tang_ruleset_t* rs, const std::vector<uint32_t>& dirty, const std::vec
             }
         }
     }
-    // slots
+    // conflict masks of fresh rules, and their bit in lower-priority rules they meet
+    if (e == hipSuccess && !fresh.empty()) {
+        pos.resize(fresh.size());
+        for (size_t i = 0; i < fresh.size(); ++i) pos[i] = rs->rules[fresh[i]].pos;
+        void* d_pos = nullptr;
+        e = dev_copy(pos.data(), pos.size() * 4, &d_pos);
+        if (e == hipSuccess)
+            e = launch_conflict_update(rs->d_recs, rs->d_cmask, rs->nw, rs->rec_used,
+                                       (const uint32_t*)d_pos, (uint32_t)pos.size(), rs->d_back, rs->d_slots, s);
+    }
+    const TupleTable tt = make_tuple_table(rs);
+    if (e == hipSuccess) e = hipMemcpyAsync(rs->d_tt, &tt, tuple_table_bytes(tt), hipMemcpyHostToDevice, s);
+    // slots, with their first records as they are now, and the filter bits of new buckets
     if (e == hipSuccess) {
         if (rehash) {
-            Slot* ns = nullptr;
+            SlotDev* ns = nullptr;
+            Slot* d_val = nullptr;
             uint32_t* nf = nullptr;
             e = hipStreamSynchronize(s);
-            if (e == hipSuccess) e = dev_alloc(&ns, rs->slots.size() * sizeof(Slot));
-            if (e == hipSuccess) e = dev_alloc(&nf, rs->filter.size() * sizeof(uint32_t));
-            if (e == hipSuccess)
-                e = hipMemcpyAsync(ns, rs->slots.data(), rs->slots.size() * sizeof(Slot),
-                                   hipMemcpyHostToDevice, s);
-            if (e == hipSuccess)
-                e = hipMemcpyAsync(nf, rs->filter.data(), rs->filter.size() * sizeof(uint32_t),
-                                   hipMemcpyHostToDevice, s);
+            if (e == hipSuccess) e = dev_alloc(&ns, rs->slots.size() * sizeof(SlotDev));
+            if (e == hipSuccess) e = dev_alloc(&nf, (size_t)rs->filter_blocks * 8);
+            if (e == hipSuccess) e = hipMemsetAsync(nf, 0, (size_t)rs->filter_blocks * 8, s);
+            if (e == hipSuccess) e = upload_slots(rs, ns, nf, &d_val, s);
             if (e == hipSuccess) e = hipStreamSynchronize(s);
+            if (d_val) (void)dev_release(d_val);
             if (e == hipSuccess) {
                 (void)dev_release(rs->d_slots);
                 (void)dev_release(rs->d_filter);
@@ -491,24 +533,9 @@ int flush(tang_ruleset_t* rs, const std::vector<uint32_t>& dirty, const std::vec
             e = dev_copy(touched_slots.data(), touched_slots.size() * 4, &d_idx);
             if (e == hipSuccess) e = dev_copy(vals.data(), vals.size() * sizeof(Slot), &d_val);
             if (e == hipSuccess)
-                e = launch_scatter_slots(rs->d_slots, (const uint32_t*)d_idx, (const Slot*)d_val,
-                                         (uint32_t)vals.size(), s);
-            if (e == hipSuccess && filter_dirty)
-                e = hipMemcpyAsync(rs->d_filter, rs->filter.data(),
-                                   rs->filter.size() * sizeof(uint32_t), hipMemcpyHostToDevice, s);
+                e = launch_fill_slots(rs->d_slots, (const uint32_t*)d_idx, (const Slot*)d_val,
+                                      (uint32_t)vals.size(), rs->d_recs, rs->d_back, rs->d_filter, rs->d_tt, s);
         }
-    }
-    TupleTable tt = make_tuple_table(rs);
-    if (e == hipSuccess) e = hipMemcpyAsync(rs->d_tt, &tt, sizeof tt, hipMemcpyHostToDevice, s);
-    // conflict masks of fresh rules, and their bit in lower-priority rules they meet
-    if (e == hipSuccess && !fresh.empty()) {
-        pos.resize(fresh.size());
-        for (size_t i = 0; i < fresh.size(); ++i) pos[i] = rs->rules[fresh[i]].pos;
-        void* d_pos = nullptr;
-        e = dev_copy(pos.data(), pos.size() * 4, &d_pos);
-        if (e == hipSuccess)
-            e = launch_conflict_update(rs->d_recs, rs->d_cmask, rs->nw, rs->rec_used,
-                                       (const uint32_t*)d_pos, (uint32_t)pos.size(), s);
     }
     hipError_t e2 = hipStreamSynchronize(s);
     for (void* p : tmp) (void)dev_release(p);
@@ -522,8 +549,8 @@ int flush(tang_ruleset_t* rs, const std::vector<uint32_t>& dirty, const std::vec
 // later call that reads its device state (tang_ruleset_export still gives the live rules
 // a rebuild starts from).
 int flush_or_fail(tang_ruleset_t* rs, const std::vector<uint32_t>& dirty,
-                  const std::vector<uint32_t>& fresh, bool rehash, bool filter_dirty) {
-    const int rc = flush(rs, dirty, fresh, rehash, filter_dirty);
+                  const std::vector<uint32_t>& fresh, bool rehash) {
+    const int rc = flush(rs, dirty, fresh, rehash);
     if (rc) {
         rs->failed = true;
         return fail(rc, std::string("update not applied on the device (") + tang_last_error() +
@@ -608,23 +635,21 @@ int apply_insert(tang_ruleset_t* rs, const tang_rule_t* rules, size_t n) {
         fresh.push_back(h);
     }
     // new buckets need slots; grow the table when it would pass half full
-    bool rehash = false, filter_dirty = false;
+    bool rehash = false;
     if (rs->buckets.size() != nb_before) {
         // keep the slot table at most 1/3 full and the filter at >= half its bits per bucket
         if (3 * rs->buckets.size() + 3 > rs->slots.size() ||
-            16 * rs->buckets.size() > rs->filter.size() * 32) {
+            rs->buckets.size() > 4 * (size_t)rs->filter_blocks) {
             rebuild_slots(rs);
             rehash = true;
         } else {
             for (size_t b = nb_before; b < rs->buckets.size(); ++b) {
                 auto& bk = rs->buckets[b];
                 bk.slot = slot_insert(rs->slots, Slot{bk.ms, bk.md, bk.t << kTlShift, 0});
-                if (is_main(bk)) filter_add(rs, bk);
             }
-            filter_dirty = true;
         }
     }
-    return flush_or_fail(rs, dirty, fresh, rehash, filter_dirty);
+    return flush_or_fail(rs, dirty, fresh, rehash);
 }
 
 int apply_delete(tang_ruleset_t* rs, const uint32_t* ids, size_t n) {
@@ -648,7 +673,7 @@ int apply_delete(tang_ruleset_t* rs, const uint32_t* ids, size_t n) {
         if (rs->sigs[hr.tuple] != std::make_pair(hr.r.sip_len, hr.r.dip_len)) rs->n_coarse--;
         if (!mark[hr.bucket]) { mark[hr.bucket] = 1; dirty.push_back(hr.bucket); }
     }
-    return flush_or_fail(rs, dirty, {}, false, false);
+    return flush_or_fail(rs, dirty, {}, false);
 }
 
 }  // namespace tang

@@ -1,0 +1,87 @@
+"""The search's forms and the slots' copies of their first records.
+
+Batch sizes on both sides of the queue rule (one set of 64 headers per wave, or four), at
+wave and workgroup edges, and one header; and conflict masks that an insertion changes,
+which a slot's copy of its first record has to follow."""
+import numpy as np
+import pytest
+
+from oracle import oracle as orc
+from paper_2601_03187_amd import synth, train
+from paper_2601_03187_amd import tang as T
+from tests._gpu import classify_dev, torch_cuda
+
+pytestmark = pytest.mark.gpu
+
+QUEUE_FROM = 3 << 18
+
+
+@pytest.mark.parametrize("space", ["narrow", "wide", "all"])
+@pytest.mark.parametrize("model", [False, True])
+def test_batch_sizes_equal_oracle(space, model):
+    torch_cuda()
+    rules = synth.make_rules(2000, seed=91, ordering="literal", mix=0.2, wide=space == "wide",
+                             all_lengths=space == "all")
+    hdr = synth.make_packets(rules, 4099, seed=92, frac_in=0.7)
+    want = orc.classify(rules, hdr)
+    rs = T.tang_ruleset_create(0, rules)
+    try:
+        if model:
+            C = T.tang_ruleset_num_tuples(rs)
+            Ws, bs = train.random_weights(C, 128, seed=3)
+            T.tang_model_load(rs, Ws, bs, "bf16", topk=2)
+        for n in (1, 63, 64, 65, 255, 256, 257, 1023, 1024, 1025, 4099):
+            assert np.array_equal(classify_dev(rs, hdr[:n]), want[:n]), n
+        if space == "narrow":
+            for n in (QUEUE_FROM - 1, QUEUE_FROM, QUEUE_FROM + 257):
+                reps = -(-n // len(hdr))
+                assert np.array_equal(classify_dev(rs, np.tile(hdr, reps)[:n]), np.tile(want, reps)[:n]), n
+    finally:
+        T.tang_ruleset_destroy(rs)
+
+
+@pytest.mark.parametrize("wide", [False, True])
+def test_inserted_conflicts_reach_the_first_records(wide):
+    """A predictor that always names the coarse tuple: its match is certified by the
+    conflict mask alone, so rules inserted into finer tuples are found only if the mask
+    that the probe reads has their bits. Inserts in several batches, some moving the
+    bucket's first record, then deletes."""
+    torch_cuda()
+    rules = synth.make_rules(3000, seed=93, wide=wide)
+    rs = T.tang_ruleset_create(0, rules)
+    try:
+        C = T.tang_ruleset_num_tuples(rs)
+        coarse = next(t for t in range(C) if T.tang_ruleset_tuple(rs, t) == (8, 8))
+        Ws, bs = train.constant_winner_weights(C, 128, coarse)
+        T.tang_model_load(rs, Ws, bs, "bf16", topk=1)
+        base = rules[(rules["sip_len"] == 8) & (rules["dip_len"] == 8)][:40]
+        N = len(base)
+        assert N >= 8
+        hdr = np.repeat(synth.sample_inside(base, np.random.default_rng(1)), 8)
+        every, live = rules, np.ones(len(rules), bool)
+        assert np.array_equal(classify_dev(rs, hdr), orc.classify(every, hdr))
+        for k in range(3):
+            ins = synth.make_rules(N, seed=94 + k, ordering="literal")
+            ins["sip"], ins["dip"] = hdr["sip"][::8], hdr["dip"][::8]
+            ins["sip_len"] = (24, 32, 8)[k]
+            ins["dip_len"] = (24, 16, 8)[k]      # the third batch: new first records of the buckets
+            for f in ("sip", "dip"):
+                ln = ins[f + "_len"].astype(np.uint64)
+                ins[f] &= (0xFFFFFFFF << (32 - ln) & 0xFFFFFFFF).astype(np.uint32)
+            ins["sp_lo"] = ins["dp_lo"] = 0
+            ins["sp_hi"] = ins["dp_hi"] = 65535
+            ins["proto"] = ins["proto_mask"] = 0
+            ins["priority"] = 5 - k
+            ins["id"] = 100_000 + 100 * k + np.arange(N)
+            T.tang_insert(rs, ins)
+            every, live = np.concatenate([every, ins]), np.concatenate([live, np.ones(N, bool)])
+            want = orc.classify(every, hdr, live=live)
+            assert np.isin(want, ins["id"]).all()
+            assert np.array_equal(classify_dev(rs, hdr), want), k
+        for k in (2, 0):
+            ids = 100_000 + 100 * k + np.arange(N)
+            T.tang_delete(rs, ids)
+            live &= ~np.isin(every["id"], ids)
+            assert np.array_equal(classify_dev(rs, hdr), orc.classify(every, hdr, live=live)), k
+    finally:
+        T.tang_ruleset_destroy(rs)
