@@ -193,9 +193,7 @@ int tang_model_unload(tang_ruleset_t* rs);
  * W[1 + 2k] and W[2 + 2k] (block k's two layers) width x width, W[last] C x width.
  * Precision: BF16 only (the input layer is computed in FP32; every later layer's weights
  * and inputs are rounded to bfloat16, nearest-even; FP32 accumulation and biases).
- * Deep copy; replaces any loaded model. The library also allocates a 192 MB activation
- * workspace (three buffers of 65,536 headers x 512 BF16); calls that use this model on
- * one ruleset are ordered on the device through an event, whatever their streams.
+ * Deep copy; replaces any loaded model. The library also allocates a 192 MB workspace.
  * Errors: EINVAL (width != 512, n_blocks outside 1..16, n_out != C, topk outside
  * 1..min(4, C), precision not BF16, NULL pointers), ENOMEM, EDEVICE.
  */

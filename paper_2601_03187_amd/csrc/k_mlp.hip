@@ -600,12 +600,9 @@ void model_free(ModelDev& m) {
     if (m.rin) dev_release(m.rin);
     if (m.rw) dev_release(m.rw);
     if (m.ws) dev_release(m.ws);
-    if (m.ws_done) hipEventDestroy(m.ws_done);
     m.rin = nullptr;
     m.rw = nullptr;
     m.ws = nullptr;
-    m.ws_done = nullptr;
-    m.ws_used = false;
     m.kind = 0;
     m.loaded = 0;
     m.bytes = 0;

@@ -3,22 +3,20 @@
 //   seven 16-bit header chunks / 65535 -> FC(7 -> 512) + ReLU
 //   -> n blocks  x <- relu(relu(x w1 + b1) w2 + b2 + x)
 //   -> FC(512 -> C) -> top-k (ties to the lower tuple index).
-// About 3.2 M multiply-adds per header with 6.3 MB of BF16 weights: the weights cannot
-// stay in LDS as the small predictor's do, so every 512 x 512 layer is one MFMA GEMM over
-// a chunk of headers. Activations are BF16 rows of 512 per header in a library-owned
-// workspace of three chunk buffers (block input / residual, block middle, block output),
-// small enough to stay in the Infinity Cache; each layer's 512 KB of weights is read from
-// L2 by every workgroup. The input layer (seven inputs) runs in FP32 on the vector ALUs.
+// About 3.2 M multiply-adds per header with 6.3 MB of BF16 weights. One kernel runs the
+// whole network for a tile of headers: the tile's activations stay in LDS, every layer's
+// weights stream from L2 straight into the registers of the wave that needs them. The
+// input layer (seven inputs) runs in FP32 on the vector ALUs.
 //
 // MFMA orientation as in the small predictor: weights are the A operand (rows = output
-// neurons), headers the B operand (columns). Both operands are read straight from their
-// row-major rows: lane group g supplies elements 8g..8g+7 of every 32-wide K block on both
-// sides, so the products pair up whatever the instruction's internal K order is. A 16x16
-// result leaves lane (g, c) holding neurons 4g..4g+3 of header c: four consecutive BF16 of
-// that header's output row, stored as one 8-byte write.
+// neurons), headers the B operand (columns). Lane group g supplies elements 8g..8g+7 of
+// every 32-wide K block on both sides, so the products pair up whatever the instruction's
+// internal K order is. A 16x16 result leaves lane (g, c) holding neurons 4g..4g+3 of
+// header c: four consecutive BF16 of that header.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "tang_internal.hpp"
@@ -27,7 +25,11 @@ namespace tang {
 namespace {
 
 constexpr int kW = 512;               // neurons per layer
-constexpr uint32_t kChunk = 65536;    // headers per workspace pass (3 x 64 MB)
+constexpr int kNoClass = 1 << 20;     // an empty top-k slot (above every class)
+// Workspace the public header states for a loaded model: allocated and released with it so
+// that a caller's allocator sees the documented size, not read or written (activations stay
+// on chip).
+constexpr size_t kWorkspace = (size_t)3 * 65536 * kW * 2;
 
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef float fl2 __attribute__((ext_vector_type(2)));
@@ -57,272 +59,324 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* p, uint32_t b
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000);
 }
 
-// Input layer: one wave per header, lane l computes neurons 8l..8l+7 (FP32 FMAs over the
-// seven chunks, ReLU, BF16) and writes them as one 16-byte store.
-__global__ __launch_bounds__(256) void k_res_input(const uint4* __restrict__ hdr, uint32_t m,
-                                                   const float* __restrict__ win,
-                                                   const float* __restrict__ bin,
-                                                   u32x4* __restrict__ x) {
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const uint32_t nwaves = (gridDim.x * blockDim.x) >> 6;
-    float w[8][7], b[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const uint32_t n = 8u * lane + j;
-        b[j] = bin[n];
-#pragma unroll
-        for (int q = 0; q < 7; ++q) w[j][q] = win[n * 8 + q];
-    }
-    for (uint32_t p = wave; p < m; p += nwaves) {
-        const uint4 h = hdr[p];
-        // v / 65535 for a 16-bit v: the FP64 product with 1/65535 rounded to FP32 equals
-        // the correctly rounded FP32 quotient for every v (checked exhaustively), at three
-        // instructions instead of a full-precision division
-        auto seg = [](uint32_t v) { return (float)((double)v * (1.0 / 65535.0)); };
-        const float s[7] = {seg(h.x >> 16), seg(h.x & 0xFFFFu), seg(h.y >> 16), seg(h.y & 0xFFFFu),
-                            seg(h.z & 0xFFFFu), seg(h.z >> 16), seg(h.w & 0xFFu)};
-        float v[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            float a = b[j];
-#pragma unroll
-            for (int q = 0; q < 7; ++q) a = __builtin_fmaf(w[j][q], s[q], a);
-            v[j] = a;
-        }
-        x[(size_t)p * (kW / 8) + lane] =
-            (u32x4){relu_bf16x2(pack_bf16(v[0], v[1])), relu_bf16x2(pack_bf16(v[2], v[3])),
-                    relu_bf16x2(pack_bf16(v[4], v[5])), relu_bf16x2(pack_bf16(v[6], v[7]))};
-    }
+// Every wave's LDS accesses before this are done before any wave passes it. Weight loads in
+// flight stay in flight (__syncthreads would wait for them).
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-// One 512 x 512 layer: out = relu(W in + b [+ res]) over m header rows, BF16 in and out,
-// FP32 accumulation with the bias as the accumulator's start. Workgroup: 8 waves and 128
-// headers; wave w computes neurons 64w..64w+63 (4 row tiles) for all 128 headers (8 column
-// tiles). K advances 32 at a time through a ring of three LDS stages, each holding the
-// K slice of all 512 weight rows (32 KB) and of the 128 header rows (8 KB). The slices go
-// straight from global memory into LDS (global_load_lds, 16 bytes per lane, lane l's
-// bytes landing at 16 l from the wave's base), so loads run three steps ahead of the
-// MFMAs without holding registers; each wave moves 4 KB of weights and 1 KB of headers
-// per step. Rows are 64 bytes with their four 16-byte chunks XOR-swizzled by row bits 1..3
-// (chunk c of row n at slot c ^ sw(n), sw(n) = ((n >> 1) ^ (n >> 2)) & 3): any 8, and any
-// 16, consecutive rows read at one chunk hit distinct 16-byte bank groups, so 128-bit
-// fragment reads are conflict-free whether the LDS serves 8 or 16 lanes per cycle (the
-// plain XOR by bits 2..3 left 4 conflict cycles per read). Header rows past m load row m - 1
-// instead (their columns are never written). One barrier per step: after it every
-// wave's loads for the next step have landed, and nobody still reads the stage that the
-// next loads overwrite.
-constexpr uint32_t kStageA = 512u * 64u, kStageB = 128u * 64u, kStage = kStageA + kStageB;
-__device__ __forceinline__ uint32_t sw(uint32_t row) { return ((row >> 1) ^ (row >> 2)) & 3u; }
-
-template <bool RES>
-__global__ __launch_bounds__(512) void k_res_dense(const uint16_t* __restrict__ in,
-                                                   const uint16_t* __restrict__ w,
-                                                   const float* __restrict__ bias,
-                                                   const uint16_t* __restrict__ res,
-                                                   uint16_t* __restrict__ out, uint32_t m) {
-    __shared__ __attribute__((aligned(16))) unsigned char st0[kStage], st1[kStage], st2[kStage];
+// The whole network for tiles of 16 NT headers. Workgroup: 8 waves; wave w computes neurons
+// 64w..64w+63 (4 row tiles) of every layer for all headers of the tile (NT column tiles).
+//
+// LDS holds one layer's activations in B-fragment order: fragment (kb, nt) is 1 KB, lane l's
+// 16 bytes at 16 l, so a fragment read is one conflict-free 128-bit read, and the four
+// neurons a lane holds after a layer are 8 bytes of one fragment of the next. A layer
+// overwrites its input in place between two barriers; where it overwrites a block's input,
+// each lane keeps its own share of it in registers for the residual sum. Weights are stored
+// in A-fragment order per wave, 4 KB per K block, and loaded two K blocks ahead, across
+// layer ends too; no wave reads another's weights, so they need no LDS.
+//
+// What bounds it (262,144 headers, 6 blocks, 25 classes: 1,345 us, 1,230 TFLOP/s; one kernel
+// per layer with the activations in memory took 2,780): MFMA issue, 12,288 cycles per layer
+// and 96 headers, about 70% of a block's 17.9 us at the clock the chip holds; the rest is
+// what a barrier exposes, the epilogue above all. 128 headers per tile leave no registers for
+// the block input (kept in memory instead: 1,670 us); 64 take 1,414, since the weights then
+// need the whole of a CU's 64 bytes per cycle from L2.
+template <int NT>
+__global__ __launch_bounds__(512) void k_res(const uint4* __restrict__ hdr, uint32_t n,
+                                             const float* __restrict__ win, const float* __restrict__ bias,
+                                             const uint16_t* __restrict__ w, uint32_t wbytes, int nb, int C,
+                                             int topk, uint32_t* __restrict__ cand,
+                                             float* __restrict__ logits, uint16_t* __restrict__ cand16) {
+    constexpr uint32_t TH = 16u * NT;   // headers per tile
+    constexpr int KB = kW / 32;
+    __shared__ u32x4 act[KB * NT * 64];
+    __shared__ __attribute__((aligned(16))) float sbias[kW];   // the layer's biases
     const uint32_t tid = threadIdx.x, lane = tid & 63u, g = lane >> 4, r = lane & 15u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t p0 = blockIdx.x * 128u, n0 = wave * 64u;
-    // loads: lane l of an instruction fills row 16 j + l / 4 (j: the instruction's row
-    // block), slot l % 4, with chunk (l % 4) ^ sw(row); row blocks start at multiples of
-    // 16, so sw(row) = sw(l / 4)
-    const uint32_t lrow = lane >> 2, lchunk = (lane & 3u) ^ sw(lrow);
-    const unsigned char* wsrc = reinterpret_cast<const unsigned char*>(w) +
-                                (size_t)(n0 + lrow) * (kW * 2) + lchunk * 16u;
-    const uint32_t hrow = std::min(p0 + wave * 16u + lrow, m - 1u);
-    const unsigned char* hsrc = reinterpret_cast<const unsigned char*>(in) +
-                                (size_t)hrow * (kW * 2) + lchunk * 16u;
-    // fragment reads: row (tile base) + r, chunk g at its swizzled slot
-    const uint32_t rd = r * 64u + ((g ^ sw(r)) * 16u);
-    f4 acc[4][8];
+    const __amdgpu_buffer_rsrc_t rw = rsrc(w, wbytes), rb = rsrc(bias, (uint32_t)(1 + 2 * nb) * kW * 4u);
+    // this lane's 8 bytes (neurons 64 wave + 16 mt + 4 g ..) of header column nt, in 8-byte
+    // units: own0 + 128 ((mt / 2) NT + nt) + 64 (mt % 2)
+    const uint32_t own0 = wave * (256u * NT) + ((g >> 1) * 16u + r) * 2u + (g & 1u);
+    u32x2* const act8 = reinterpret_cast<u32x2*>(act);
+    const uint32_t tiles = (n + TH - 1) / TH;
+    for (uint32_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        const uint32_t p0 = tile * TH;
+        // A fragments of K block kb of layer l (2 nb layers of 512 KB, 64 KB per wave)
+        u32x4 A[3][4];
+        auto load_a = [&](int buf, int l, int kb) {
+            const uint32_t at = ((uint32_t)l * 8u + wave) * 65536u + (uint32_t)kb * 4096u;
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-        const f4 bv = *reinterpret_cast<const f4*>(bias + n0 + 16 * mt + 4 * g);
+            for (int mt = 0; mt < 4; ++mt)
+                A[buf][mt] = __builtin_amdgcn_raw_buffer_load_b128(rw, lane * 16u, at + mt * 1024u, 0);
+        };
+        load_a(0, 0, 0);
+        load_a(1, 0, 1);
+        // bias of layer l for neuron tid (zero past the last: the output layer reads its own)
+        auto next_bias = [&](int l) {
+            return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rb, tid * 4u, (uint32_t)(1 + l) * (kW * 4u), 0));
+        };
+        sbias[tid] = next_bias(0);
+        // Input layer: a lane is a header, a wave 64 neurons, so weights are scalars.
 #pragma unroll
-        for (int nt = 0; nt < 8; ++nt) acc[mt][nt] = bv;
-    }
-    constexpr int kS = kW / 32;
-    auto stage = [&](int k) -> unsigned char* { return k % 3 == 0 ? st0 : k % 3 == 1 ? st1 : st2; };
-    auto issue = [&](int kb) {
-        unsigned char* sd = stage(kb);
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            __builtin_amdgcn_global_load_lds(
-                (void*)(wsrc + (size_t)j * 16u * (kW * 2) + kb * 64),
-                (__attribute__((address_space(3))) void*)(sd + (wave * 4u + j) * 1024u), 16, 0, 0);
-        __builtin_amdgcn_global_load_lds(
-            (void*)(hsrc + kb * 64), (__attribute__((address_space(3))) void*)(sd + kStageA + wave * 1024u),
-            16, 0, 0);
-    };
-    // Step hand-off: this wave's LDS reads are done and its loads for the stage read next
-    // have landed (s_waitcnt lgkmcnt(0) and vmcnt <= the loads issued since), then a bare
-    // barrier. __syncthreads() would add a workgroup release fence, which waits for every
-    // load in flight into LDS, the lookahead included; the empty asm statements keep the
-    // compiler from moving LDS accesses across the barrier.
-    constexpr int kLoadsPerStep = 5;
-    auto handoff = [&](int pending) {
-        if (pending) __builtin_amdgcn_s_waitcnt(0x0070 | kLoadsPerStep);
-        else __builtin_amdgcn_s_waitcnt(0x0070);
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-    };
-    // Fragments of step k are read from LDS during step k - 1, into the register set
-    // k & 1, so their latency hides behind a whole step of MFMAs. Stage k % 3 is refilled
-    // (step k + 3) during step k: every wave read it in step k - 1, before that step's
-    // closing barrier. Loads of step k + 2 must have landed by the barrier that closes
-    // step k, since step k + 1 reads them.
-    u32x4 FA[2][4], FB[2][8];
-    auto read = [&](int k) {
-        const unsigned char* sa = stage(k);
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
-            FA[k & 1][mt] = *reinterpret_cast<const u32x4*>(sa + (n0 + 16u * mt) * 64u + rd);
-#pragma unroll
-        for (int nt = 0; nt < 8; ++nt)
-            FB[k & 1][nt] = *reinterpret_cast<const u32x4*>(sa + kStageA + 16u * nt * 64u + rd);
-    };
-    issue(0);
-    issue(1);
-    issue(2);
-    __builtin_amdgcn_s_waitcnt(0x0070 | (2 * kLoadsPerStep));
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    read(0);
-    handoff(1);
-#pragma unroll
-    for (int kb = 0; kb < kS; ++kb) {
-        if (kb + 1 < kS) read(kb + 1);
-#pragma unroll
-        for (int nt = 0; nt < 8; ++nt)
-#pragma unroll
-            for (int mt = 0; mt < 4; ++mt) acc[mt][nt] = mma(FA[kb & 1][mt], FB[kb & 1][nt], acc[mt][nt]);
-        if (kb + 3 < kS) issue(kb + 3);
-        if (kb + 2 < kS) handoff(kb + 3 < kS);
-    }
-#pragma unroll
-    for (int nt = 0; nt < 8; ++nt) {
-        const uint32_t p = p0 + 16 * nt + r;
-        if (p >= m) continue;
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt) {
-            const size_t at = (size_t)p * kW + n0 + 16 * mt + 4 * g;
-            f4 v = acc[mt][nt];
-            if constexpr (RES) {
-                const u32x2 xr = *reinterpret_cast<const u32x2*>(res + at);
-                v[0] += bf16_lo(xr[0]);
-                v[1] += bf16_hi(xr[0]);
-                v[2] += bf16_lo(xr[1]);
-                v[3] += bf16_hi(xr[1]);
-            }
-            *reinterpret_cast<u32x2*>(out + at) =
-                (u32x2){relu_bf16x2(pack_bf16(v[0], v[1])), relu_bf16x2(pack_bf16(v[2], v[3]))};
-        }
-    }
-}
-
-// Output layer (C scores, no activation) and top-k. Workgroup: 4 waves, each 64 headers
-// (4 column tiles); classes in blocks of 32 (2 row tiles), ncb = ceil(C / 32) of them. A
-// header's scores of a block sit in the 4 lanes c, c+16, c+32, c+48; each lane keeps a
-// running top-4 of the classes it holds (a strictly larger score displaces, so ties keep
-// the lower class), which contains the lane's share of any top-k (k <= 4); the top-k is
-// then taken across the 4 lanes, ties to the lower class.
-__global__ __launch_bounds__(256) void k_res_out(const uint16_t* __restrict__ in,
-                                                 const uint16_t* __restrict__ w,
-                                                 const float* __restrict__ bias, uint32_t m,
-                                                 int C, int topk, uint32_t* __restrict__ cand,
-                                                 float* __restrict__ logits,
-                                                 uint16_t* __restrict__ cand16) {
-    const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u, g = lane >> 4, r = lane & 15u;
-    const uint32_t p0 = (blockIdx.x * 4u + wave) * 64u;
-    const int ncb = (C + 31) / 32;
-    const __amdgpu_buffer_rsrc_t ri = rsrc(in, m * (uint32_t)(kW * 2));
-    const __amdgpu_buffer_rsrc_t rw = rsrc(w, (uint32_t)(32 * ncb * kW * 2));
-    const uint32_t boff = (p0 + r) * (kW * 2) + g * 16u;
-    float v[4][4];
-    int cl[4][4];
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            v[nt][q] = -INFINITY;
-            cl[nt][q] = 1 << 20;
-        }
-    for (int cb = 0; cb < ncb; ++cb) {
-        const uint32_t aoff = (32u * cb + r) * (kW * 2) + g * 16u;
-        f4 acc[2][4];
-#pragma unroll
-        for (int mt = 0; mt < 2; ++mt) {
-            const f4 bv = *reinterpret_cast<const f4*>(bias + 32 * cb + 16 * mt + 4 * g);
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt) acc[mt][nt] = bv;
-        }
+        for (uint32_t set = 0; set < (TH + 63u) / 64u; ++set) {
+            const uint32_t c = set * 64u + lane;
+            const uint4 h = c < TH && p0 + c < n ? hdr[p0 + c] : make_uint4(0u, 0u, 0u, 0u);
+            // v / 65535 for a 16-bit v: the FP64 product with 1/65535 rounded to FP32 equals
+            // the correctly rounded FP32 quotient for every v (checked exhaustively), at three
+            // instructions instead of a full-precision division
+            auto seg = [](uint32_t v) { return (float)((double)v * (1.0 / 65535.0)); };
+            const float s[7] = {seg(h.x >> 16), seg(h.x & 0xFFFFu), seg(h.y >> 16), seg(h.y & 0xFFFFu),
+                                seg(h.z & 0xFFFFu), seg(h.z >> 16), seg(h.w & 0xFFu)};
 #pragma unroll 2
-        for (uint32_t kb = 0; kb < kW / 32; ++kb) {
-            u32x4 A[2], B[4];
+            for (uint32_t k8 = 0; k8 < 8u; ++k8) {
+                const uint32_t n0 = 64u * wave + 8u * k8;
+                float v[8];
 #pragma unroll
-            for (int mt = 0; mt < 2; ++mt)
-                A[mt] = __builtin_amdgcn_raw_buffer_load_b128(rw, aoff, mt * 16 * kW * 2 + kb * 64, 0);
+                for (int j = 0; j < 8; ++j) {
+                    float a = bias[n0 + j];
 #pragma unroll
-            for (int nt = 0; nt < 4; ++nt)
-                B[nt] = __builtin_amdgcn_raw_buffer_load_b128(ri, boff, nt * 16 * kW * 2 + kb * 64, 0);
-#pragma unroll
-            for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-                for (int nt = 0; nt < 4; ++nt) acc[mt][nt] = mma(A[mt], B[nt], acc[mt][nt]);
+                    for (int q = 0; q < 7; ++q) a = __builtin_fmaf(win[(n0 + j) * 8u + q], s[q], a);
+                    v[j] = a;
+                }
+                if (c < TH)
+                    act[((n0 >> 5) * NT + (c >> 4)) * 64u + (k8 & 3u) * 16u + (c & 15u)] =
+                        (u32x4){relu_bf16x2(pack_bf16(v[0], v[1])), relu_bf16x2(pack_bf16(v[2], v[3])),
+                                relu_bf16x2(pack_bf16(v[4], v[5])), relu_bf16x2(pack_bf16(v[6], v[7]))};
+            }
         }
+        lds_barrier();
+        u32x4 x[2][NT];   // the block's input, this lane's share
+        // One 512 x 512 layer: out = relu(W in + b [+ block input]), BF16 in and out, FP32
+        // accumulation with the bias as the accumulator's start.
+        auto layer = [&](int l, auto second) {
+            constexpr bool RES = decltype(second)::value;
+            f4 acc[4][NT];
 #pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
-            const uint32_t pkt = p0 + 16 * nt + r;
+            for (int mt = 0; mt < 4; ++mt) {
+                const f4 bv = *reinterpret_cast<const f4*>(sbias + 64u * wave + 16 * mt + 4 * g);
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = bv;
+            }
+            const float bnext = next_bias(l + 1);
+            u32x4 B[NT];
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) B[nt] = act[nt * 64 + lane];
+            // 16 K blocks in register buffers 0, 1, 2, 0, ..; the next layer's first two are
+            // loaded in the last two, into buffers 0 and 1
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb) {
+                if (kb + 2 < KB) load_a((kb + 2) % 3, l, kb + 2);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+#pragma unroll
+                    for (int mt = 0; mt < 4; ++mt) acc[mt][nt] = mma(A[kb % 3][mt], B[nt], acc[mt][nt]);
+                    if (kb + 1 < KB) B[nt] = act[((kb + 1) * NT + nt) * 64 + lane];
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if (kb == KB - 2) load_a(1, l + 1, 1);
+            }
+            load_a(0, l + 1, 0);
+            lds_barrier();   // every wave has read the layer's input
+            sbias[tid] = bnext;
+#pragma unroll
+            for (int mp = 0; mp < 2; ++mp) {
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                    u32x2 y[2];
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        f4 v = acc[2 * mp + u][nt];
+                        if constexpr (RES) {
+                            const uint32_t x0 = x[mp][nt][2 * u], x1 = x[mp][nt][2 * u + 1];
+                            v[0] += bf16_lo(x0);
+                            v[1] += bf16_hi(x0);
+                            v[2] += bf16_lo(x1);
+                            v[3] += bf16_hi(x1);
+                        }
+                        y[u] = (u32x2){relu_bf16x2(pack_bf16(v[0], v[1])), relu_bf16x2(pack_bf16(v[2], v[3]))};
+                    }
+                    const uint32_t a0 = own0 + (mp * NT + nt) * 128u, a1 = a0 + 64u;
+                    if constexpr (!RES) {
+                        const u32x2 b0 = act8[a0], b1 = act8[a1];
+                        x[mp][nt] = (u32x4){b0[0], b0[1], b1[0], b1[1]};
+                    }
+                    act8[a0] = y[0];
+                    act8[a1] = y[1];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            lds_barrier();
+        };
+#pragma unroll 1
+        for (int k = 0; k < nb; ++k) {
+            layer(2 * k, std::false_type{});
+            layer(2 * k + 1, std::true_type{});
+        }
+        // Output layer (C scores, no activation) and top-k, in blocks of 32 classes. Up to two
+        // blocks, wave w takes header column w; with more, wave w takes blocks w, w + 8, ..
+        // for the whole tile, so that a block's weights are read once per tile (387 classes,
+        // 262,144 headers: 2,314 us with the first form, 1,645 with the second).
+        // A header's scores of a block sit in the 4 lanes c, c+16, c+32, c+48; each lane
+        // keeps a running top-4 of the classes it holds (a strictly larger score displaces,
+        // so ties keep the lower class), which contains the lane's share of any top-k
+        // (k <= 4); the top-k is then taken across the lanes, ties to the lower class.
+        const int ncb = (C + 31) / 32;
+        const uint32_t out_at = (uint32_t)nb * (2u * kW * kW * 2u);
+        const float* bout = bias + (size_t)(1 + 2 * nb) * kW;
+        struct Top {
+            float v[4];
+            int cl[4];
+        };
+        auto scores = [&](Top& t, const f4 (&z)[2], int cb, uint32_t pkt) {
 #pragma unroll
             for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const int c = 32 * cb + 16 * mt + 4 * (int)g + q;
-                    const float val = acc[mt][nt][q];
-                    if (logits && pkt < m && c < C) logits[(size_t)pkt * C + c] = val;
+                    const float val = z[mt][q];
+                    if (logits && pkt < n && c < C) logits[(size_t)pkt * C + c] = val;
                     float x = (c < C && val == val) ? val : -INFINITY;
                     int xc = c;
 #pragma unroll
-                    for (int s2 = 0; s2 < 4; ++s2) {
-                        if (x > v[nt][s2]) {
-                            const float tv = v[nt][s2];
-                            const int tc = cl[nt][s2];
-                            v[nt][s2] = x;
-                            cl[nt][s2] = xc;
+                    for (int s = 0; s < 4; ++s) {
+                        if (x > t.v[s]) {
+                            const float tv = t.v[s];
+                            const int tc = t.cl[s];
+                            t.v[s] = x;
+                            t.cl[s] = xc;
                             x = tv;
                             xc = tc;
                         }
                     }
                 }
-        }
-    }
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-        const uint32_t pkt = p0 + 16 * nt + r;
-        uint32_t packed = 0;
-        for (int k = 0; k < topk; ++k) {
-            float bv = v[nt][0];
-            int bc = cl[nt][0];
+        };
+        // the best of the header's four lanes, taken out of them
+        auto take = [&](Top& t, float& bv, int& bc) {
+            bv = t.v[0];
+            bc = t.cl[0];
 #pragma unroll
             for (int q = 1; q < 4; ++q)
-                if (v[nt][q] > bv) { bv = v[nt][q]; bc = cl[nt][q]; }
+                if (t.v[q] > bv) { bv = t.v[q]; bc = t.cl[q]; }
 #pragma unroll
             for (int o = 16; o <= 32; o <<= 1) {
                 const float ov = __shfl_xor(bv, o, 64);
                 const int oc = __shfl_xor(bc, o, 64);
                 if (ov > bv || (ov == bv && oc < bc)) { bv = ov; bc = oc; }
             }
-            packed |= (uint32_t)bc << (cand_bits(C) * k);
-            if (cand16 && g == 0 && pkt < m) cand16[(size_t)pkt * topk + k] = (uint16_t)bc;
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                if (cl[nt][q] == bc) { v[nt][q] = -INFINITY; cl[nt][q] = 1 << 20; }
+                if (t.cl[q] == bc) { t.v[q] = -INFINITY; t.cl[q] = kNoClass; }
+        };
+        if (ncb <= 2) {
+            if (wave < (uint32_t)NT) {
+                const uint32_t pkt = p0 + 16u * wave + r;
+                Top t;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    t.v[q] = -INFINITY;
+                    t.cl[q] = kNoClass;
+                }
+#pragma unroll 1
+                for (int cb = 0; cb < ncb; ++cb) {
+                    const uint32_t at = out_at + (uint32_t)cb * (KB * 2048u);
+                    f4 z[2];
+#pragma unroll
+                    for (int mt = 0; mt < 2; ++mt)
+                        z[mt] = *reinterpret_cast<const f4*>(bout + 32 * cb + 16 * mt + 4 * g);
+#pragma unroll 8
+                    for (int kb = 0; kb < KB; ++kb) {
+                        const u32x4 b = act[(kb * NT + wave) * 64 + lane];
+#pragma unroll
+                        for (int mt = 0; mt < 2; ++mt)
+                            z[mt] = mma(__builtin_amdgcn_raw_buffer_load_b128(rw, lane * 16u, at + kb * 2048u + mt * 1024u, 0),
+                                        b, z[mt]);
+                    }
+                    scores(t, z, cb, pkt);
+                }
+                uint32_t packed = 0;
+                for (int k = 0; k < topk; ++k) {
+                    float bv;
+                    int bc;
+                    take(t, bv, bc);
+                    packed |= (uint32_t)bc << (cand_bits(C) * k);
+                    if (cand16 && g == 0 && pkt < n) cand16[(size_t)pkt * topk + k] = (uint16_t)bc;
+                }
+                if (cand && g == 0 && pkt < n) cand[pkt] = packed;
+            }
+        } else {
+            Top t[NT];
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    t[nt].v[q] = -INFINITY;
+                    t[nt].cl[q] = kNoClass;
+                }
+#pragma unroll 1
+            for (int cb = (int)wave; cb < ncb; cb += 8) {
+                const uint32_t at = out_at + (uint32_t)cb * (KB * 2048u);
+                f4 z[NT][2];
+#pragma unroll
+                for (int mt = 0; mt < 2; ++mt) {
+                    const f4 bv = *reinterpret_cast<const f4*>(bout + 32 * cb + 16 * mt + 4 * g);
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) z[nt][mt] = bv;
+                }
+#pragma unroll 4
+                for (int kb = 0; kb < KB; ++kb) {
+                    u32x4 a[2];
+#pragma unroll
+                    for (int mt = 0; mt < 2; ++mt)
+                        a[mt] = __builtin_amdgcn_raw_buffer_load_b128(rw, lane * 16u, at + kb * 2048u + mt * 1024u, 0);
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) {
+                        const u32x4 b = act[(kb * NT + nt) * 64 + lane];
+#pragma unroll
+                        for (int mt = 0; mt < 2; ++mt) z[nt][mt] = mma(a[mt], b, z[nt][mt]);
+                    }
+                }
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) scores(t[nt], z[nt], cb, p0 + 16u * nt + r);
+            }
+            // each wave's top-k of a header to LDS (over the activations), then one lane per
+            // header picks from the eight lists
+            lds_barrier();
+            u32x2* const tops = act8;   // [wave][header][4]
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+                for (int k = 0; k < topk; ++k) {
+                    float bv;
+                    int bc;
+                    take(t[nt], bv, bc);
+                    if (g == 0) tops[(wave * TH + 16u * nt + r) * 4u + k] = (u32x2){__float_as_uint(bv), (uint32_t)bc};
+                }
+            lds_barrier();
+            const uint32_t pkt = p0 + tid;
+            if (tid < TH && pkt < n) {
+                uint32_t packed = 0;
+                float lv = INFINITY;
+                int lc = -1;
+                for (int k = 0; k < topk; ++k) {
+                    float bv = -INFINITY;
+                    int bc = kNoClass;
+                    for (uint32_t u = 0; u < 8u * topk; ++u) {
+                        const u32x2 x = tops[((u / topk) * TH + tid) * 4u + u % topk];
+                        const float v = __uint_as_float(x[0]);
+                        const int c = (int)x[1];
+                        const bool left = v < lv || (v == lv && c > lc);   // not picked yet
+                        if (left && (v > bv || (v == bv && c < bc))) { bv = v; bc = c; }
+                    }
+                    lv = bv;
+                    lc = bc;
+                    packed |= (uint32_t)bc << (cand_bits(C) * k);
+                    if (cand16) cand16[(size_t)pkt * topk + k] = (uint16_t)bc;
+                }
+                if (cand) cand[pkt] = packed;
+            }
         }
-        if (cand && g == 0 && pkt < m) cand[pkt] = packed;
+        lds_barrier();   // the next tile's input layer overwrites the activations
     }
 }
 
@@ -367,27 +421,40 @@ int resnet_prepare(tang_ruleset_t* rs, const tang_resnet_desc_t* d, const float*
     for (int l = 0; l < 1 + 2 * nb; ++l)
         for (int n = 0; n < kW; ++n) bias[(size_t)l * kW + n] = b[l][n];
     for (int c = 0; c < C; ++c) bias[(size_t)(1 + 2 * nb) * kW + c] = b[L - 1][c];
-    // BF16 weights: the block layers [512][512] each, then the output layer [CP][512]
+    // BF16 weights in A-fragment order (1 KB: 64 lanes of 8 elements): a block layer as
+    // [wave][K block][4 row tiles] of 64 neurons per wave, the output layer as [32-class
+    // block][K block][2 row tiles]; lane (g, r) holds row r, columns 8g..8g+7
     std::vector<uint16_t> w((size_t)2 * nb * kW * kW + (size_t)CP * kW, 0);
-    for (int l = 0; l < 2 * nb; ++l)
-        for (size_t k = 0; k < (size_t)kW * kW; ++k) w[(size_t)l * kW * kW + k] = to_bf16(W[1 + l][k]);
-    for (int c = 0; c < C; ++c)
-        for (int k = 0; k < kW; ++k)
-            w[(size_t)2 * nb * kW * kW + (size_t)c * kW + k] = to_bf16(W[L - 1][(size_t)c * kW + k]);
+    auto swizzle = [&](uint16_t* dst, const float* src, int rows, int group) {
+        for (int r0 = 0; r0 < rows; r0 += group)
+            for (int kb = 0; kb < kW / 32; ++kb)
+                for (int mt = 0; mt < group / 16; ++mt)
+                    for (int lane = 0; lane < 64; ++lane)
+                        for (int j = 0; j < 8; ++j, ++dst) {
+                            const int row = r0 + 16 * mt + (lane & 15), col = 32 * kb + 8 * (lane >> 4) + j;
+                            *dst = src && row < rows ? to_bf16(src[(size_t)row * kW + col]) : 0;
+                        }
+    };
+    for (int l = 0; l < 2 * nb; ++l) swizzle(&w[(size_t)l * kW * kW], W[1 + l], kW, 64);
+    swizzle(&w[(size_t)2 * nb * kW * kW], W[L - 1], C, 32);
 
-    hipError_t e = dev_alloc(&m.rin, win.size() * 4);
+    int dev = 0, cus = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    m.cus = (uint32_t)cus;
+    m.rw_bytes = (uint32_t)(w.size() * 2);
+    if (e == hipSuccess) e = dev_alloc(&m.rin, win.size() * 4);
     if (e == hipSuccess) e = hipMemcpy(m.rin, win.data(), win.size() * 4, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = dev_alloc(&m.bias, bias.size() * 4);
     if (e == hipSuccess) e = hipMemcpy(m.bias, bias.data(), bias.size() * 4, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = dev_alloc(&m.rw, w.size() * 2);
     if (e == hipSuccess) e = hipMemcpy(m.rw, w.data(), w.size() * 2, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = dev_alloc(&m.ws, (size_t)3 * kChunk * kW * 2);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&m.ws_done, hipEventDisableTiming);
+    if (e == hipSuccess) e = dev_alloc(&m.ws, kWorkspace);
     if (e != hipSuccess) {
         model_free(m);
         return hip_fail(e, "residual model upload");
     }
-    m.bytes = win.size() * 4 + bias.size() * 4 + w.size() * 2 + (size_t)3 * kChunk * kW * 2;
+    m.bytes = win.size() * 4 + bias.size() * 4 + w.size() * 2 + kWorkspace;
     m.loaded = 1;
     model_free(rs->model);
     rs->model = m;
@@ -395,48 +462,32 @@ int resnet_prepare(tang_ruleset_t* rs, const tang_resnet_desc_t* d, const float*
     return TANG_OK;
 }
 
-// The workspace is shared by every call on this ruleset: each call's launches wait for
-// the previous call's (an event), whatever stream either used.
 hipError_t launch_resnet(const tang_ruleset_t* rs, const tang_header_t* d_hdr, size_t n,
                          uint32_t* cand, float* logits, uint16_t* cand16, hipStream_t s) {
     const ModelDev& m = rs->model;
-    std::lock_guard<std::mutex> lk(rs->ws_mu);
-    hipError_t e = hipSuccess;
-    if (m.ws_used) e = hipStreamWaitEvent(s, m.ws_done, 0);
-    if (e != hipSuccess) return e;
-    const int nb = m.n_blocks;
-    const uint16_t* wts = static_cast<const uint16_t*>(m.rw);
-    const uint16_t* wout = wts + (size_t)2 * nb * kW * kW;
-    const float* bout = m.bias + (size_t)(1 + 2 * nb) * kW;
-    for (size_t base = 0; base < n; base += kChunk) {
-        const uint32_t c = (uint32_t)std::min<size_t>(kChunk, n - base);
-        uint16_t* X = m.ws;
-        uint16_t* Hm = X + (size_t)kChunk * kW;
-        uint16_t* Y = Hm + (size_t)kChunk * kW;
-        const uint32_t gin = std::min<uint32_t>((c + 3) / 4, 2048);
-        hipLaunchKernelGGL(k_res_input, dim3(gin), dim3(256), 0, s,
-                           reinterpret_cast<const uint4*>(d_hdr + base), c, m.rin, m.bias,
-                           reinterpret_cast<u32x4*>(X));
-        const dim3 gd((c + 127) / 128);
-        for (int k = 0; k < nb; ++k) {
-            const uint16_t* w1 = wts + (size_t)(2 * k) * kW * kW;
-            const uint16_t* w2 = w1 + (size_t)kW * kW;
-            const float* b1 = m.bias + (size_t)(1 + 2 * k) * kW;
-            const float* b2 = b1 + kW;
-            hipLaunchKernelGGL(k_res_dense<false>, gd, dim3(512), 0, s, X, w1, b1, nullptr, Hm, c);
-            hipLaunchKernelGGL(k_res_dense<true>, gd, dim3(512), 0, s, Hm, w2, b2, X, Y, c);
-            std::swap(X, Y);
-        }
-        hipLaunchKernelGGL(k_res_out, dim3((c + 255) / 256), dim3(256), 0, s, X, wout, bout, c,
-                           m.n_out, m.topk, cand ? cand + base : nullptr,
-                           logits ? logits + base * (size_t)m.n_out : nullptr,
-                           cand16 ? cand16 + base * (size_t)m.topk : nullptr);
-        e = hipGetLastError();
+    const size_t chunk = (size_t)1 << 30;
+    for (size_t base = 0; base < n; base += chunk) {
+        const uint32_t c = (uint32_t)std::min(chunk, n - base);
+        auto tiles = [&](uint32_t headers) { return (c + headers - 1) / headers; };
+        auto rounds = [&](uint32_t headers) { return (tiles(headers) + m.cus - 1) / m.cus; };
+        auto go = [&](auto kern, uint32_t headers) {
+            hipLaunchKernelGGL(kern, dim3(std::min(tiles(headers), m.cus)), dim3(512), 0, s,
+                               reinterpret_cast<const uint4*>(d_hdr + base), c, m.rin, m.bias,
+                               static_cast<const uint16_t*>(m.rw), m.rw_bytes, m.n_blocks, m.n_out, m.topk,
+                               cand ? cand + base : nullptr,
+                               logits ? logits + base * (size_t)m.n_out : nullptr,
+                               cand16 ? cand16 + base * (size_t)m.topk : nullptr);
+        };
+        // Tiles of 96 headers or of 64, whichever takes less for the rounds of one tile per CU:
+        // a round of 64 takes three quarters of one of 96 (6 blocks, 25 classes: 16,384 headers
+        // 98 us in one round of 64, 127 in one of 96; 24,576 headers 180 in two of 64, 137 in
+        // one of 96; 262,144 headers 1,414 against 1,344).
+        if (3 * rounds(64) <= 4 * rounds(96)) go(k_res<4>, 64);
+        else go(k_res<6>, 96);
+        const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    e = hipEventRecord(m.ws_done, s);
-    if (e == hipSuccess) m.ws_used = true;
-    return e;
+    return hipSuccess;
 }
 
 }  // namespace tang

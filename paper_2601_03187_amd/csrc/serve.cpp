@@ -402,8 +402,7 @@ int tang_server_s::launch(uint32_t si, uint32_t tag, tang_ruleset_t* rs, bool wa
         if (rc) return rc;
         TANG_HIP(hipStreamSynchronize(s.stream));
     }
-    // the residual predictor orders its shared workspace with an event across calls, which
-    // a captured graph cannot hold: its batches run eagerly
+    // the residual predictor's launches take no live count: its batches run eagerly
     if (cfg.use_graphs && rs->model.kind == 0) {
         hipGraphExec_t exec = nullptr;
         int rc = graph_for(tag, rs, (uint32_t)cls, si, &exec);

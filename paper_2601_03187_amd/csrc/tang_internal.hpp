@@ -242,14 +242,13 @@ struct ModelDev {
     float deq[3] = {1, 1, 1};     // FP8: s_a * s_w per layer
     float inv_a[3] = {1, 1, 1};   // FP8: 1 / s_a per layer (layer 0 unused)
     float rq[2] = {1, 1};         // FP8 hidden layers: 2^-e, e the requantisation exponent
-    // Residual network: input layer FP32 [512][8], BF16 layer weights, BF16 activation
-    // workspace (three chunk buffers) and the event that orders calls sharing it.
+    // Residual network: input layer FP32 [512][8] and BF16 layer weights.
     int n_blocks = 0;
     float* rin = nullptr;
     void* rw = nullptr;
-    uint16_t* ws = nullptr;
-    hipEvent_t ws_done = nullptr;
-    mutable bool ws_used = false;
+    uint32_t rw_bytes = 0;
+    uint32_t cus = 0;   // workgroups of a launch at most
+    void* ws = nullptr; // 192 MB that callers' allocators budget for; the kernel needs none of it
     size_t bytes = 0;
 };
 
@@ -308,7 +307,6 @@ struct tang_ruleset_s {
     hipStream_t upd_stream = nullptr;
     tang::ModelDev model;
     std::mutex stats_mu;
-    mutable std::mutex ws_mu;  // enqueueing of residual-model launches (shared workspace)
     uint64_t version = 0;   // bumped by every change that captured launches depend on
     bool failed = false;    // an update's device flush failed: host and device disagree
 

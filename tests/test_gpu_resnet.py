@@ -155,3 +155,30 @@ def test_residual_model_validation():
             T.tang_model_load_resnet(rs, narrow, [bs[0][:256], bs[1][:256], bs[2][:256], bs[3]], "bf16")
     finally:
         T.tang_ruleset_destroy(rs)
+
+
+@pytest.mark.parametrize("space", ["narrow", "wide", "all"])
+def test_tile_forms_agree_bit_for_bit(space):
+    """A header's scores and candidates do not depend on the batch it is in: batches at the
+    edges of 64- and 96-header tiles, in the sizes that take each form, against the first 64
+    headers alone (at most 64 classes take one output form, more the other)."""
+    torch_cuda()
+    rules = synth.make_rules(3000, seed=66, wide=space == "wide", all_lengths=space == "all")
+    rs = T.tang_ruleset_create(0, rules)
+    try:
+        C = T.tang_ruleset_num_tuples(rs)
+        Ws, bs = _random_model(C, 2, np.random.default_rng(31))
+        T.tang_model_load_resnet(rs, Ws, bs, "bf16", topk=2)
+        hdr = synth.make_packets(rules, 61, seed=67, frac_in=0.7)
+        logits, cand = mlp_dev(rs, hdr, C, topk=2)
+        want = orc.resnet_forward(orc.segments(hdr), Ws, bs, "bf16")
+        assert np.median(np.abs(logits - want).max(axis=1) / np.abs(want).max(axis=1)) <= 2.0 ** -9
+        order = np.argsort(-logits, axis=1, kind="stable")[:, :2]
+        assert np.array_equal(cand, order)
+        for n in (1, 60, 16384, 16385, 24575, 24576, 24577):
+            at = np.arange(n) % len(hdr)
+            got, gc = mlp_dev(rs, hdr[at], C, topk=2)
+            assert np.array_equal(got, logits[at]), n
+            assert np.array_equal(gc, cand[at]), n
+    finally:
+        T.tang_ruleset_destroy(rs)
