@@ -2,6 +2,8 @@
 // 104 -> H -> H -> C) followed by argmax / top-k over the C tuple scores (Sec. 6.1,
 // Sec. 5.1.1), for FP32, BF16 and FP8 (OCP E4M3) operands with FP32 accumulation:
 // v_mfma_f32_16x16x4_f32, v_mfma_f32_16x16x32_bf16 and v_mfma_f32_16x16x128_f8f6f4.
+// FP32 models normally run as three BF16 planes (k_mlp_split below); the FP32 instructions
+// serve weights out of the planes' range.
 //
 // Orientation: every layer computes out^T = W * in^T with output neurons as MFMA rows
 // (the A operand, weights) and packets as MFMA columns (the B operand, activations).
@@ -236,6 +238,54 @@ __device__ __forceinline__ void epi_hidden(const f4 (&acc)[NT], int mt, float rq
 }
 
 constexpr int kNoClass = 1 << 20;  // an empty or removed top-k slot (above every class)
+
+struct Scored {
+    float first;
+    int second;
+};
+// The best of the classes that the four lanes of a header hold (KL each), ties to the lower
+// class; it is taken out.
+template <int KL>
+__device__ __forceinline__ Scored take_best(float (&v)[KL], int (&cl)[KL]) {
+    float bv = v[0];
+    int bc = cl[0];
+#pragma unroll
+    for (int q = 1; q < KL; ++q)
+        if (v[q] > bv) { bv = v[q]; bc = cl[q]; }   // lower classes first
+#pragma unroll
+    for (int o = 16; o <= 32; o <<= 1) {
+        const float ov = __shfl_xor(bv, o, 64);
+        const int oc = __shfl_xor(bc, o, 64);
+        if (ov > bv || (ov == bv && oc < bc)) { bv = ov; bc = oc; }
+    }
+    // a removed class must never win again: pushed below -inf ties
+#pragma unroll
+    for (int q = 0; q < KL; ++q)
+        if (cl[q] == bc) {
+            v[q] = -INFINITY;
+            cl[q] = kNoClass;
+        }
+    return {bv, bc};
+}
+// Score val of class c into a running top-KS of ascending classes: a strictly larger score
+// displaces, so ties keep the lower class; a NaN or -inf score counts as -FLT_MAX, so every
+// real class beats an empty slot and a padded class.
+template <int KS, int KL>
+__device__ __forceinline__ void keep_best(float (&v)[KL], int (&cl)[KL], float val, int c, int C) {
+    float x = c < C ? (val == val ? fmaxf(val, -FLT_MAX) : -FLT_MAX) : -INFINITY;
+    int xc = c;
+#pragma unroll
+    for (int q = 0; q < KS; ++q) {
+        if (x > v[q]) {
+            const float tv = v[q];
+            const int tc = cl[q];
+            v[q] = x;
+            cl[q] = xc;
+            x = tv;
+            xc = tc;
+        }
+    }
+}
 
 // OUTB: most blocks of 32 output classes (1, or 16 for up to 512 tuples; the W3 fragments
 // of a multi-block model are read from L2).
@@ -496,19 +546,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_mlp(
                                 v[nt][4 * mt + r] = (c < C && val == val) ? val : -INFINITY;
                                 cl[nt][4 * mt + r] = c;
                             } else {
-                                float x = c < C ? (val == val ? fmaxf(val, -FLT_MAX) : -FLT_MAX) : -INFINITY;
-                                int xc = c;
-#pragma unroll
-                                for (int q = 0; q < KS; ++q) {
-                                    if (x > v[nt][q]) {
-                                        const float tv = v[nt][q];
-                                        const int tc = cl[nt][q];
-                                        v[nt][q] = x;
-                                        cl[nt][q] = xc;
-                                        x = tv;
-                                        xc = tc;
-                                    }
-                                }
+                                keep_best<KS>(v[nt], cl[nt], val, c, C);
                             }
                         }
                     }
@@ -524,29 +562,299 @@ __global__ __launch_bounds__(64 * WAVES) void k_mlp(
             const uint32_t pkt = pbase + nt * 16 + col;
             uint32_t packed = 0;
             for (int k = 0; k < a.topk; ++k) {
-                float bv = v[nt][0];
-                int bc = cl[nt][0];
-#pragma unroll
-                for (int q = 1; q < KL; ++q)
-                    if (v[nt][q] > bv) { bv = v[nt][q]; bc = cl[nt][q]; }   // lower classes first
-#pragma unroll
-                for (int o = 16; o <= 32; o <<= 1) {
-                    const float ov = __shfl_xor(bv, o, 64);
-                    const int oc = __shfl_xor(bc, o, 64);
-                    if (ov > bv || (ov == bv && oc < bc)) { bv = ov; bc = oc; }
-                }
+                const int bc = take_best<KL>(v[nt], cl[nt]).second;
                 packed |= (uint32_t)bc << (cand_bits(C) * k);
                 if (cand16 && g == 0 && pkt < n) cand16[(size_t)pkt * a.topk + k] = (uint16_t)bc;
-#pragma unroll
-                for (int q = 0; q < KL; ++q)
-                    if (cl[nt][q] == bc) v[nt][q] = -INFINITY;
-                // a removed class must never win again: push it below -inf ties
-#pragma unroll
-                for (int q = 0; q < KL; ++q)
-                    if (cl[nt][q] == bc) cl[nt][q] = kNoClass;
             }
             if (cand && g == 0 && pkt < n) cand[pkt] = packed;
         }
+    }
+}
+
+// ---------------------------------------------------------------------------------------
+// FP32 on the BF16 matrix units. Weights and activations are held as three BF16 planes that
+// sum to the FP32 value (hi = the value rounded to BF16, mid = the rest rounded, lo = the
+// rest of that, which fits), and a product is the six plane products above 2^-27 of it:
+// hi hi in one accumulator, hi mid, mid hi, hi lo, lo hi and mid mid in another, added at the
+// end. The plane products are exact, the accumulation stays FP32, and the large sum is
+// rounded once per 32 inputs where the FP32 instruction rounds it once per 4. Measured
+// against 64 bits (norm of the error over norm of the scores; 25, 144 and 387 classes alike):
+// 1.2e-7 at hidden 128 and 1.4e-7 at 256; the FP32 instructions have 2.2e-7 and 3.0e-7.
+// The input layer's inputs are bits, one plane each.
+//
+// Workgroup: 8 waves and 16 NT headers; a wave computes 32 neurons of both hidden layers, for
+// all of the headers (H = 256) or half of them (128). LDS holds one layer's activations, three planes of B fragments
+// (fragment (plane, kb, nt): 1 KB, lane l's 16 bytes at 16 l); a layer overwrites its input
+// between two barriers. Weight fragments stream from L2, a K block ahead, across the layers'
+// ends too.
+// What bounds it (hidden 256, 25 classes, 1,048,576 headers: 826 us; the FP32 instructions
+// took 1,427): MFMA issue, 1,056 of 16 cycles per 16 headers, about 60% of the time; the
+// barriers between the layers expose the rest, and with fewer headers per workgroup the
+// weights' 42 bytes per cycle from L2. 10,000 headers: 17 against 54 us.
+__device__ __forceinline__ void lds_barrier() {
+    // every wave's LDS accesses done; weight loads in flight stay in flight
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// Two values' planes, packed in pairs.
+__device__ __forceinline__ void split_pair(float a, float b, uint32_t (&p)[3]) {
+#pragma unroll
+    for (int pl = 0; pl < 3; ++pl) {
+        p[pl] = pack_bf16(a, b);
+        a -= __uint_as_float(p[pl] << 16);
+        b -= __uint_as_float(p[pl] & 0xFFFF0000u);
+    }
+}
+
+template <int H, int NT, int OCC, int KS>
+__global__ __launch_bounds__(512, OCC) void k_mlp_split(
+    const uint4* __restrict__ hdr, uint32_t n, const u32x4* __restrict__ w1, const u32x4* __restrict__ w2,
+    const u32x4* __restrict__ w3, const float* __restrict__ bias, int C, int topk, uint32_t* __restrict__ cand,
+    float* __restrict__ logits, uint16_t* __restrict__ cand16, const uint32_t* __restrict__ live) {
+    constexpr int KBH = H / 32, MT = 2;
+    constexpr uint32_t TH = 16u * NT;
+    constexpr uint32_t WN = H / 32, WH = 8 / WN;   // waves over the neurons and over the headers
+    constexpr int NTW = NT / (int)WH;
+    static_assert(NT % WH == 0, "the header columns divide over the waves");
+    __shared__ u32x4 act[3 * KBH * NT * 64];
+    __shared__ __attribute__((aligned(16))) float sbias[2 * H + (KS ? TANG_MAX_TUPLES : kOutPad)];
+    __shared__ __attribute__((aligned(16))) unsigned char stab[256 * Bits<TANG_BF16>::kEntry];
+    if (live) n = min(n, *live);
+    const uint32_t tiles = (n + TH - 1) / TH;
+    if (blockIdx.x >= tiles) return;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, g = lane >> 4, r = lane & 15u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t wn = wave % WN, nt0 = wave / WN * NTW;
+    const int ncb = (C + 31) / 32;
+    const __amdgpu_buffer_rsrc_t r1 = __builtin_amdgcn_make_buffer_rsrc((void*)w1, 0, (H / 16) * 12 * 1024, 0x00020000);
+    const __amdgpu_buffer_rsrc_t r2 = __builtin_amdgcn_make_buffer_rsrc((void*)w2, 0, (H / 16) * KBH * 3072, 0x00020000);
+    const __amdgpu_buffer_rsrc_t r3 = __builtin_amdgcn_make_buffer_rsrc((void*)w3, 0, ncb * 2 * KBH * 3072, 0x00020000);
+    u32x4 A[2][MT][3];   // K block kb's weight fragments, loaded a block ahead
+    auto load_a = [&](__amdgpu_buffer_rsrc_t rs, int buf, uint32_t mt0, int kbs, int kb) {
+#pragma unroll
+        for (int u = 0; u < MT; ++u)
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl)
+                A[buf][u][pl] = __builtin_amdgcn_raw_buffer_load_b128(
+                    rs, lane * 16u, (((mt0 + u) * kbs + kb) * 3u + pl) * 1024u, 0);
+    };
+    load_a(r1, 0, wn * MT, 4, 0);
+    for (uint32_t k = tid; k < 2u * H + 32u * ncb; k += 512u) sbias[k] = bias[k];
+    if (tid < 256u) Bits<TANG_BF16>::entry(tid, stab + tid * Bits<TANG_BF16>::kEntry);
+    lds_barrier();
+    u32x2* const act8 = reinterpret_cast<u32x2*>(act);
+    for (uint32_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        const uint32_t p0 = tile * TH;
+        // ReLU of a hidden layer's rows and their planes, to the next layer's B fragments
+        auto store = [&](int u, int nt, const f4& acc) {
+            const uint32_t mt = wn * MT + u;
+            uint32_t p[2][3];
+            split_pair(fmaxf(acc[0], 0.0f), fmaxf(acc[1], 0.0f), p[0]);
+            split_pair(fmaxf(acc[2], 0.0f), fmaxf(acc[3], 0.0f), p[1]);
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl)
+                act8[(((pl * KBH + (mt >> 1)) * NT + nt0 + nt) * 64u + (2u * (mt & 1u) + (g >> 1)) * 16u + r) * 2u + (g & 1u)] =
+                    (u32x2){p[0][pl], p[1][pl]};
+        };
+        {   // input layer
+            uint4 hv[NTW];
+#pragma unroll
+            for (int nt = 0; nt < NTW; ++nt) {
+                const uint32_t p = p0 + (nt0 + nt) * 16 + r;
+                hv[nt] = p < n ? hdr[p] : make_uint4(0u, 0u, 0u, 0u);
+            }
+            f4 acc[MT][NTW];
+#pragma unroll
+            for (int u = 0; u < MT; ++u)
+#pragma unroll
+                for (int nt = 0; nt < NTW; ++nt) acc[u][nt] = *reinterpret_cast<const f4*>(sbias + 16 * (wn * MT + u) + 4 * g);
+#pragma unroll
+            for (int kb = 0; kb < 4; ++kb) {
+                if (kb < 3) load_a(r1, (kb + 1) & 1, wn * MT, 4, kb + 1);
+                else load_a(r2, 0, wn * MT, KBH, 0);
+#pragma unroll
+                for (int nt = 0; nt < NTW; ++nt) {
+                    const u32x4 xb = Bits<TANG_BF16>::get(hv[nt], kb, g, stab);
+#pragma unroll
+                    for (int pl = 0; pl < 3; ++pl)
+#pragma unroll
+                        for (int u = 0; u < MT; ++u) acc[u][nt] = mma(A[kb & 1][u][pl], xb, acc[u][nt]);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int u = 0; u < MT; ++u)
+#pragma unroll
+                for (int nt = 0; nt < NTW; ++nt) store(u, nt, acc[u][nt]);
+        }
+        lds_barrier();
+        // six plane products of K block kb: weights a, activations b
+        auto six = [&](const u32x4 (&a)[3], const u32x4 (&b)[3], f4& big, f4& small) {
+            small = mma(a[2], b[0], small);
+            small = mma(a[0], b[2], small);
+            small = mma(a[1], b[1], small);
+            small = mma(a[1], b[0], small);
+            small = mma(a[0], b[1], small);
+            big = mma(a[0], b[0], big);
+        };
+        auto acts = [&](int kb, int nt, u32x4 (&b)[3]) {
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl) b[pl] = act[((pl * KBH + kb) * NT + nt) * 64 + lane];
+        };
+        u32x4 O[2][3];   // KS: the output layer's fragments, two K blocks ahead
+        auto load_o = [&](int buf, int ct, int kb) {
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl)
+                O[buf][pl] = __builtin_amdgcn_raw_buffer_load_b128(r3, lane * 16u, (((uint32_t)ct * KBH + kb) * 3u + pl) * 1024u, 0);
+        };
+        {   // hidden layer
+            f4 big[MT][NTW], small[MT][NTW];
+#pragma unroll
+            for (int u = 0; u < MT; ++u)
+#pragma unroll
+                for (int nt = 0; nt < NTW; ++nt) {
+                    big[u][nt] = *reinterpret_cast<const f4*>(sbias + H + 16 * (wn * MT + u) + 4 * g);
+                    small[u][nt] = (f4){0, 0, 0, 0};
+                }
+#pragma unroll
+            for (int kb = 0; kb < KBH; ++kb) {
+                if (kb + 1 < KBH) load_a(r2, (kb + 1) & 1, wn * MT, KBH, kb + 1);
+                else if constexpr (KS == 0) load_a(r3, 0, 0u, KBH, 0);
+#pragma unroll
+                for (int nt = 0; nt < NTW; ++nt) {
+                    u32x4 b[3];
+                    acts(kb, nt0 + nt, b);
+#pragma unroll
+                    for (int u = 0; u < MT; ++u) six(A[kb & 1][u], b, big[u][nt], small[u][nt]);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if constexpr (KS != 0) {
+                load_o(0, (int)wave, 0);
+                load_o(1, (int)wave, 1);
+            }
+            lds_barrier();   // every wave has read the layer's input
+#pragma unroll
+            for (int u = 0; u < MT; ++u)
+#pragma unroll
+                for (int nt = 0; nt < NTW; ++nt) store(u, nt, big[u][nt] + small[u][nt]);
+        }
+        lds_barrier();
+        // Output layer in blocks of 32 classes: with one block, wave w takes header column w;
+        // with more, 16-class tiles w, w + 8, .. for all headers, and the waves' top-k lists are
+        // merged through LDS.
+        if constexpr (KS == 0) {
+            if (wave < (uint32_t)NT) {
+                const uint32_t nt = wave, pkt = p0 + 16u * nt + r;
+                f4 big[2], small[2];
+#pragma unroll
+                for (int u = 0; u < 2; ++u) big[u] = small[u] = (f4){0, 0, 0, 0};
+#pragma unroll
+                for (int kb = 0; kb < KBH; ++kb) {
+                    if (kb + 1 < KBH) load_a(r3, (kb + 1) & 1, 0, KBH, kb + 1);
+                    u32x4 b[3];
+                    acts(kb, nt, b);
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) six(A[kb & 1][u], b, big[u], small[u]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                float v[8];
+                int cl[8];
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int c = 16 * u + 4 * (int)g + q;
+                        const float val = (big[u][q] + small[u][q]) + sbias[2 * H + c];
+                        if (logits && pkt < n && c < C) logits[(size_t)pkt * C + c] = val;
+                        v[4 * u + q] = (c < C && val == val) ? val : -INFINITY;
+                        cl[4 * u + q] = c;
+                    }
+                uint32_t packed = 0;
+                for (int k = 0; k < topk; ++k) {
+                    const int bc = take_best<8>(v, cl).second;
+                    packed |= (uint32_t)bc << (8 * k);
+                    if (cand16 && g == 0 && pkt < n) cand16[(size_t)pkt * topk + k] = (uint16_t)bc;
+                }
+                if (cand && g == 0 && pkt < n) cand[pkt] = packed;
+            }
+        } else {
+            float v[NT][KS];
+            int cl[NT][KS];
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int q = 0; q < KS; ++q) {
+                    v[nt][q] = -INFINITY;
+                    cl[nt][q] = kNoClass;
+                }
+#pragma unroll 1
+            for (int ct = (int)wave; ct < (C + 15) / 16; ct += 8) {
+                f4 big[NT], small[NT];
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) big[nt] = small[nt] = (f4){0, 0, 0, 0};
+#pragma unroll
+                for (int kb = 0; kb < KBH; ++kb) {
+                    u32x4 a[3];
+#pragma unroll
+                    for (int pl = 0; pl < 3; ++pl) a[pl] = O[kb & 1][pl];
+                    if (kb + 2 < KBH) load_o(kb & 1, ct, kb + 2);
+                    else load_o(kb & 1, ct + 8, kb + 2 - KBH);   // past the last tile: zeros
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) {
+                        u32x4 b[3];
+                        acts(kb, nt, b);
+                        six(a, b, big[nt], small[nt]);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                const f4 b3 = *reinterpret_cast<const f4*>(sbias + 2 * H + 16 * ct + 4 * g);
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                    const uint32_t pkt = p0 + 16u * nt + r;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int c = 16 * ct + 4 * (int)g + q;
+                        const float val = (big[nt][q] + small[nt][q]) + b3[q];
+                        if (logits && pkt < n && c < C) logits[(size_t)pkt * C + c] = val;
+                        keep_best<KS>(v[nt], cl[nt], val, c, C);
+                    }
+                }
+            }
+            lds_barrier();
+            u32x2* const tops = act8;   // [wave][header][4], over the activations
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+                for (int k = 0; k < topk; ++k) {
+                    const Scored b = take_best<KS>(v[nt], cl[nt]);
+                    if (g == 0) tops[(wave * TH + 16u * nt + r) * 4u + k] = (u32x2){__float_as_uint(b.first), (uint32_t)b.second};
+                }
+            lds_barrier();
+            const uint32_t pkt = p0 + tid;
+            if (tid < TH && pkt < n) {
+                uint32_t packed = 0;
+                float lv = INFINITY;
+                int lc = -1;
+                for (int k = 0; k < topk; ++k) {
+                    float bv = -INFINITY;
+                    int bc = kNoClass;
+                    for (uint32_t x = 0; x < 8u * topk; ++x) {
+                        const u32x2 t = tops[((x / topk) * TH + tid) * 4u + x % topk];
+                        const float tv = __uint_as_float(t[0]);
+                        const int tc = (int)t[1];
+                        const bool left = tv < lv || (tv == lv && tc > lc);   // not picked yet
+                        if (left && (tv > bv || (tv == bv && tc < bc))) { bv = tv; bc = tc; }
+                    }
+                    lv = bv;
+                    lc = bc;
+                    packed |= (uint32_t)bc << (cand_bits(C) * k);
+                    if (cand16) cand16[(size_t)pkt * topk + k] = (uint16_t)bc;
+                }
+                if (cand) cand[pkt] = packed;
+            }
+        }
+        load_a(r1, 0, wn * MT, 4, 0);
+        lds_barrier();   // the next tile's input layer overwrites the activations
     }
 }
 
@@ -584,6 +892,34 @@ int in_col(int prec, int layer, int kb, int g, int j) {
     if (prec == TANG_BF16)
         return layer == 0 ? 32 * kb + 8 * g + j : 16 * (2 * kb + (j >> 2)) + 4 * g + (j & 3);
     return layer == 0 ? 128 * kb + 32 * g + j : 16 * (8 * kb + (j >> 2)) + 4 * g + (j & 3);
+}
+
+// The BF16 planes of an FP32 value (see k_mlp_split): each rounded, the last one exact.
+void planes(float w, uint16_t (&q)[3]) {
+    for (int pl = 0; pl < 3; ++pl) {
+        q[pl] = f32_to_bf16(w);
+        const uint32_t u = (uint32_t)q[pl] << 16;
+        float back;
+        std::memcpy(&back, &u, 4);
+        w -= back;
+    }
+}
+
+// Whether every value the FP32 network can meet stays far from BF16's range limits, where
+// the planes would overflow or vanish: finite weights, bounded hidden outputs.
+bool can_split(const tang_mlp_desc_t* d, const float* const* W, const float* const* b) {
+    double in = 1.0;   // largest input of the layer
+    for (int l = 0; l < 3; ++l) {
+        double most = 0.0;
+        for (uint32_t o = 0; o < d->dims[l + 1]; ++o) {
+            double sum = std::fabs((double)b[l][o]);
+            for (uint32_t i = 0; i < d->dims[l]; ++i) sum += in * std::fabs((double)W[l][(size_t)o * d->dims[l] + i]);
+            if (!(sum < 1e30)) return false;   // NaN and infinities too
+            most = std::max(most, sum);
+        }
+        in = most;
+    }
+    return true;
 }
 
 }  // namespace
@@ -645,7 +981,28 @@ int model_prepare(tang_ruleset_t* rs, const tang_mlp_desc_t* d, const float* con
     const int outs[3] = {H, H, C}, ins[3] = {104, H, H};
     const int outp[3] = {H, H, CP}, inp[3] = {kInPad, H, H};
     m.w3frags = (uint32_t)(CP / 16 * (H / KB) * 64);
+    m.split = p == TANG_FP32 && can_split(d, W, b);
     for (int l = 0; l < 3; ++l) {
+        if (m.split) {
+            // three planes per fragment: [row tile][K block][plane], lane (g, r) row r, columns
+            // 8g..8g+7 of the block (layer 0: the input bits' order, which is the same)
+            const int MT = outp[l] / 16, KBN = inp[l] / 32;
+            std::vector<uint16_t> buf((size_t)MT * KBN * 3 * 512, 0);
+            for (int row = 0; row < outs[l]; ++row)
+                for (int c = 0; c < ins[l]; ++c) {
+                    uint16_t q[3];
+                    planes(W[l][(size_t)row * ins[l] + c], q);
+                    const size_t frag = ((size_t)(row / 16) * KBN + c / 32) * 3;
+                    const size_t at = ((size_t)((c % 32) / 8) * 16 + row % 16) * 8 + c % 8;
+                    for (int pl = 0; pl < 3; ++pl) buf[(frag + pl) * 512 + at] = q[pl];
+                }
+            hipError_t e = dev_alloc(&m.w[l], buf.size() * 2);
+            if (e == hipSuccess) e = hipMemcpy(m.w[l], buf.data(), buf.size() * 2, hipMemcpyHostToDevice);
+            if (e != hipSuccess) { model_free(m); return hip_fail(e, "model upload"); }
+            m.wbytes[l] = buf.size() * 2;
+            m.bytes += buf.size() * 2;
+            continue;
+        }
         float s_w = 1.0f, inv_w = 1.0f, s_a = 1.0f;
         if (p == TANG_FP8) {
             float amax = 0.0f;
@@ -695,7 +1052,7 @@ int model_prepare(tang_ruleset_t* rs, const tang_mlp_desc_t* d, const float* con
         m.wbytes[l] = buf.size();
         m.bytes += buf.size();
     }
-    if (p == TANG_FP32) {
+    if (p == TANG_FP32 && !m.split) {
         // W1 as three BF16 planes in BF16 layer-0 fragment order: hi = w cut to BF16
         // (low 16 bits dropped), mid = (w - hi) cut likewise, lo = w - hi - mid. Each
         // difference is exact in FP32 and lo keeps at most 8 significant bits, so
@@ -788,6 +1145,21 @@ hipError_t launch_t(const ModelDev& m, const tang_header_t* d_hdr, uint32_t n, u
     return hipGetLastError();
 }
 
+template <int H, int NT, int OCC, int KS = 0>
+hipError_t launch_split(const ModelDev& m, const tang_header_t* d_hdr, uint32_t n, uint32_t* cand, float* logits,
+                        uint16_t* cand16, hipStream_t s, const uint32_t* live) {
+    int dev = 0, cus = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e != hipSuccess) return e;
+    const uint32_t tiles = (n + 16 * NT - 1) / (16 * NT);
+    const uint32_t grid = std::max<uint32_t>(1, std::min<uint32_t>(tiles, (uint32_t)cus * (OCC / 2)));
+    hipLaunchKernelGGL((k_mlp_split<H, NT, OCC, KS>), dim3(grid), dim3(512), 0, s, reinterpret_cast<const uint4*>(d_hdr),
+                       n, (const u32x4*)m.w[0], (const u32x4*)m.w[1], (const u32x4*)m.w[2], m.bias, m.n_out, m.topk,
+                       cand, logits, cand16, live);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t launch_mlp(const tang_ruleset_t* rs, const tang_header_t* d_hdr, size_t n,
@@ -816,7 +1188,25 @@ hipError_t launch_mlp(const tang_ruleset_t* rs, const tang_header_t* d_hdr, size
         // workgroup of 512 headers would leave half of the CUs idle on a 65,536-header batch.
         // More than 32 tuples: up to 16 blocks of 32 classes, W3 read from L2.
         const bool wide = m.n_out > kOutPad;
-        if (wide) {
+        // FP32 on BF16 planes: tiles of 16 NT headers, OCC waves per SIMD (two workgroups per CU
+        // at 4). Small batches take small tiles, so that every CU has one: hidden 256, 4,096
+        // headers 13 us with 32 per tile, 15 with 48, 22 with 96; 131,072 headers 149, 131 and
+        // 134; 1,048,576 974, 857 and 826. Hidden 128, 10,000 headers 9.5 us with 64, 11.3
+        // with 96; 1,048,576 359 and 318. More than 32 classes: 64 per tile (144 classes,
+        // 524,288 headers, hidden 256: 713 us, 750 with 48 and four waves, 703 with 96, which
+        // takes 36 against 26 for 10,000).
+        if (m.split) {
+            const bool one = m.topk == 1;
+            if (m.hidden == 128 && wide && one) e = launch_split<128, 4, 2, 1>(m, h, k, c, lg, c8, s, d_live);
+            else if (m.hidden == 128 && wide) e = launch_split<128, 4, 2, 4>(m, h, k, c, lg, c8, s, d_live);
+            else if (m.hidden == 128 && k <= 16384) e = launch_split<128, 4, 4>(m, h, k, c, lg, c8, s, d_live);
+            else if (m.hidden == 128) e = launch_split<128, 6, 4>(m, h, k, c, lg, c8, s, d_live);
+            else if (wide && one) e = launch_split<256, 4, 2, 1>(m, h, k, c, lg, c8, s, d_live);
+            else if (wide) e = launch_split<256, 4, 2, 4>(m, h, k, c, lg, c8, s, d_live);
+            else if (k <= 8192) e = launch_split<256, 2, 4>(m, h, k, c, lg, c8, s, d_live);
+            else if (k < (1u << 18)) e = launch_split<256, 3, 4>(m, h, k, c, lg, c8, s, d_live);
+            else e = launch_split<256, 6, 2>(m, h, k, c, lg, c8, s, d_live);
+        } else if (wide) {
             if (m.prec == TANG_FP32 && m.hidden == 128) e = launch_t<TANG_FP32, 128, 2, 2, 8,16>(m, h, k, c, lg, c8, s, d_live);
             else if (m.prec == TANG_FP32) e = launch_t<TANG_FP32, 256, 1, 0, 8,16>(m, h, k, c, lg, c8, s, d_live);
             else if (m.prec == TANG_BF16 && m.hidden == 128) e = launch_t<TANG_BF16, 128, 2, 3, 8,16>(m, h, k, c, lg, c8, s, d_live);
