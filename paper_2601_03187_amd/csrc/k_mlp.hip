@@ -118,12 +118,19 @@ template <> struct Bits<TANG_BF16> {
     // features 32kb + 8g + j (j = 0..7): byte 4kb + g, bit (from the MSB) j; a table entry
     // is 4 words, each two BF16 (1.0 = 0x3F80) for bits 2w and 2w + 1 of the byte
     static constexpr int kEntry = 16;
-    __device__ static __forceinline__ void entry(uint32_t byte, unsigned char* dst) {
+    __device__ static __forceinline__ u32x4 expand(uint32_t byte) {
         u32x4 r;
 #pragma unroll
         for (int w = 0; w < 4; ++w)
             r[w] = ((byte >> (7 - 2 * w)) & 1u) * 0x3F80u | ((byte >> (6 - 2 * w)) & 1u) * 0x3F800000u;
-        *reinterpret_cast<u32x4*>(dst) = r;
+        return r;
+    }
+    __device__ static __forceinline__ void entry(uint32_t byte, unsigned char* dst) {
+        *reinterpret_cast<u32x4*>(dst) = expand(byte);
+    }
+    // the fragment without the table
+    __device__ static __forceinline__ u32x4 make(const uint4& h, int kb, int g) {
+        return expand((hword(h, kb) >> (24 - 8 * g)) & 0xFFu);
     }
     __device__ static __forceinline__ u32x4 get(const uint4& h, int kb, int g, const unsigned char* tab) {
         const uint32_t byte = (hword(h, kb) >> (24 - 8 * g)) & 0xFFu;
@@ -135,7 +142,7 @@ template <> struct Bits<TANG_FP8> {
     // most significant first; 1.0 in E4M3 is 0x38. A table entry is the 8 bytes of one
     // header byte's bits (two words of the fragment).
     static constexpr int kEntry = 8;
-    __device__ static __forceinline__ void entry(uint32_t byte, unsigned char* dst) {
+    __device__ static __forceinline__ u32x2 expand(uint32_t byte) {
         u32x2 r;
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
@@ -144,7 +151,22 @@ template <> struct Bits<TANG_FP8> {
             for (int b = 0; b < 4; ++b) v |= ((byte >> (7 - 4 * half - b)) & 1u) * (0x38u << (8 * b));
             r[half] = v;
         }
-        *reinterpret_cast<u32x2*>(dst) = r;
+        return r;
+    }
+    __device__ static __forceinline__ void entry(uint32_t byte, unsigned char* dst) {
+        *reinterpret_cast<u32x2*>(dst) = expand(byte);
+    }
+    __device__ static __forceinline__ u32x8 make(const uint4& h, int, int g) {
+        const uint32_t w = g == 0 ? h.x : g == 1 ? h.y : g == 2 ? ((h.z << 16) | (h.z >> 16))
+                                                                : ((h.w & 0xFFu) << 24);
+        u32x8 r;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const u32x2 e = expand((w >> (24 - 8 * k)) & 0xFFu);
+            r[2 * k] = e[0];
+            r[2 * k + 1] = e[1];
+        }
+        return r;
     }
     __device__ static __forceinline__ u32x8 get(const uint4& h, int, int g, const unsigned char* tab) {
         const uint32_t w = g == 0 ? h.x : g == 1 ? h.y : g == 2 ? ((h.z << 16) | (h.z >> 16))
@@ -237,6 +259,11 @@ __device__ __forceinline__ void epi_hidden(const f4 (&acc)[NT], int mt, float rq
     }
 }
 
+// Every wave's LDS accesses done; loads in flight stay in flight (__syncthreads would wait).
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
 constexpr int kNoClass = 1 << 20;  // an empty or removed top-k slot (above every class)
 
 struct Scored {
@@ -285,6 +312,43 @@ __device__ __forceinline__ void keep_best(float (&v)[KL], int (&cl)[KL], float v
             xc = tc;
         }
     }
+}
+
+// Where a header's classes are spread over 8 waves: each wave's top-k of its classes to LDS
+// ([wave][header][KS]), then one thread per header picks from the eight lists.
+template <int NT, int KS>
+__device__ __forceinline__ void put_tops(u32x2* tops, float (&v)[NT][KS], int (&cl)[NT][KS], uint32_t wave,
+                                         uint32_t g, uint32_t r, int topk) {
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+        for (int k = 0; k < topk; ++k) {
+            const Scored b = take_best<KS>(v[nt], cl[nt]);
+            if (g == 0) tops[(wave * 16u * NT + 16u * nt + r) * KS + k] = (u32x2){__float_as_uint(b.first), (uint32_t)b.second};
+        }
+}
+template <int KS>
+__device__ __forceinline__ void merge_tops(const u32x2* tops, uint32_t headers, uint32_t h, int topk, int C,
+                                           uint32_t pkt, uint32_t* cand, uint16_t* cand16) {
+    uint32_t packed = 0;
+    float lv = INFINITY;
+    int lc = -1;
+    for (int k = 0; k < topk; ++k) {
+        float bv = -INFINITY;
+        int bc = kNoClass;
+        for (uint32_t w = 0; w < 8u; ++w)
+            for (int j = 0; j < topk; ++j) {
+                const u32x2 t = tops[(w * headers + h) * KS + j];
+                const float tv = __uint_as_float(t[0]);
+                const int tc = (int)t[1];
+                const bool left = tv < lv || (tv == lv && tc > lc);   // not picked yet
+                if (left && (tv > bv || (tv == bv && tc < bc))) { bv = tv; bc = tc; }
+            }
+        lv = bv;
+        lc = bc;
+        packed |= (uint32_t)bc << (cand_bits(C) * k);
+        if (cand16) cand16[(size_t)pkt * topk + k] = (uint16_t)bc;
+    }
+    if (cand) cand[pkt] = packed;
 }
 
 // OUTB: most blocks of 32 output classes (1, or 16 for up to 512 tuples; the W3 fragments
@@ -591,11 +655,6 @@ __global__ __launch_bounds__(64 * WAVES) void k_mlp(
 // took 1,427): MFMA issue, 1,056 of 16 cycles per 16 headers, about 60% of the time; the
 // barriers between the layers expose the rest, and with fewer headers per workgroup the
 // weights' 42 bytes per cycle from L2. 10,000 headers: 17 against 54 us.
-__device__ __forceinline__ void lds_barrier() {
-    // every wave's LDS accesses done; weight loads in flight stay in flight
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
 // Two values' planes, packed in pairs.
 __device__ __forceinline__ void split_pair(float a, float b, uint32_t (&p)[3]) {
 #pragma unroll
@@ -822,39 +881,198 @@ __global__ __launch_bounds__(512, OCC) void k_mlp_split(
                 }
             }
             lds_barrier();
-            u32x2* const tops = act8;   // [wave][header][4], over the activations
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
-                for (int k = 0; k < topk; ++k) {
-                    const Scored b = take_best<KS>(v[nt], cl[nt]);
-                    if (g == 0) tops[(wave * TH + 16u * nt + r) * 4u + k] = (u32x2){__float_as_uint(b.first), (uint32_t)b.second};
-                }
+            u32x2* const tops = act8;   // over the activations
+            put_tops<NT, KS>(tops, v, cl, wave, g, r, topk);
             lds_barrier();
-            const uint32_t pkt = p0 + tid;
-            if (tid < TH && pkt < n) {
-                uint32_t packed = 0;
-                float lv = INFINITY;
-                int lc = -1;
-                for (int k = 0; k < topk; ++k) {
-                    float bv = -INFINITY;
-                    int bc = kNoClass;
-                    for (uint32_t x = 0; x < 8u * topk; ++x) {
-                        const u32x2 t = tops[((x / topk) * TH + tid) * 4u + x % topk];
-                        const float tv = __uint_as_float(t[0]);
-                        const int tc = (int)t[1];
-                        const bool left = tv < lv || (tv == lv && tc > lc);   // not picked yet
-                        if (left && (tv > bv || (tv == bv && tc < bc))) { bv = tv; bc = tc; }
-                    }
-                    lv = bv;
-                    lc = bc;
-                    packed |= (uint32_t)bc << (cand_bits(C) * k);
-                    if (cand16) cand16[(size_t)pkt * topk + k] = (uint16_t)bc;
-                }
-                if (cand) cand[pkt] = packed;
-            }
+            if (tid < TH && p0 + tid < n) merge_tops<KS>(tops, TH, tid, topk, C, p0 + tid, cand, cand16);
         }
         load_a(r1, 0, wn * MT, 4, 0);
         lds_barrier();   // the next tile's input layer overwrites the activations
+    }
+}
+
+// ---------------------------------------------------------------------------------------
+// BF16 and FP8 for small batches. k_mlp gives a wave whole headers and stages 100 to 150 KB of
+// weights per workgroup first, which a batch of a few tiles waits for. Here the workgroup's 8
+// waves split the neurons: wave w computes H/8 of them in both hidden layers for 16 NT
+// headers, holds its share of those weights in registers (loaded at once, at the start) and
+// exchanges activations through LDS. Fragments, K order and epilogues are k_mlp's, so the
+// scores are the same bit for bit.
+// KS: 0 with at most 32 classes, else the top-k slots kept (wave w takes the 16-class tiles
+// w, w + 8, .. and the waves' lists are merged through LDS).
+// What bounds it: the chain of loads and layers, not the matrix units. Predictor call, k_mlp
+// and this (hidden 256): BF16, 25 classes, 512 headers 17.6 and 6.3 us; 387 classes 39.6 and
+// 8.3; FP8 13.6 and 6.3, 30.8 and 6.9.
+template <int PREC, int H, int NT, int KS>
+__global__ __launch_bounds__(512) void k_mlp_small(
+    const uint4* __restrict__ hdr, uint32_t n, const typename FragT<PREC>::T* __restrict__ w1,
+    const typename FragT<PREC>::T* __restrict__ w2, const typename FragT<PREC>::T* __restrict__ w3,
+    const float* __restrict__ bias, MlpArgs a, uint32_t* __restrict__ cand, float* __restrict__ logits,
+    uint16_t* __restrict__ cand16, const uint32_t* __restrict__ live) {
+    using F = typename FragT<PREC>::T;
+    constexpr int KB = FragT<PREC>::KB, KB1 = kInPad / KB, KBH = H / KB, MT = H / 128;
+    constexpr int KT = KB / 16;   // row tiles per K block of the next layer
+    constexpr uint32_t TH = 16u * NT;
+    __shared__ F act[2][KBH * NT * 64];   // first and second hidden layer, B fragments
+    __shared__ u32x2 tops[KS ? 8 * TH * KS : 1];
+    if (live) n = min(n, *live);
+    const uint32_t tiles = (n + TH - 1) / TH;
+    if (blockIdx.x >= tiles) return;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, g = lane >> 4, r = lane & 15u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int C = a.n_out;
+    const uint32_t size3 = a.n3 * (uint32_t)sizeof(F);
+    const __amdgpu_buffer_rsrc_t r1 = __builtin_amdgcn_make_buffer_rsrc((void*)w1, 0, (H / 16) * KB1 * 64 * sizeof(F), 0x00020000);
+    const __amdgpu_buffer_rsrc_t r2 = __builtin_amdgcn_make_buffer_rsrc((void*)w2, 0, (H / 16) * KBH * 64 * sizeof(F), 0x00020000);
+    const __amdgpu_buffer_rsrc_t r3 = __builtin_amdgcn_make_buffer_rsrc((void*)w3, 0, size3, 0x00020000);
+    auto frag = [&](__amdgpu_buffer_rsrc_t rs, uint32_t k) { return ldf<false>((const F*)nullptr, rs, k, lane, 0u, nullptr); };
+    F A1[MT][KB1], A2[MT][KBH], A3[KS ? 1 : 2][KBH];
+#pragma unroll
+    for (int u = 0; u < MT; ++u)
+#pragma unroll
+        for (int kb = 0; kb < KB1; ++kb) A1[u][kb] = frag(r1, (wave * MT + u) * KB1 + kb);
+    auto load3 = [&](int u, int ct) {   // class tile ct
+#pragma unroll
+        for (int kb = 0; kb < KBH; ++kb) A3[u][kb] = frag(r3, (uint32_t)ct * KBH + kb);
+    };
+    // rows of a hidden layer to the next one's B fragments: a lane's four rows are its own
+    // elements of that fragment
+    auto store = [&](F* dst, int u, int nt, const f4& acc, float rq, float rb) {
+        const uint32_t mt = wave * MT + u;
+        uint32_t* at = reinterpret_cast<uint32_t*>(dst + ((mt / KT) * NT + nt) * 64 + lane);
+        if constexpr (PREC == TANG_BF16) {
+            reinterpret_cast<u32x2*>(at)[mt % KT] =
+                (u32x2){relu_bf16x2(pack_bf16(acc[0], acc[1])), relu_bf16x2(pack_bf16(acc[2], acc[3]))};
+        } else {
+            float v[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[q] = __builtin_amdgcn_fmed3f(acc[q], 0.0f, rb);
+            at[mt % KT] = pack_fp8(v[0], v[1], v[2], v[3], rq);
+        }
+    };
+    f4 b1[MT], b2[MT];
+#pragma unroll
+    for (int u = 0; u < MT; ++u) {
+        b1[u] = *reinterpret_cast<const f4*>(bias + 16 * (wave * MT + u) + 4 * g);
+        b2[u] = *reinterpret_cast<const f4*>(bias + H + 16 * (wave * MT + u) + 4 * g);
+    }
+    bool first = true;
+    for (uint32_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        const uint32_t p0 = tile * TH;
+        uint4 hv[NT];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            const uint32_t p = p0 + nt * 16 + r;
+            hv[nt] = p < n ? hdr[p] : make_uint4(0u, 0u, 0u, 0u);
+        }
+        if (first) {
+#pragma unroll
+            for (int u = 0; u < MT; ++u)
+#pragma unroll
+                for (int kb = 0; kb < KBH; ++kb) A2[u][kb] = frag(r2, (wave * MT + u) * KBH + kb);
+            if constexpr (KS == 0) {
+                load3(0, 0);
+                load3(1, 1);
+            }
+            first = false;
+        }
+        if constexpr (KS != 0) load3(0, (int)wave);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            f4 acc[MT];
+#pragma unroll
+            for (int u = 0; u < MT; ++u) acc[u] = b1[u];
+#pragma unroll
+            for (int kb = 0; kb < KB1; ++kb) {
+                const F x = Bits<PREC>::make(hv[nt], kb, g);
+#pragma unroll
+                for (int u = 0; u < MT; ++u) acc[u] = mma(A1[u][kb], x, acc[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < MT; ++u) store(act[0], u, nt, acc[u], a.rq[0], a.rb[0]);
+        }
+        lds_barrier();
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            f4 acc[MT];
+#pragma unroll
+            for (int u = 0; u < MT; ++u) acc[u] = b2[u];
+#pragma unroll
+            for (int kb = 0; kb < KBH; ++kb) {
+                const F x = act[0][(kb * NT + nt) * 64 + lane];
+#pragma unroll
+                for (int u = 0; u < MT; ++u) acc[u] = mma(A2[u][kb], x, acc[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < MT; ++u) store(act[1], u, nt, acc[u], a.rq[1], a.rb[1]);
+        }
+        lds_barrier();
+        const float* sb3 = bias + 2 * H;
+        if constexpr (KS == 0) {
+            if (wave < (uint32_t)NT) {
+                const uint32_t pkt = p0 + 16u * wave + r;
+                float v[8];
+                int cl[8];
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    f4 z = (f4){0, 0, 0, 0};
+#pragma unroll
+                    for (int kb = 0; kb < KBH; ++kb) z = mma(A3[u][kb], act[1][(kb * NT + wave) * 64 + lane], z);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int c = 16 * u + 4 * (int)g + q;
+                        const float val = (PREC == TANG_FP8 ? z[q] * a.deq[2] : z[q]) + sb3[c];
+                        if (logits && pkt < n && c < C) logits[(size_t)pkt * C + c] = val;
+                        v[4 * u + q] = (c < C && val == val) ? val : -INFINITY;
+                        cl[4 * u + q] = c;
+                    }
+                }
+                uint32_t packed = 0;
+                for (int k = 0; k < a.topk; ++k) {
+                    const int bc = take_best<8>(v, cl).second;
+                    packed |= (uint32_t)bc << (8 * k);
+                    if (cand16 && g == 0 && pkt < n) cand16[(size_t)pkt * a.topk + k] = (uint16_t)bc;
+                }
+                if (cand && g == 0 && pkt < n) cand[pkt] = packed;
+            }
+        } else {
+            float v[NT][KS ? KS : 1];
+            int cl[NT][KS ? KS : 1];
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int q = 0; q < KS; ++q) {
+                    v[nt][q] = -INFINITY;
+                    cl[nt][q] = kNoClass;
+                }
+#pragma unroll 1
+            for (int ct = (int)wave; ct < (C + 15) / 16; ct += 8) {
+                const f4 b3 = *reinterpret_cast<const f4*>(sb3 + 16 * ct + 4 * g);
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                    f4 z = (f4){0, 0, 0, 0};
+#pragma unroll
+                    for (int kb = 0; kb < KBH; ++kb) {
+                        z = mma(A3[0][kb], act[1][(kb * NT + nt) * 64 + lane], z);
+                        if (nt == NT - 1) A3[0][kb] = frag(r3, (uint32_t)(ct + 8) * KBH + kb);   // past the end: zeros
+                    }
+                    const uint32_t pkt = p0 + 16u * nt + r;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int c = 16 * ct + 4 * (int)g + q;
+                        const float val = (PREC == TANG_FP8 ? z[q] * a.deq[2] : z[q]) + b3[q];
+                        if (logits && pkt < n && c < C) logits[(size_t)pkt * C + c] = val;
+                        keep_best<KS ? KS : 1>(v[nt], cl[nt], val, c, C);
+                    }
+                }
+            }
+            put_tops<NT, KS ? KS : 1>(tops, v, cl, wave, g, r, a.topk);
+            lds_barrier();
+            if (tid < TH && p0 + tid < n) merge_tops<KS ? KS : 1>(tops, TH, tid, a.topk, C, p0 + tid, cand, cand16);
+        }
+        // the next tile's first layer writes act[0], read before the last barrier, and its
+        // second act[1] after another one
+        if constexpr (KS != 0) lds_barrier();
     }
 }
 
@@ -1104,6 +1322,17 @@ int model_prepare(tang_ruleset_t* rs, const tang_mlp_desc_t* d, const float* con
 
 namespace {
 
+MlpArgs mlp_args(const ModelDev& m) {
+    MlpArgs a;
+    a.n_out = m.n_out;
+    a.topk = m.topk;
+    a.n3 = m.w3frags;
+    a.nbias = 2 * m.hidden + kOutPad * ((m.n_out + kOutPad - 1) / kOutPad);
+    for (int l = 0; l < 3; ++l) { a.deq[l] = m.deq[l]; a.inv_a[l] = m.inv_a[l]; }
+    for (int l = 0; l < 2; ++l) { a.rq[l] = m.rq[l]; a.rb[l] = 448.0f * m.rq[l]; }
+    return a;
+}
+
 template <int PREC, int H, int NT, int LDSM, int WAVES = 8, int OUTB = 1>
 hipError_t launch_t(const ModelDev& m, const tang_header_t* d_hdr, uint32_t n, uint32_t* cand,
                     float* logits, uint16_t* cand16, hipStream_t s, const uint32_t* live) {
@@ -1132,16 +1361,20 @@ hipError_t launch_t(const ModelDev& m, const tang_header_t* d_hdr, uint32_t n, u
     const uint32_t tiles = (n + 16 * NT - 1) / (16 * NT);
     const uint32_t want = (tiles + WAVES - 1) / WAVES;
     const uint32_t grid = std::max<uint32_t>(1, std::min<uint32_t>(want, (uint32_t)(cus * per_cu)));
-    MlpArgs a;
-    a.n_out = m.n_out;
-    a.topk = m.topk;
-    a.n3 = m.w3frags;
-    a.nbias = 2 * H + kOutPad * ((m.n_out + kOutPad - 1) / kOutPad);
-    for (int l = 0; l < 3; ++l) { a.deq[l] = m.deq[l]; a.inv_a[l] = m.inv_a[l]; }
-    for (int l = 0; l < 2; ++l) { a.rq[l] = m.rq[l]; a.rb[l] = 448.0f * m.rq[l]; }
+    const MlpArgs a = mlp_args(m);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * WAVES), lds, s,
                        reinterpret_cast<const uint4*>(d_hdr), n, (const F*)m.w[0], (const F*)m.w[1],
                        (const F*)m.w[2], (const u32x4*)m.w1x3, m.bias, a, cand, logits, cand16, live);
+    return hipGetLastError();
+}
+
+template <int PREC, int H, int NT, int KS = 0>
+hipError_t launch_small(const ModelDev& m, const tang_header_t* d_hdr, uint32_t n, uint32_t* cand, float* logits,
+                        uint16_t* cand16, hipStream_t s, const uint32_t* live) {
+    using F = typename FragT<PREC>::T;
+    hipLaunchKernelGGL((k_mlp_small<PREC, H, NT, KS>), dim3((n + 16 * NT - 1) / (16 * NT)), dim3(512), 0, s,
+                       reinterpret_cast<const uint4*>(d_hdr), n, (const F*)m.w[0], (const F*)m.w[1],
+                       (const F*)m.w[2], m.bias, mlp_args(m), cand, logits, cand16, live);
     return hipGetLastError();
 }
 
@@ -1188,6 +1421,14 @@ hipError_t launch_mlp(const tang_ruleset_t* rs, const tang_header_t* d_hdr, size
         // workgroup of 512 headers would leave half of the CUs idle on a 65,536-header batch.
         // More than 32 tuples: up to 16 blocks of 32 classes, W3 read from L2.
         const bool wide = m.n_out > kOutPad;
+        // BF16 and FP8, small batches: tiles of 16 headers up to 4,096 (one per CU), of 64 up to
+        // 16,384 (one per CU; BF16 hidden 128 10,000 headers 6.5 us, k_mlp 8.6; FP8 387 classes
+        // 12 and 25), with hidden 256 and at most 32 classes twice that (BF16 32,768 headers
+        // 17.0 and 19.1; 65,536 31.8 and 20.4). Not for BF16 hidden 256 with more classes:
+        // its weights and a class tile leave no registers (10,000 headers 29 and 24).
+        const uint32_t small_to = m.hidden == 256 && !wide                       ? 32768u
+                                  : m.hidden == 256 && m.prec == TANG_BF16 ? 4096u
+                                                                           : 16384u;
         // FP32 on BF16 planes: tiles of 16 NT headers, OCC waves per SIMD (two workgroups per CU
         // at 4). Small batches take small tiles, so that every CU has one: hidden 256, 4,096
         // headers 13 us with 32 per tile, 15 with 48, 22 with 96; 131,072 headers 149, 131 and
@@ -1206,6 +1447,25 @@ hipError_t launch_mlp(const tang_ruleset_t* rs, const tang_header_t* d_hdr, size
             else if (k <= 8192) e = launch_split<256, 2, 4>(m, h, k, c, lg, c8, s, d_live);
             else if (k < (1u << 18)) e = launch_split<256, 3, 4>(m, h, k, c, lg, c8, s, d_live);
             else e = launch_split<256, 6, 2>(m, h, k, c, lg, c8, s, d_live);
+        } else if (m.prec != TANG_FP32 && k <= small_to) {
+            const bool one = m.topk == 1;
+            auto small = [&](auto prec, auto hidden) {
+                constexpr int P = decltype(prec)::value, H = decltype(hidden)::value;
+                if (k <= 4096) {
+                    if (!wide) return launch_small<P, H, 1>(m, h, k, c, lg, c8, s, d_live);
+                    if (one) return launch_small<P, H, 1, 1>(m, h, k, c, lg, c8, s, d_live);
+                    return launch_small<P, H, 1, 4>(m, h, k, c, lg, c8, s, d_live);
+                }
+                if (!wide) return launch_small<P, H, 4>(m, h, k, c, lg, c8, s, d_live);
+                if constexpr (P == TANG_BF16 && H == 256) return hipErrorInvalidValue;   // small_to excludes it
+                else if (one) return launch_small<P, H, 4, 1>(m, h, k, c, lg, c8, s, d_live);
+                else return launch_small<P, H, 4, 4>(m, h, k, c, lg, c8, s, d_live);
+            };
+            using std::integral_constant;
+            if (m.prec == TANG_BF16 && m.hidden == 128) e = small(integral_constant<int, TANG_BF16>{}, integral_constant<int, 128>{});
+            else if (m.prec == TANG_BF16) e = small(integral_constant<int, TANG_BF16>{}, integral_constant<int, 256>{});
+            else if (m.hidden == 128) e = small(integral_constant<int, TANG_FP8>{}, integral_constant<int, 128>{});
+            else e = small(integral_constant<int, TANG_FP8>{}, integral_constant<int, 256>{});
         } else if (wide) {
             if (m.prec == TANG_FP32 && m.hidden == 128) e = launch_t<TANG_FP32, 128, 2, 2, 8,16>(m, h, k, c, lg, c8, s, d_live);
             else if (m.prec == TANG_FP32) e = launch_t<TANG_FP32, 256, 1, 0, 8,16>(m, h, k, c, lg, c8, s, d_live);

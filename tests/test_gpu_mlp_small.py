@@ -1,0 +1,47 @@
+"""The small-batch form of the BF16 and FP8 predictors equals the large-batch one."""
+import numpy as np
+import pytest
+
+from oracle import oracle as orc
+from paper_2601_03187_amd import synth, train
+from paper_2601_03187_amd import tang as T
+from tests._gpu import mlp_dev, torch_cuda
+
+pytestmark = pytest.mark.gpu
+
+LARGE = 32769   # past every size that takes the small form
+
+
+@pytest.mark.parametrize("topk", [1, 2])
+@pytest.mark.parametrize("space", ["narrow", "wide", "all"])
+@pytest.mark.parametrize("hidden", [128, 256])
+@pytest.mark.parametrize("prec", ["bf16", "fp8"])
+def test_small_form_equals_large_form_bit_for_bit(prec, hidden, space, topk):
+    """Scores and candidates of a header at the edges of the small form's tiles and size
+    rules are those of a large batch, bit for bit (k_mlp's are checked against the oracle in
+    test_gpu_mlp); tied scores and NaN scores too."""
+    torch_cuda()
+    rules = synth.make_rules(3000, seed=111, wide=space == "wide", all_lengths=space == "all")
+    rs = T.tang_ruleset_create(0, rules)
+    try:
+        C = T.tang_ruleset_num_tuples(rs)
+        Ws, bs = train.random_weights(C, hidden, seed=5)
+        Ws[2][7] = Ws[2][3]         # two classes with equal scores
+        bs[2][7] = bs[2][3]
+        bs[2][11] = np.nan
+        hdr = synth.make_packets(rules, 83, seed=112, frac_in=0.7)
+        sc = train.act_scales(Ws, bs, train.feature_bits_torch(hdr)) if prec == "fp8" else None
+        T.tang_model_load(rs, Ws, bs, prec, topk=topk, act_scales=sc)
+        big, bc = mlp_dev(rs, hdr[np.arange(LARGE) % len(hdr)], C, topk=topk)
+        logits, cand = big[:83], bc[:83]
+        finite = np.arange(C) != 11
+        want = orc.mlp_forward(orc.feature_bits(hdr), Ws, bs, prec, act_scales=sc)[:, finite]
+        got = logits[:, finite]
+        assert np.median(np.abs(got - want).max(axis=1) / np.abs(want).max(axis=1)) < 2.0 ** -8
+        for n in (1, 15, 17, 83, 4096, 4097, 16384, 16385, 32768):
+            at = np.arange(n) % len(hdr)
+            small, sc_ = mlp_dev(rs, hdr[at], C, topk=topk)
+            assert np.array_equal(small, logits[at], equal_nan=True), n
+            assert np.array_equal(sc_, cand[at]), n
+    finally:
+        T.tang_ruleset_destroy(rs)
