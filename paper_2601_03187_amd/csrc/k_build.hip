@@ -217,6 +217,12 @@ __global__ void k_fill_slots(SlotDev* __restrict__ slots, const uint32_t* __rest
     atomicOr(blk + 1, 0x80000000u >> filter_pos_y(h));
 }
 
+__global__ void k_fill_split(SlotDev* __restrict__ slots, const uint32_t* __restrict__ idx,
+                             const SplitInfo* __restrict__ info, uint32_t n) {
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) *reinterpret_cast<SplitInfo*>(&slots[idx[i]].first) = info[i];
+}
+
 }  // namespace
 
 hipError_t launch_conflict_build(const BoxDev* d_boxes, size_t n, Rec* d_recs, uint32_t* d_cmask,
@@ -280,6 +286,13 @@ hipError_t launch_fill_slots(SlotDev* d_slots, const uint32_t* d_idx, const Slot
     if (!n) return hipSuccess;
     hipLaunchKernelGGL(k_fill_slots, dim3((n + 255) / 256), dim3(256), 0, s, d_slots, d_idx, d_val, n,
                        d_recs, d_back, d_filter, d_tt);
+    return hipGetLastError();
+}
+
+hipError_t launch_fill_split(SlotDev* d_slots, const uint32_t* d_idx, const SplitInfo* d_info, uint32_t n,
+                             hipStream_t s) {
+    if (!n) return hipSuccess;
+    hipLaunchKernelGGL(k_fill_split, dim3((n + 255) / 256), dim3(256), 0, s, d_slots, d_idx, d_info, n);
     return hipGetLastError();
 }
 

@@ -25,11 +25,13 @@ namespace tang {
 namespace {
 
 constexpr uint32_t kNoTuple = 0xFFFFFFFFu;
-// Sets of 64 headers per wave, rulesets of at most 32 tuples: four from this many headers on,
+// Sets of 64 headers per wave, rulesets of at most 32 tuples: two from this many headers on,
 // one below. More sets keep a wave's lanes busy longer, fewer make more waves (100,000
-// rules, one set against four: 131,072 headers 83 against 106 us, 524,288 117 against 126,
-// 1,048,576 185 against 148; 4.2M at 512k rules 389 against 290; with U = 1).
-constexpr uint32_t kQueueFrom = 3u << 18;
+// rules, one set and two: 262,144 headers 76 and 97 us, 600,000 116 and 115, 1,048,576 162
+// and 150; 512k rules with 25% wildcard-heavy rules 51 and 53, 92 and 78, 138 and 116). Four
+// sets need 36 KB of LDS and leave four waves per SIMD: 1,800 rules, 4.2M headers 316 us
+// against 265 with two.
+constexpr uint32_t kQueueFrom = 1u << 19;
 
 __device__ __forceinline__ bool kless(uint32_t p1, uint32_t i1, uint32_t p2, uint32_t i2) {
     return p1 < p2 || (p1 == p2 && i1 < i2);
@@ -65,13 +67,13 @@ struct alignas(16) Entry {
 // per wave. U: records of a list per step: a small batch lasts as long as its longest list
 // scan, so more records in flight pay there, until the registers cost waves.
 //
-// What bounds it (25 tuples, 512k rules, no predictor, 4.2M Zipf headers): random 128-byte
-// lines. The card serves 265 G random accesses/s that hit an L2 and 60 G that miss it, and
-// a header needs about 7.4 and 1.3 of them, together 210 of the kernel's 290 us; vector
-// issue takes about 205 us beside them. One header per lane with a slot table, its records
-// and the filter each on lines of their own (8.6 and 2.0 accesses) took 396 us, 93% of it
-// vector issue: the wave ran its probe loop as long as its busiest lane needed, 25 steps
-// where a header needs 3.3 on average.
+// What bounds it (25 tuples, 512k rules, no predictor, 4.2M Zipf headers: 258 us): vector
+// issue, about 225 us of it, and random 128-byte lines beside it: the card serves 265 G
+// random accesses/s that hit an L2 and 60 G that miss it, and a header needs about 7.5 and
+// 1.1 of them, together 195 us. One header per lane with a slot table, its records and the
+// filter each on lines of their own (8.6 and 2.0 accesses) took 396 us, 93% of it vector
+// issue: the wave ran its probe loop as long as its busiest lane needed, 25 steps where a
+// header needs 3.1 on average.
 template <bool STATS, int NW, int R, int U>
 __global__ __launch_bounds__(256) void k_classify(const uint4* __restrict__ hdr,
                                                   uint32_t* __restrict__ out, uint32_t n,
@@ -280,12 +282,12 @@ __global__ __launch_bounds__(256) void k_classify(const uint4* __restrict__ hdr,
         // takes the next header of the queue, so the wave's lanes stay busy until the queue
         // is empty.
         enum : uint32_t { P_IDLE = 0, P_NEXT, P_START, P_SLOT, P_REC };
-        constexpr uint32_t kMain = 8;   // `sub` while walking to a tuple's main bucket
         uint32_t taken = 0;
         uint32_t ps = P_IDLE, e = 0, sip = 0, dip = 0, ports = 0, proto = 0;
         uint32_t bp = kDead, bid = kDead, bcm = 0;   // the lane's header's best
         uint32_t cur = 0, word = 0, nz = 0;   // tuples left (of mask word `word`), words left
-        uint32_t ct = 0, tk = 0, k0 = 0, k1 = 0, sub = kMain, bi = 0, left = 0;
+        uint32_t ct = 0, tk = 0, k0 = 0, k1 = 0, bi = 0, left = 0;
+        uint32_t sub = 0;   // sub-lists of a split bucket still to visit (bit 0 DP, SP, protocol, rest)
         uint32_t at = 0, walk = 0;   // slot or record index; steps of the slot walk
         for (;;) {
             const unsigned long long idle = __ballot(ps == P_IDLE);
@@ -337,7 +339,7 @@ __global__ __launch_bounds__(256) void k_classify(const uint4* __restrict__ hdr,
                         tk = t;
                         k0 = sip & td.smask;
                         k1 = dip & td.dmask;
-                        sub = kMain;
+                        sub = 0;
                         ps = P_START;
                         if (STATS) ++n_probe;
                         break;
@@ -356,81 +358,83 @@ __global__ __launch_bounds__(256) void k_classify(const uint4* __restrict__ hdr,
                 ps = P_SLOT;
             }
             // one step's loads: the slot (its key and its bucket's first record share a
-            // 64-byte line) or the next U records of the list
-            uint4 a = make_uint4(0u, 0u, 0u, 0u), b = a, c = a;
+            // 64-byte line) or the next U records of the list. Every lane loads, an idle one
+            // slot 0 with the others, and the step is decided in selects: with a branch per
+            // state the copies where the branches meet were a third of the loop's vector
+            // instructions.
+            const bool slot = ps == P_SLOT, rec = ps == P_REC;
+            const uint4* const ps_slot = reinterpret_cast<const uint4*>(slots + (slot ? at : 0u));
+            const uint4* const p = rec ? reinterpret_cast<const uint4*>(recs + at) : ps_slot + 1;
+            const uint4 a = *ps_slot;
+            const uint4 b = p[0];   // sp, dp, prio, meta
+            const uint4 c = p[1];   // sip, dip, id, cmask
             uint4 xb[U], xc[U];
-            const bool rec = ps == P_REC;
-            if (ps != P_IDLE) {
-                const uint4* p = rec ? reinterpret_cast<const uint4*>(recs + at)
-                                     : reinterpret_cast<const uint4*>(slots + at) + 1;
-                if (!rec) a = p[-1];
-                b = p[0];   // sp, dp, prio, meta
-                c = p[1];   // sip, dip, id, cmask
-                if (rec) {
+            if constexpr (U > 1) {
 #pragma unroll
-                    for (uint32_t j = 1; j < (uint32_t)U; ++j) {
-                        const uint32_t k = min(j, left - 1u);   // the list's last record past its end
-                        xb[j] = p[2u * k];
-                        xc[j] = p[2u * k + 1u];
-                    }
+                for (uint32_t j = 1; j < (uint32_t)U; ++j) {
+                    // the list's last record past its end; an idle or slot lane its own again
+                    const uint32_t k = rec ? min(j, left - 1u) : 0u;
+                    xb[j] = p[2u * k];
+                    xc[j] = p[2u * k + 1u];
                 }
             }
-            // Records are in (priority, id) order: the first match is the list's best, and the
-            // list ends at the first record that cannot beat the answer.
             const uint32_t sp = ports & 0xFFFFu, dp = ports >> 16;
-            auto test = [&](const uint4& b, const uint4& c) {
-                if (STATS) ++n_recs;
+            // Records are in (priority, id) order: the first match is the list's best, and the
+            // list ends at the first record that cannot beat the answer. True: it ended.
+            auto test = [&](bool on, const uint4& b, const uint4& c) {
+                if (STATS) n_recs += on;
                 bool ok = ((uint32_t)(sp >= (b.x & 0xFFFFu)) & (uint32_t)(sp <= (b.x >> 16)) &
                            (uint32_t)(dp >= (b.y & 0xFFFFu)) & (uint32_t)(dp <= (b.y >> 16)) &
                            ((uint32_t)(meta_exact(b.w) == 0) | (uint32_t)(proto == meta_proto(b.w)))) != 0u;
                 const bool better = kless(b.z, c.z, bp, bid);
-                if (ok && better && meta_check(b.w))   // held by a coarser tuple: its own prefixes
+                bool hit = on & ok & better;
+                if (hit && meta_check(b.w)) {   // held by a coarser tuple: its own prefixes
                     ok = (((sip ^ c.x) & pmask(meta_sl(b.w))) | ((dip ^ c.y) & pmask(meta_dl(b.w)))) == 0u;
-                if (ok && better) {
-                    bp = b.z;
-                    bid = c.z;
-                    bcm = NW == 1 ? c.w : at;
-                    if (STATS) s_tup[wave][e] = ct;
+                    hit = ok;
                 }
-                ++at;
-                --left;
-                return ok || !better || left == 0;
+                bp = hit ? b.z : bp;
+                bid = hit ? c.z : bid;
+                bcm = hit ? (NW == 1 ? c.w : at) : bcm;
+                if (STATS && hit) s_tup[wave][e] = ct;
+                at += on ? 1u : 0u;
+                left -= on ? 1u : 0u;
+                return on & (ok | !better | (left == 0u));
             };
-            bool first = rec, done = false;
-            if (ps == P_SLOT) {
-                if (STATS) ++n_slots;
-                if (a.z == kEmptyTL) {
-                    done = true;
-                } else if (a.x == k0 && a.y == k1 && (a.z >> kTlShift) == tk) {
-                    left = a.z & kMaxBucketLen;
-                    if (a.w & kSplit) {   // a split bucket: the sub-lists the header selects
-                        bi = a.w & ~kSplit;
-                        sub = 0;
-                        done = true;
-                    } else {
-                        at = a.w;
-                        ps = P_REC;
-                        first = left != 0;
-                        done = !first;
-                    }
-                } else {
-                    at = (at + 1u) & slot_mask;
-                    done = ++walk > slot_mask;   // only a corrupted table has no empty slot
-                }
+            if (STATS) n_slots += slot;
+            const bool empty = slot & (a.z == kEmptyTL);
+            // (an empty slot's key is above every tuple's)
+            const bool match = slot & (a.x == k0) & (a.y == k1) & ((a.z >> kTlShift) == tk);
+            const bool split = match & ((a.w & kSplit) != 0u);
+            const bool miss = slot & !empty & !match;
+            left = match ? a.z & kMaxBucketLen : left;
+            at = match ? a.w : miss ? (at + 1u) & slot_mask : at;
+            walk += miss ? 1u : 0u;
+            if (split) {
+                // a split bucket: the sub-lists the header selects, where the summary in the
+                // record's place (SplitInfo) has them
+                bi = a.w & ~kSplit;
+                const uint32_t d = split_dp_bit(dp), p = split_sp_bit(sp);
+                const uint32_t dw = d & 64u ? (d & 32u ? b.w : b.z) : (d & 32u ? b.y : b.x);
+                const uint32_t pw = p >= 64u ? c.z : p >= 32u ? c.y : c.x;
+                sub = ((dw >> (d & 31u)) & 1u) | ((pw >> (p & 31u)) & 1u) << 1 |
+                      ((c.w >> split_proto_bit(proto)) & 1u) << 2 | (c.w >> 31) << 3;
             }
-            if (first) done = test(b, c);
+            const bool first = match & !split & (left != 0u);
+            // (only a corrupted table has no empty slot to end the walk)
+            bool done = empty | (match & !first) | (walk > slot_mask);
+            done |= test(rec | first, b, c);
             if constexpr (U > 1) {
 #pragma unroll
-                for (uint32_t j = 1; j < (uint32_t)U; ++j)
-                    if (rec && !done) done = test(xb[j], xc[j]);
+                for (uint32_t j = 1; j < (uint32_t)U; ++j) done |= test(rec & !done, xb[j], xc[j]);
             }
+            ps = first ? P_REC : ps;
             if (done) {
-                if (sub < 4u) {
+                if (sub) {
                     // the next sub-list of a split bucket
-                    const uint32_t kind = sub == 0 ? kSubDp : sub == 1 ? kSubSp : sub == 2 ? kSubProto : kSubRest;
-                    k1 = sub == 0 ? ports >> 16 : sub == 1 ? ports & 0xFFFFu : sub == 2 ? proto : 0u;
-                    ++sub;
-                    tk = ct | (kind << kKindShift);
+                    const uint32_t q = (uint32_t)__builtin_ctz(sub);
+                    sub &= sub - 1u;
+                    k1 = q == 0 ? dp : q == 1 ? sp : q == 2 ? proto : 0u;
+                    tk = ct | ((q + kSubDp) << kKindShift);
                     k0 = bi;
                     ps = P_START;
                 } else if (cur | nz) {
@@ -490,16 +494,17 @@ hipError_t launch_classify(const tang_ruleset_t* rs, const tang_header_t* d_hdr,
                                reinterpret_cast<const uint2*>(rs->d_filter), rs->d_tt, kcand, rs->d_stats,
                                d_live);
         };
-        // Records per step (100,000 rules; U = 1, 2, 4, 8): 65,536 headers 75, 66, 56, 57 us; 5M
-        // with four sets 933 (U = 1) against 900 (2); 144 tuples, 1M 230, 223, 251, 339; 387
-        // tuples, 1M 829, 838, 854, 944.
+        // Records per step, small batches (U = 1, 2, 4; 65,536 headers): 100,000 rules 52, 45,
+        // 43 us, 1,800 rules 28, 30, 33; two sets, 4.2M headers (U = 1, 2): 100,000 rules 368
+        // and 344, 512k 259 and 265, 1,800 225 and 241. 144 tuples, 1M (U = 1, 2, 4) 230, 223,
+        // 251; 387 tuples, 1M 829, 838, 854.
         // Wider rulesets take one set: two need 44 and 71 KB of LDS per workgroup, and the
         // waves lost cost more than the fuller lanes give (144 tuples, 2.1M headers: 387
         // against 476 us; 387 tuples, 1M: 884 against 977).
         if (rs->nw == 1) {
-            if (stats) go(k_classify<true, 1, 4, 2>, 4);
-            else if (m >= kQueueFrom) go(k_classify<false, 1, 4, 2>, 4);
-            else go(k_classify<false, 1, 1, 4>, 1);
+            if (stats) go(k_classify<true, 1, 2, 1>, 2);
+            else if (m >= kQueueFrom) go(k_classify<false, 1, 2, 1>, 2);
+            else go(k_classify<false, 1, 1, 2>, 1);
         } else if (rs->nw == kMaskWords) {
             if (stats) go(k_classify<true, kMaskWords, 1, 2>, 1);
             else go(k_classify<false, kMaskWords, 1, 2>, 1);

@@ -92,6 +92,17 @@ struct alignas(64) SlotDev {
     Rec first;
     uint32_t pad[4];
 };
+// In place of a first record, the slot of a split bucket says which of its sub-lists may
+// exist: a bit per exact DP value (128 of them, in the record's first half), per exact SP
+// value (96) and per protocol (31), and whether there is a rest list. A header then walks
+// only to the lists it may find.
+struct alignas(16) SplitInfo {
+    uint32_t dp[4], sp[3], proto;   // proto: bit 31 the rest list
+};
+static_assert(sizeof(SplitInfo) == sizeof(Rec), "the summary takes the record's place");
+__host__ __device__ inline uint32_t split_dp_bit(uint32_t dp) { return (dp * 0x9E3779B1u) >> 25; }
+__host__ __device__ inline uint32_t split_sp_bit(uint32_t sp) { return ((sp * 0x9E3779B1u) >> 24) * 96u >> 8; }
+__host__ __device__ inline uint32_t split_proto_bit(uint32_t proto) { return proto % 31u; }
 
 __host__ __device__ inline uint32_t meta_pack(uint32_t sl, uint32_t dl, uint32_t proto,
                                               uint32_t exact, uint32_t tuple, uint32_t check) {
@@ -164,7 +175,9 @@ inline size_t tuple_table_bytes(const TupleTable& tt) {
 // the slot stores the full key, so answers never depend on the hash.
 // The bucket filter uses its own hashes (filter_block / filter_hash below).
 __host__ __device__ inline uint32_t key_hash(uint32_t t, uint32_t ms, uint32_t md) {
-    uint32_t x = (ms ^ (t + 1u) * 0x9E3779B9u) * 0x85EBCA6Bu;
+    // a 24-bit product (full rate on the vector units); tuple keys are below 2^12
+    const uint32_t salt = ((t + 1u) & 0xFFFFFFu) * 0x9E3779u;
+    uint32_t x = (ms ^ salt) * 0x85EBCA6Bu;
     x ^= x >> 15;
     x = (x ^ md) * 0xC2B2AE35u;
     x ^= x >> 15;
@@ -273,6 +286,7 @@ struct tang_ruleset_s {
         uint32_t off, cap;
         std::vector<uint32_t> members;  // rule handles in (priority, id) order
         bool split = false;             // main bucket whose rules live in sub-lists
+        uint32_t info = 0;              // split: index of its summary
     };
     struct BKey {
         uint32_t t, ms, md;
@@ -294,6 +308,7 @@ struct tang_ruleset_s {
     std::vector<Bucket> buckets;
     std::unordered_map<BKey, uint32_t, BKeyHash> bucket_of;
     std::vector<tang::Slot> slots;                 // host mirror of the slot table
+    std::vector<tang::SplitInfo> split_info;       // summaries of the split buckets' sub-lists
     uint32_t filter_blocks = 0;                    // size of the bucket filter (device only)
     uint32_t rec_used = 0, rec_cap = 0;
     uint32_t nw = 1;   // conflict-mask words per rule (fixed at build: words_for(tuples))
@@ -374,6 +389,9 @@ hipError_t launch_move_masks(uint32_t* d_cmask, uint32_t nw, const uint32_t* d_s
 hipError_t launch_fill_slots(SlotDev* d_slots, const uint32_t* d_idx, const Slot* d_val, uint32_t n,
                              const Rec* d_recs, uint32_t* d_back, uint32_t* d_filter,
                              const TupleTable* d_tt, hipStream_t s);
+// Writes the summaries of split buckets into their slots.
+hipError_t launch_fill_split(SlotDev* d_slots, const uint32_t* d_idx, const SplitInfo* d_info, uint32_t n,
+                             hipStream_t s);
 // Largest batch of tang_classify_host_noalloc (its static staging: 5 MiB per GPU).
 constexpr size_t kNoAllocMaxHeaders = (size_t)1 << 18;
 // tang_classify's body; every launch is on stream s (callers may be capturing it).

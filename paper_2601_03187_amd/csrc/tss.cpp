@@ -46,12 +46,22 @@ tang_ruleset_t::BKey sub_key(const tang_ruleset_t* rs, uint32_t b, uint32_t h) {
     return sub_key_of(rs->buckets[b].t, b, rs->rules[h].r);
 }
 
+// A new sub-list (key (tuple | kind, bucket index, value)) enters its bucket's summary.
 uint32_t find_or_add_bucket(tang_ruleset_t* rs, const tang_ruleset_t::BKey& k) {
     auto it = rs->bucket_of.find(k);
     if (it != rs->bucket_of.end()) return it->second;
     const uint32_t b = (uint32_t)rs->buckets.size();
     rs->buckets.push_back({k.t, k.ms, k.md, 0, 0, 0, {}, false});
     rs->bucket_of.emplace(k, b);
+    const uint32_t kind = k.t >> kKindShift;
+    if (kind) {
+        SplitInfo& f = rs->split_info[rs->buckets[k.ms].info];
+        const uint32_t d = split_dp_bit(k.md), p = split_sp_bit(k.md);
+        if (kind == kSubDp) f.dp[d >> 5] |= 1u << (d & 31u);
+        else if (kind == kSubSp) f.sp[p >> 5] |= 1u << (p & 31u);
+        else if (kind == kSubProto) f.proto |= 1u << split_proto_bit(k.md);
+        else f.proto |= 1u << 31;
+    }
     return b;
 }
 
@@ -62,6 +72,8 @@ std::vector<uint32_t> split_bucket(tang_ruleset_t* rs, uint32_t b) {
     std::vector<uint32_t> mem;
     mem.swap(rs->buckets[b].members);
     rs->buckets[b].split = true;
+    rs->buckets[b].info = (uint32_t)rs->split_info.size();
+    rs->split_info.push_back(SplitInfo{});
     for (uint32_t h : mem) {
         const uint32_t sb = find_or_add_bucket(rs, sub_key(rs, b, h));
         auto& sm = rs->buckets[sb].members;
@@ -285,6 +297,25 @@ static hipError_t upload_slots(const tang_ruleset_t* rs, SlotDev* d_slots, uint3
     if (e == hipSuccess)
         e = launch_fill_slots(d_slots, nullptr, *d_val, (uint32_t)rs->slots.size(), rs->d_recs, rs->d_back,
                               d_filter, rs->d_tt, s);
+    std::vector<uint32_t> idx;
+    std::vector<SplitInfo> info;
+    for (const auto& bk : rs->buckets)
+        if (bk.split) {
+            idx.push_back(bk.slot);
+            info.push_back(rs->split_info[bk.info]);
+        }
+    uint32_t* d_idx = nullptr;
+    SplitInfo* d_info = nullptr;
+    if (e == hipSuccess && !idx.empty()) {
+        e = dev_alloc(&d_idx, idx.size() * sizeof idx[0]);
+        if (e == hipSuccess) e = dev_alloc(&d_info, info.size() * sizeof info[0]);
+        if (e == hipSuccess) e = hipMemcpyAsync(d_idx, idx.data(), idx.size() * sizeof idx[0], hipMemcpyHostToDevice, s);
+        if (e == hipSuccess) e = hipMemcpyAsync(d_info, info.data(), info.size() * sizeof info[0], hipMemcpyHostToDevice, s);
+        if (e == hipSuccess) e = launch_fill_split(d_slots, d_idx, d_info, (uint32_t)idx.size(), s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        if (d_idx) (void)dev_release(d_idx);
+        if (d_info) (void)dev_release(d_info);
+    }
     return e;
 }
 
@@ -374,7 +405,8 @@ int flush(tang_ruleset_t* rs, const std::vector<uint32_t>& dirty, const std::vec
     std::vector<uint32_t> src, dst;   // src: old position, or kNew | index into newrecs
     std::vector<Rec> newrecs;
     const uint32_t kNew = 0x80000000u;
-    std::vector<uint32_t> touched_slots;
+    std::vector<uint32_t> touched_slots, split_slots;
+    std::vector<SplitInfo> split_info;
     uint32_t need_end = rs->rec_used;
     // first pass: capacity planning
     for (uint32_t b : dirty) {
@@ -452,6 +484,12 @@ int flush(tang_ruleset_t* rs, const std::vector<uint32_t>& dirty, const std::vec
         }
         rs->slots[bk.slot] = slot_value(rs, b);
         touched_slots.push_back(bk.slot);
+        // the summary of a split bucket whose sub-lists changed
+        const auto& main = is_main(bk) ? bk : rs->buckets[bk.ms];
+        if (main.split) {
+            split_slots.push_back(main.slot);
+            split_info.push_back(rs->split_info[main.info]);
+        }
     }
 
     std::vector<void*> tmp;
@@ -535,6 +573,12 @@ int flush(tang_ruleset_t* rs, const std::vector<uint32_t>& dirty, const std::vec
             if (e == hipSuccess)
                 e = launch_fill_slots(rs->d_slots, (const uint32_t*)d_idx, (const Slot*)d_val,
                                       (uint32_t)vals.size(), rs->d_recs, rs->d_back, rs->d_filter, rs->d_tt, s);
+            void *d_sidx = nullptr, *d_info = nullptr;
+            if (e == hipSuccess) e = dev_copy(split_slots.data(), split_slots.size() * 4, &d_sidx);
+            if (e == hipSuccess) e = dev_copy(split_info.data(), split_info.size() * sizeof(SplitInfo), &d_info);
+            if (e == hipSuccess)
+                e = launch_fill_split(rs->d_slots, (const uint32_t*)d_sidx, (const SplitInfo*)d_info,
+                                      (uint32_t)split_slots.size(), s);
         }
     }
     hipError_t e2 = hipStreamSynchronize(s);

@@ -1,6 +1,6 @@
 """The search's forms and the slots' copies of their first records.
 
-Batch sizes on both sides of the queue rule (one set of 64 headers per wave, or four), at
+Batch sizes on both sides of the queue rule (one set of 64 headers per wave, or two), at
 wave and workgroup edges, and one header; and conflict masks that an insertion changes,
 which a slot's copy of its first record has to follow."""
 import numpy as np
@@ -13,7 +13,7 @@ from tests._gpu import classify_dev, torch_cuda
 
 pytestmark = pytest.mark.gpu
 
-QUEUE_FROM = 3 << 18
+QUEUE_FROM = 1 << 19
 
 
 @pytest.mark.parametrize("space", ["narrow", "wide", "all"])
@@ -83,5 +83,47 @@ def test_inserted_conflicts_reach_the_first_records(wide):
             T.tang_delete(rs, ids)
             live &= ~np.isin(every["id"], ids)
             assert np.array_equal(classify_dev(rs, hdr), orc.classify(every, hdr, live=live)), k
+    finally:
+        T.tang_ruleset_destroy(rs)
+
+
+def test_split_bucket_summaries_follow_inserts():
+    """One bucket of many rules (all prefixes of length 8 over one value) split into
+    sub-lists by exact DP, exact SP, protocol and the rest; values that share a summary bit
+    with others, values that first appear by insertion, and the first rule of the rest list
+    inserted last: every answer equals the oracle's."""
+    torch_cuda()
+    n = 400
+    rng = np.random.default_rng(12)
+    rules = synth.make_rules(n, seed=97, ordering="literal")
+    for f in ("sip", "dip"):
+        rules[f] = 0x0A000000
+        rules[f + "_len"] = 8
+    kind = np.arange(n) % 3
+    port = rng.integers(0, 65536, n).astype(np.uint16)
+    for f in ("sp", "dp"):
+        rules[f + "_lo"], rules[f + "_hi"] = 0, 65535
+    rules["dp_lo"][kind == 0] = rules["dp_hi"][kind == 0] = port[kind == 0]
+    rules["sp_lo"][kind == 1] = rules["sp_hi"][kind == 1] = port[kind == 1]
+    rules["proto"] = np.where(kind == 2, rng.integers(0, 200, n), 0)
+    rules["proto_mask"] = np.where(kind == 2, 255, 0)
+    rules["priority"] = rng.permutation(n)
+    rules["id"] = np.arange(n)
+    rest = rules[:1].copy()
+    rest["dp_lo"], rest["dp_hi"], rest["priority"], rest["id"] = 0, 65535, 10_000, 9_000
+    hdr = np.concatenate([synth.sample_inside(rules[rng.integers(0, n, 4000)], rng),
+                          synth.sample_inside(rest[np.zeros(500, int)], rng)])
+    first = rules[:100]
+    rs = T.tang_ruleset_create(0, first)
+    try:
+        have = first
+        assert np.array_equal(classify_dev(rs, hdr), orc.classify(have, hdr))
+        for more in (rules[100:103], rules[103:300], rules[300:], rest):
+            T.tang_insert(rs, more)
+            have = np.concatenate([have, more])
+            assert np.array_equal(classify_dev(rs, hdr), orc.classify(have, hdr)), len(have)
+        T.tang_delete(rs, rules["id"][::2])
+        live = ~np.isin(have["id"], rules["id"][::2])
+        assert np.array_equal(classify_dev(rs, hdr), orc.classify(have, hdr, live=live))
     finally:
         T.tang_ruleset_destroy(rs)
