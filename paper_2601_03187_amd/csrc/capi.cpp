@@ -109,7 +109,7 @@ size_t tang_ruleset_s::device_bytes() const {
     return slots.size() * sizeof(SlotDev) + (nw == 1 ? (size_t)rec_cap * 4 : 0) + (size_t)filter_blocks * 8 +
            (size_t)rec_cap * sizeof(Rec) + (nw > 1 ? (size_t)rec_cap * nw * 4 : 0) +
            sizeof(TupleTable) +
-           kStatCopies * sizeof(StatsDev) + model.bytes;
+           kStatCopies * sizeof(StatsDev) + upd_dev_cap + model.bytes;
 }
 
 #define TANG_GUARD_BEGIN try {
@@ -130,6 +130,10 @@ static void free_device(tang_ruleset_t* rs) {
     (void)hipSetDevice(rs->device);
     model_free(rs->model);
     if (rs->d_slots) (void)dev_release(rs->d_slots);
+    if (rs->upd_host) (void)hipHostFree(rs->upd_host);
+    if (rs->upd_dev) (void)dev_release(rs->upd_dev);
+    rs->upd_host = rs->upd_dev = nullptr;
+    rs->upd_host_cap = rs->upd_dev_cap = 0;
     if (rs->d_back) (void)dev_release(rs->d_back);
     rs->d_back = nullptr;
     if (rs->d_filter) (void)dev_release(rs->d_filter);

@@ -230,6 +230,12 @@ struct alignas(16) BoxDev {
     uint32_t slo, shi, dlo, dhi, sp, dp, pt, pos;  // pt = proto | exact << 8 | tuple << 16
 };
 
+// A fresh rule as an update compares it with every record: prefixes with their masks,
+// protocol with its mask (0: any), the low and the high bounds of both ports (SP | DP << 16).
+struct alignas(16) FreshDev {
+    uint32_t sip, sm, dip, dm, proto, pm, lo, hi, prio, id, tuple, pos;
+};
+
 // ---------------------------------------------------------------------------------------
 // Model on the device.
 
@@ -322,6 +328,12 @@ struct tang_ruleset_s {
     tang::TupleTable* d_tt = nullptr;
     tang::StatsDev* d_stats = nullptr;
     hipStream_t upd_stream = nullptr;
+    // Updates' staging, kept up to 16 MB each and released with the ruleset: pinned host memory
+    // that a batch is packed into, and the device block it is copied to (with scratch behind
+    // it). One update runs at a time and ends synchronised, so both are free again.
+    void* upd_host = nullptr;
+    void* upd_dev = nullptr;
+    size_t upd_host_cap = 0, upd_dev_cap = 0;
     tang::ModelDev model;
     std::mutex stats_mu;
     uint64_t version = 0;   // bumped by every change that captured launches depend on
@@ -374,7 +386,7 @@ hipError_t launch_conflict_build(const BoxDev* d_boxes, size_t n, Rec* d_recs, u
                                  hipStream_t s);
 // back, slots (nw = 1): the mask copies in the slots of records that are their list's first.
 hipError_t launch_conflict_update(Rec* d_recs, uint32_t* d_cmask, uint32_t nw, uint32_t rec_used,
-                                  const uint32_t* d_new_pos, uint32_t n_new, const uint32_t* d_back,
+                                  const FreshDev* d_fresh, uint32_t n_new, const uint32_t* d_back,
                                   SlotDev* d_slots, hipStream_t s);
 // Clears `back` (nw = 1) at every destination.
 hipError_t launch_move_records(Rec* d_recs, const Rec* d_src_recs, const uint32_t* d_src,

@@ -2,6 +2,7 @@
 // deletion (Sec. 5.2.1), and the device deltas they produce.
 #include <algorithm>
 #include <numeric>
+#include <unordered_set>
 
 #include "tang_internal.hpp"
 
@@ -150,6 +151,13 @@ Rec make_rec(const tang_ruleset_t* rs, uint32_t h) {
     x.prio = r.priority;
     x.id = r.id;
     return x;
+}
+
+static BoxDev box_of(const tang_ruleset_s::HRule& hr) {
+    const tang_rule_t& r = hr.r;
+    return BoxDev{r.sip, r.sip | ~pmask(r.sip_len), r.dip, r.dip | ~pmask(r.dip_len),
+                  (uint32_t)r.sp_lo | ((uint32_t)r.sp_hi << 16), (uint32_t)r.dp_lo | ((uint32_t)r.dp_hi << 16),
+                  (uint32_t)r.proto | ((r.proto_mask ? 1u : 0u) << 8) | (hr.tuple << 16), hr.pos};
 }
 
 static Rec dead_rec() {
@@ -319,6 +327,28 @@ static hipError_t upload_slots(const tang_ruleset_t* rs, SlotDev* d_slots, uint3
     return e;
 }
 
+// Makes room for a batch of an update; the least serves ordinary ones (100 rules take 30 KB).
+static hipError_t grow_staging(tang_ruleset_t* rs, size_t host_bytes, size_t dev_bytes) {
+    hipError_t e = hipSuccess;
+    if (host_bytes > rs->upd_host_cap) {
+        if (rs->upd_host) e = hipHostFree(rs->upd_host);
+        rs->upd_host = nullptr;
+        rs->upd_host_cap = 0;
+        const size_t cap = std::max<size_t>(host_bytes + host_bytes / 2, 1u << 18);
+        if (e == hipSuccess) e = hipHostMalloc(&rs->upd_host, cap, hipHostMallocDefault);
+        if (e == hipSuccess) rs->upd_host_cap = cap;
+    }
+    if (e == hipSuccess && dev_bytes > rs->upd_dev_cap) {
+        if (rs->upd_dev) e = dev_release(rs->upd_dev);
+        rs->upd_dev = nullptr;
+        rs->upd_dev_cap = 0;
+        const size_t cap = std::max<size_t>(dev_bytes + dev_bytes / 2, 1u << 18);
+        if (e == hipSuccess) e = dev_alloc(&rs->upd_dev, cap);
+        if (e == hipSuccess) rs->upd_dev_cap = cap;
+    }
+    return e;
+}
+
 int upload_all(tang_ruleset_t* rs) {
     TANG_HIP(hipSetDevice(rs->device));
     hipStream_t s = rs->upd_stream;
@@ -335,6 +365,7 @@ int upload_all(tang_ruleset_t* rs) {
     }
     TANG_HIP(dev_alloc(&rs->d_tt, sizeof(TupleTable)));
     TANG_HIP(dev_alloc(&rs->d_stats, kStatCopies * sizeof(StatsDev)));
+    TANG_HIP(grow_staging(rs, 1, 1));   // here rather than in the first update
 
     std::vector<Rec> recs(rs->rec_cap, dead_rec());
     for (uint32_t h = 0; h < rs->rules.size(); ++h)
@@ -354,14 +385,7 @@ int upload_all(tang_ruleset_t* rs) {
     if (!order.empty()) {
         std::vector<BoxDev> boxes(order.size());
         for (size_t i = 0; i < order.size(); ++i) {
-            const auto& hr = rs->rules[order[i]];
-            const tang_rule_t& r = hr.r;
-            uint32_t sm = pmask(r.sip_len), dm = pmask(r.dip_len);
-            boxes[i] = BoxDev{r.sip, r.sip | ~sm, r.dip, r.dip | ~dm,
-                              (uint32_t)r.sp_lo | ((uint32_t)r.sp_hi << 16),
-                              (uint32_t)r.dp_lo | ((uint32_t)r.dp_hi << 16),
-                              (uint32_t)r.proto | ((r.proto_mask ? 1u : 0u) << 8) | (hr.tuple << 16),
-                              hr.pos};
+            boxes[i] = box_of(rs->rules[order[i]]);
         }
         BoxDev* d_boxes = nullptr;
         TANG_HIP(dev_alloc(&d_boxes, boxes.size() * sizeof(BoxDev)));
@@ -388,6 +412,48 @@ int upload_all(tang_ruleset_t* rs) {
 
 namespace {
 
+// Arrays laid out one after another (16-byte aligned) in a staging block.
+struct Packer {
+    struct Part {
+        const void* p;
+        size_t at, bytes;
+    };
+    std::vector<Part> parts;
+    size_t size = 0;
+    size_t add(const void* p, size_t bytes) {
+        const size_t at = size;
+        parts.push_back({p, at, bytes});
+        size = (at + bytes + 15) & ~(size_t)15;
+        return at;
+    }
+    template <class T>
+    size_t add(const std::vector<T>& v) {
+        return add(v.data(), v.size() * sizeof(T));
+    }
+    void write(void* to) const {
+        for (const Part& x : parts)
+            if (x.bytes) std::memcpy(static_cast<char*>(to) + x.at, x.p, x.bytes);
+    }
+};
+
+// Staging that a batch larger than the ordinary left behind is given back.
+hipError_t trim_staging(tang_ruleset_t* rs) {
+    constexpr size_t kKeep = 16u << 20;
+    hipError_t e = hipSuccess;
+    if (rs->upd_host_cap > kKeep) {
+        e = hipHostFree(rs->upd_host);
+        rs->upd_host = nullptr;
+        rs->upd_host_cap = 0;
+    }
+    if (rs->upd_dev_cap > kKeep) {
+        const hipError_t e2 = dev_release(rs->upd_dev);
+        if (e == hipSuccess) e = e2;
+        rs->upd_dev = nullptr;
+        rs->upd_dev_cap = 0;
+    }
+    return e;
+}
+
 // Rewrites the given buckets on the device: each keeps its slot, its records are
 // re-laid in member order (in place if they fit, else at the end of the record array),
 // freed record positions are marked dead, conflict masks of moved rules move with them.
@@ -399,8 +465,8 @@ int flush(tang_ruleset_t* rs, const std::vector<uint32_t>& dirty, const std::vec
     if (rs->device == TANG_HOST_ONLY) return TANG_OK;
     TANG_HIP(hipSetDevice(rs->device));
     hipStream_t s = rs->upd_stream;
-    std::vector<char> is_fresh(rs->rules.size(), 0);
-    for (uint32_t h : fresh) is_fresh[h] = 1;
+    // fresh handles are the newest ones, in order
+    auto is_fresh = [&](uint32_t h) { return !fresh.empty() && h >= fresh.front(); };
 
     std::vector<uint32_t> src, dst;   // src: old position, or kNew | index into newrecs
     std::vector<Rec> newrecs;
@@ -466,7 +532,7 @@ int flush(tang_ruleset_t* rs, const std::vector<uint32_t>& dirty, const std::vec
         for (uint32_t i = 0; i < len; ++i) {
             uint32_t h = bk.members[i];
             auto& hr = rs->rules[h];
-            if (is_fresh[h]) {
+            if (is_fresh(h)) {
                 src.push_back(kNew | (uint32_t)newrecs.size());
                 newrecs.push_back(make_rec(rs, h));
             } else {
@@ -492,97 +558,77 @@ int flush(tang_ruleset_t* rs, const std::vector<uint32_t>& dirty, const std::vec
         }
     }
 
-    std::vector<void*> tmp;
-    std::vector<Slot> vals;   // host sources of async copies: alive until the final sync
-    std::vector<uint32_t> pos;
-    auto dev_copy = [&](const void* host, size_t bytes, void** out) -> hipError_t {
-        *out = nullptr;
-        if (!bytes) return hipSuccess;
-        hipError_t e = dev_alloc(out, bytes);
-        if (e != hipSuccess) return e;
-        tmp.push_back(*out);
-        return hipMemcpyAsync(*out, host, bytes, hipMemcpyHostToDevice, s);
-    };
-    hipError_t e = hipSuccess;
-    void *d_src = nullptr, *d_dst = nullptr, *d_new = nullptr, *d_stage = nullptr;
-    if (!dst.empty()) {
-        e = dev_copy(src.data(), src.size() * 4, &d_src);
-        if (e == hipSuccess) e = dev_copy(dst.data(), dst.size() * 4, &d_dst);
-        if (e == hipSuccess && !newrecs.empty())
-            e = dev_copy(newrecs.data(), newrecs.size() * sizeof(Rec), &d_new);
-        if (e == hipSuccess) {
-            e = dev_alloc(&d_stage, dst.size() * sizeof(Rec));
-            if (e == hipSuccess) tmp.push_back(d_stage);
-        }
-        if (e == hipSuccess)
-            e = launch_move_records(rs->d_recs, (const Rec*)d_new, (const uint32_t*)d_src,
-                                    (const uint32_t*)d_dst, (uint32_t)dst.size(), (Rec*)d_stage, rs->d_back, s);
-        if (e == hipSuccess && rs->nw > 1) {
-            void* d_mstage = nullptr;
-            e = dev_alloc(&d_mstage, dst.size() * rs->nw * sizeof(uint32_t));
-            if (e == hipSuccess) {
-                tmp.push_back(d_mstage);
-                e = launch_move_masks(rs->d_cmask, rs->nw, (const uint32_t*)d_src, (const uint32_t*)d_dst,
-                                      (uint32_t)dst.size(), (uint32_t*)d_mstage, s);
-            }
-        }
-    }
-    // conflict masks of fresh rules, and their bit in lower-priority rules they meet
-    if (e == hipSuccess && !fresh.empty()) {
-        pos.resize(fresh.size());
-        for (size_t i = 0; i < fresh.size(); ++i) pos[i] = rs->rules[fresh[i]].pos;
-        void* d_pos = nullptr;
-        e = dev_copy(pos.data(), pos.size() * 4, &d_pos);
-        if (e == hipSuccess)
-            e = launch_conflict_update(rs->d_recs, rs->d_cmask, rs->nw, rs->rec_used,
-                                       (const uint32_t*)d_pos, (uint32_t)pos.size(), rs->d_back, rs->d_slots, s);
+    std::sort(touched_slots.begin(), touched_slots.end());
+    touched_slots.erase(std::unique(touched_slots.begin(), touched_slots.end()), touched_slots.end());
+    std::vector<Slot> vals(touched_slots.size());
+    for (size_t i = 0; i < vals.size(); ++i) vals[i] = rs->slots[touched_slots[i]];
+    std::vector<FreshDev> fdev(fresh.size());
+    for (size_t i = 0; i < fresh.size(); ++i) {
+        const auto& hr = rs->rules[fresh[i]];
+        const tang_rule_t& r = hr.r;
+        fdev[i] = FreshDev{r.sip, pmask(r.sip_len), r.dip, pmask(r.dip_len), r.proto, r.proto_mask ? 0xFFu : 0u,
+                           (uint32_t)r.sp_lo | ((uint32_t)r.dp_lo << 16), (uint32_t)r.sp_hi | ((uint32_t)r.dp_hi << 16),
+                           r.priority, r.id, hr.tuple, hr.pos};
     }
     const TupleTable tt = make_tuple_table(rs);
-    if (e == hipSuccess) e = hipMemcpyAsync(rs->d_tt, &tt, tuple_table_bytes(tt), hipMemcpyHostToDevice, s);
-    // slots, with their first records as they are now, and the filter bits of new buckets
+
+    // The batch packed into the staging block, one copy; device-only scratch behind it.
+    Packer pk;
+    const size_t o_src = pk.add(src), o_dst = pk.add(dst), o_new = pk.add(newrecs), o_fresh = pk.add(fdev),
+                 o_idx = pk.add(touched_slots), o_val = pk.add(vals), o_sidx = pk.add(split_slots),
+                 o_info = pk.add(split_info);
+    const size_t packed = pk.size, o_tt = pk.add(&tt, tuple_table_bytes(tt)), host_bytes = pk.size;
+    const size_t o_stage = (packed + 255) & ~(size_t)255, o_mstage = o_stage + dst.size() * sizeof(Rec);
+    const size_t dev_bytes = o_mstage + (rs->nw > 1 ? dst.size() * rs->nw * sizeof(uint32_t) : 0);
+    hipError_t e = grow_staging(rs, host_bytes, dev_bytes);
+    char* const d = static_cast<char*>(rs->upd_dev);
+    auto at = [&](size_t off) { return reinterpret_cast<uint32_t*>(d + off); };
     if (e == hipSuccess) {
-        if (rehash) {
-            SlotDev* ns = nullptr;
-            Slot* d_val = nullptr;
-            uint32_t* nf = nullptr;
-            e = hipStreamSynchronize(s);
-            if (e == hipSuccess) e = dev_alloc(&ns, rs->slots.size() * sizeof(SlotDev));
-            if (e == hipSuccess) e = dev_alloc(&nf, (size_t)rs->filter_blocks * 8);
-            if (e == hipSuccess) e = hipMemsetAsync(nf, 0, (size_t)rs->filter_blocks * 8, s);
-            if (e == hipSuccess) e = upload_slots(rs, ns, nf, &d_val, s);
-            if (e == hipSuccess) e = hipStreamSynchronize(s);
-            if (d_val) (void)dev_release(d_val);
-            if (e == hipSuccess) {
-                (void)dev_release(rs->d_slots);
-                (void)dev_release(rs->d_filter);
-                rs->d_slots = ns;
-                rs->d_filter = nf;
-            } else {
-                if (ns) (void)dev_release(ns);
-                if (nf) (void)dev_release(nf);
-            }
-        } else if (!touched_slots.empty()) {
-            std::sort(touched_slots.begin(), touched_slots.end());
-            touched_slots.erase(std::unique(touched_slots.begin(), touched_slots.end()),
-                                touched_slots.end());
-            vals.resize(touched_slots.size());
-            for (size_t i = 0; i < vals.size(); ++i) vals[i] = rs->slots[touched_slots[i]];
-            void *d_idx = nullptr, *d_val = nullptr;
-            e = dev_copy(touched_slots.data(), touched_slots.size() * 4, &d_idx);
-            if (e == hipSuccess) e = dev_copy(vals.data(), vals.size() * sizeof(Slot), &d_val);
-            if (e == hipSuccess)
-                e = launch_fill_slots(rs->d_slots, (const uint32_t*)d_idx, (const Slot*)d_val,
-                                      (uint32_t)vals.size(), rs->d_recs, rs->d_back, rs->d_filter, rs->d_tt, s);
-            void *d_sidx = nullptr, *d_info = nullptr;
-            if (e == hipSuccess) e = dev_copy(split_slots.data(), split_slots.size() * 4, &d_sidx);
-            if (e == hipSuccess) e = dev_copy(split_info.data(), split_info.size() * sizeof(SplitInfo), &d_info);
-            if (e == hipSuccess)
-                e = launch_fill_split(rs->d_slots, (const uint32_t*)d_sidx, (const SplitInfo*)d_info,
-                                      (uint32_t)split_slots.size(), s);
+        pk.write(rs->upd_host);
+        if (packed) e = hipMemcpyAsync(d, rs->upd_host, packed, hipMemcpyHostToDevice, s);
+    }
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(rs->d_tt, static_cast<char*>(rs->upd_host) + o_tt, tuple_table_bytes(tt),
+                           hipMemcpyHostToDevice, s);
+    if (e == hipSuccess)
+        e = launch_move_records(rs->d_recs, (const Rec*)(d + o_new), at(o_src), at(o_dst), (uint32_t)dst.size(),
+                                (Rec*)(d + o_stage), rs->d_back, s);
+    if (e == hipSuccess && rs->nw > 1)
+        e = launch_move_masks(rs->d_cmask, rs->nw, at(o_src), at(o_dst), (uint32_t)dst.size(), at(o_mstage), s);
+    // conflict masks of fresh rules, and their bit in lower-priority rules they meet
+    if (e == hipSuccess)
+        e = launch_conflict_update(rs->d_recs, rs->d_cmask, rs->nw, rs->rec_used, (const FreshDev*)(d + o_fresh),
+                                   (uint32_t)fdev.size(), rs->d_back, rs->d_slots, s);
+    // slots, with their first records as they are now, and the filter bits of new buckets
+    if (e == hipSuccess && rehash) {
+        SlotDev* ns = nullptr;
+        uint32_t* nf = nullptr;
+        Slot* d_val = nullptr;
+        e = hipStreamSynchronize(s);
+        if (e == hipSuccess) e = dev_alloc(&ns, rs->slots.size() * sizeof(SlotDev));
+        if (e == hipSuccess) e = dev_alloc(&nf, (size_t)rs->filter_blocks * 8);
+        if (e == hipSuccess) e = hipMemsetAsync(nf, 0, (size_t)rs->filter_blocks * 8, s);
+        if (e == hipSuccess) e = upload_slots(rs, ns, nf, &d_val, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        if (d_val) (void)dev_release(d_val);
+        if (e == hipSuccess) {
+            (void)dev_release(rs->d_slots);
+            (void)dev_release(rs->d_filter);
+            rs->d_slots = ns;
+            rs->d_filter = nf;
+        } else {
+            if (ns) (void)dev_release(ns);
+            if (nf) (void)dev_release(nf);
         }
+    } else if (e == hipSuccess) {
+        e = launch_fill_slots(rs->d_slots, at(o_idx), (const Slot*)(d + o_val), (uint32_t)vals.size(), rs->d_recs,
+                              rs->d_back, rs->d_filter, rs->d_tt, s);
+        if (e == hipSuccess)
+            e = launch_fill_split(rs->d_slots, at(o_sidx), (const SplitInfo*)(d + o_info),
+                                  (uint32_t)split_slots.size(), s);
     }
     hipError_t e2 = hipStreamSynchronize(s);
-    for (void* p : tmp) (void)dev_release(p);
+    if (e2 == hipSuccess) e2 = trim_staging(rs);
     if (e != hipSuccess) return hip_fail(e, "update flush");
     if (e2 != hipSuccess) return hip_fail(e2, "update flush sync");
     return TANG_OK;
@@ -644,7 +690,7 @@ int apply_insert(tang_ruleset_t* rs, const tang_rule_t* rules, size_t n) {
                                          std::to_string(kMaxBucketLen) + " rules");
     }
     std::vector<uint32_t> dirty, fresh;
-    std::vector<char> mark(rs->buckets.size() + n, 0);
+    std::unordered_set<uint32_t> mark;
     size_t nb_before = rs->buckets.size();
     for (size_t i = 0; i < n; ++i) {
         tang_rule_t r = normalise(rules[i]);
@@ -664,7 +710,6 @@ int apply_insert(tang_ruleset_t* rs, const tang_rule_t* rules, size_t n) {
                                r.dip & pmask(rs->sigs[t].second)};
         const uint32_t mb = find_or_add_bucket(rs, k);
         const uint32_t b = rs->buckets[mb].split ? find_or_add_bucket(rs, sub_key(rs, mb, h)) : mb;
-        if (rs->buckets.size() > mark.size()) mark.resize(rs->buckets.size() + n, 0);
         auto& mem = rs->buckets[b].members;
         auto pos = std::upper_bound(mem.begin(), mem.end(), h, [&](uint32_t a, uint32_t x) {
             return key_of(rs->rules[a].r) < key_of(rs->rules[x].r);
@@ -673,9 +718,8 @@ int apply_insert(tang_ruleset_t* rs, const tang_rule_t* rules, size_t n) {
         rs->rules[h].bucket = b;
         std::vector<uint32_t> changed{b};
         if (b == mb && mem.size() > kSplitAt) changed = split_bucket(rs, mb);
-        if (rs->buckets.size() > mark.size()) mark.resize(rs->buckets.size() + n, 0);
         for (uint32_t c : changed)
-            if (!mark[c]) { mark[c] = 1; dirty.push_back(c); }
+            if (mark.insert(c).second) dirty.push_back(c);
         fresh.push_back(h);
     }
     // new buckets need slots; grow the table when it would pass half full
@@ -705,7 +749,7 @@ int apply_delete(tang_ruleset_t* rs, const uint32_t* ids, size_t n) {
             return fail(TANG_ENOTFOUND, "rule id " + std::to_string(ids[i]) + " is not live");
     }
     std::vector<uint32_t> dirty;
-    std::vector<char> mark(rs->buckets.size(), 0);
+    std::unordered_set<uint32_t> mark;
     for (size_t i = 0; i < n; ++i) {
         uint32_t h = rs->id2h[ids[i]];
         auto& hr = rs->rules[h];
@@ -715,7 +759,7 @@ int apply_delete(tang_ruleset_t* rs, const uint32_t* ids, size_t n) {
         rs->id2h.erase(ids[i]);
         rs->n_live--;
         if (rs->sigs[hr.tuple] != std::make_pair(hr.r.sip_len, hr.r.dip_len)) rs->n_coarse--;
-        if (!mark[hr.bucket]) { mark[hr.bucket] = 1; dirty.push_back(hr.bucket); }
+        if (mark.insert(hr.bucket).second) dirty.push_back(hr.bucket);
     }
     return flush_or_fail(rs, dirty, {}, false);
 }

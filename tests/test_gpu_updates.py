@@ -145,3 +145,25 @@ def test_update_rounds_at_512k_sampled():
                 assert orc.rule_matches(all_rules[by_id[int(got[k])]], pk[k])
     finally:
         T.tang_ruleset_destroy(rs)
+
+
+@pytest.mark.parametrize("n_new", [1, 256, 601])
+@pytest.mark.parametrize("space", ["narrow", "wide", "all"])
+def test_inserted_masks_equal_bruteforce(space, n_new):
+    """One batch inserted (one rule; one whole tile of 256; two tiles and a remainder), keys
+    between those of the old rules and with ties: every rule's mask, old and new, has exactly
+    the brute-force bits."""
+    torch_cuda()
+    rules = synth.make_rules(900 + n_new, seed=406, wide=space == "wide", all_lengths=space == "all")
+    rng = np.random.default_rng(3)
+    rules["priority"] = rng.integers(0, 100, len(rules))
+    rules = rules[rng.permutation(len(rules))]
+    rs = T.tang_ruleset_create(0, rules[:900])
+    try:
+        T.tang_insert(rs, rules[900:])
+        rt = np.array([T.tang_ruleset_rule_tuple(rs, int(i)) for i in rules["id"]])
+        want = orc.conflict_masks(rules, rt)
+        for k in range(len(rules)):
+            assert T.tang_ruleset_conflict_mask(rs, int(rules[k]["id"])) == int(want[k]), (k, k >= 900)
+    finally:
+        T.tang_ruleset_destroy(rs)
