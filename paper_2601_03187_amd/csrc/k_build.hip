@@ -224,7 +224,7 @@ __global__ void k_fill_slots(SlotDev* __restrict__ slots, const uint32_t* __rest
     if (g.gkey == kNoGroup) return;
     const bool by_dip = (g.gkey & 64u) != 0u;
     const uint32_t v = by_dip ? d.s.md : d.s.ms, o = by_dip ? d.s.ms : d.s.md;
-    uint32_t* blk = filter + 2u * (filter_block(g.salt, v) & tt->filter_mask);
+    uint32_t* blk = filter + 2u * filter_block(g.salt, v, tt->filter_shift);
     const uint32_t h = filter_hash(filter_salt(tk), o);
     atomicOr(blk, 0x80000000u >> filter_pos_x(h));
     atomicOr(blk + 1, 0x80000000u >> filter_pos_y(h));

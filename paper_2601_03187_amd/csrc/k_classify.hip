@@ -25,12 +25,12 @@ namespace tang {
 namespace {
 
 constexpr uint32_t kNoTuple = 0xFFFFFFFFu;
-// Sets of 64 headers per wave, rulesets of at most 32 tuples: two from this many headers on,
-// one below. More sets keep a wave's lanes busy longer, fewer make more waves (100,000
-// rules, one set and two: 262,144 headers 76 and 97 us, 600,000 116 and 115, 1,048,576 162
-// and 150; 512k rules with 25% wildcard-heavy rules 51 and 53, 92 and 78, 138 and 116). Four
-// sets need 36 KB of LDS and leave four waves per SIMD: 1,800 rules, 4.2M headers 316 us
-// against 265 with two.
+// Sets of 64 headers per wave, rulesets of at most 32 tuples: two, through a queue, from this
+// many headers on, one below. More sets keep a wave's lanes busy longer, fewer make more waves
+// (one set and two: 100,000 rules, 600,000 headers 99 and 112 us, 1,048,576 141 and 151,
+// 4,194,304 436 and 362; 512k rules with 25% wildcard-heavy rules 92 and 77, 139 and 114, 471
+// and 355). Four sets need 36 KB of LDS and leave four waves per SIMD: 1,800 rules, 4.2M
+// headers 316 us against 265 with two.
 constexpr uint32_t kQueueFrom = 1u << 19;
 
 __device__ __forceinline__ bool kless(uint32_t p1, uint32_t i1, uint32_t p2, uint32_t i2) {
@@ -87,13 +87,16 @@ __global__ __launch_bounds__(256) void k_classify(const uint4* __restrict__ hdr,
     constexpr uint32_t NT = 32u * NW;
     constexpr uint32_t CB = NW > kMaskWords ? 16u : 8u;   // bits per packed candidate
     constexpr uint32_t NE = 64u * R;                      // entries per wave
+    // The largest tables leave out the ranks, which then come from memory: 28 KB of LDS and
+    // five waves per SIMD, 32 KB and four with them.
+    constexpr bool kRankLds = NW <= kMaskWords;
     __shared__ TupleDev s_t[NT];
-    __shared__ TupleGroup s_tg[NT];
     __shared__ uint2 s_after[NT];   // smallest best key from a tuple on
-    __shared__ uint2 s_rank[NT];  // best keys in ascending order
-    __shared__ uint4 s_hdr[4][NE];
-    __shared__ Entry s_ent[4][NE];
-    __shared__ uint16_t s_queue[4][NE];
+    __shared__ uint2 s_rank[kRankLds ? NT : 1];   // best keys in ascending order
+    // with one set a lane keeps its own header, and nothing is queued
+    __shared__ uint4 s_hdr[4][R > 1 ? NE : 1];
+    __shared__ Entry s_ent[4][R > 1 ? NE : 1];
+    __shared__ uint16_t s_queue[4][R > 1 ? NE : 1];
     __shared__ uint32_t s_work[4][NW > 1 ? NW : 1][NW > 1 ? NE : 1];
     __shared__ uint32_t s_prefix[NW == 1 ? NT + 1 : 1];
     __shared__ uint32_t s_tup[4][STATS ? NE : 1];   // the answer's tuple
@@ -102,12 +105,11 @@ __global__ __launch_bounds__(256) void k_classify(const uint4* __restrict__ hdr,
     if (live) n = min(n, *live);
     if (blockIdx.x * 4u * NE >= n) return;   // uniform over the block (a live count below the grid)
     const uint32_t ntup = ttg->n, ngroups = ttg->ngroups;
-    const uint32_t slot_mask = ttg->slot_mask, filter_mask = ttg->filter_mask;
+    const uint32_t slot_mask = ttg->slot_mask, filter_shift = ttg->filter_shift;
     for (uint32_t k = tid; k < ntup; k += 256u) {
         s_t[k] = ttg->t[k];
-        s_tg[k] = ttg->tg[k];
         s_after[k] = make_uint2(ttg->after_prio[k], ttg->after_id[k]);
-        s_rank[k] = make_uint2(ttg->rank_prio[k], ttg->rank_id[k]);
+        if (kRankLds) s_rank[k] = make_uint2(ttg->rank_prio[k], ttg->rank_id[k]);
     }
     if constexpr (NW == 1)
         if (tid <= NT) s_prefix[tid] = ttg->prefix[tid][0];
@@ -117,8 +119,15 @@ __global__ __launch_bounds__(256) void k_classify(const uint4* __restrict__ hdr,
     uint4* const hd = s_hdr[wave];
     Entry* const ent = s_ent[wave];
     uint16_t* const queue = s_queue[wave];
+    uint4 own_hdr = make_uint4(0u, 0u, 0u, 0u);
+    Entry own = Entry{kDead, kDead, 0u, 0u};
+    auto header = [&](uint32_t e) -> uint4& { return R > 1 ? hd[e] : own_hdr; };
+    auto entry = [&](uint32_t e) -> Entry& { return R > 1 ? ent[e] : own; };
     uint32_t n_probe = 0, n_slots = 0, n_recs = 0, top1 = 0, fb = 0, nm = 0;
     uint32_t n_filter = 0, n_steps = 0, n_rounds = 0;
+    // a vector instruction takes one scalar operand: the salt, so this one is held in a vector
+    uint32_t hash_c = kFilterHashC;
+    asm("" : "+v"(hash_c));
 
     // Pass 0 probes the predicted tuples, pass 1 certifies.
     for (uint32_t pass = kcand > 0 ? 0u : 1u; pass < 2u; ++pass) {
@@ -130,10 +139,10 @@ __global__ __launch_bounds__(256) void k_classify(const uint4* __restrict__ hdr,
             uint4 h = make_uint4(0u, 0u, 0u, 0u);
             if (pass == 0 || kcand == 0) {
                 if (active) h = hdr[base + e];
-                hd[e] = h;
+                header(e) = h;
                 if (STATS) s_tup[wave][e] = kNoTuple;
             } else {
-                h = hd[e];
+                h = header(e);
             }
             const uint32_t sip = h.x, dip = h.y;
             uint32_t cand = 0;
@@ -147,13 +156,13 @@ __global__ __launch_bounds__(256) void k_classify(const uint4* __restrict__ hdr,
                 for (int c = 0; c < kcand; ++c) {
                     const uint32_t t = (cand >> (CB * c)) & ((1u << CB) - 1u);
                     if (!active || t >= ntup) continue;
-                    const TupleGroup tg = s_tg[t];
+                    const TupleGroup tg = ttg->tg[t];
                     bool pass_f = true;
                     if (tg.gkey != kNoGroup) {
                         const uint32_t ms = sip & s_t[t].smask, md = dip & s_t[t].dmask;
                         const bool by_dip = (tg.gkey & 64u) != 0u;   // the group's field
                         const uint32_t v = by_dip ? md : ms, o = by_dip ? ms : md;
-                        const uint2 blk = filter[filter_block(tg.salt, v) & filter_mask];
+                        const uint2 blk = filter[filter_block(tg.salt, v, filter_shift)];
                         pass_f = filter_has(blk, filter_hash(filter_salt(t), o)) >> 31;
                         if (STATS) ++n_filter;
                     }
@@ -165,10 +174,10 @@ __global__ __launch_bounds__(256) void k_classify(const uint4* __restrict__ hdr,
                         work |= 1u << (t >> 5);
                     }
                 }
-                ent[e] = Entry{kDead, kDead, 0u, work};
+                entry(e) = Entry{kDead, kDead, 0u, work};
             } else {
                 Entry b{kDead, kDead, 0u, 0u};
-                if (kcand > 0) b = ent[e];
+                if (kcand > 0) b = entry(e);
                 const bool found = b.id != kDead;
                 if (STATS) fb += active && !found;
                 // The certification set: the answer's conflict mask, or every tuple after a
@@ -180,8 +189,11 @@ __global__ __launch_bounds__(256) void k_classify(const uint4* __restrict__ hdr,
                     k = 0;
 #pragma unroll
                     for (uint32_t step = NT; step > 0; step >>= 1)
-                        if (k + step <= ntup && kless(s_rank[k + step - 1].x, s_rank[k + step - 1].y, b.prio, b.id))
-                            k += step;
+                        if (k + step <= ntup) {
+                            const uint32_t j = k + step - 1u;
+                            const uint2 r = kRankLds ? s_rank[j] : make_uint2(ttg->rank_prio[j], ttg->rank_id[j]);
+                            if (kless(r.x, r.y, b.prio, b.id)) k += step;
+                        }
                 }
                 uint32_t todo[NW];
                 if constexpr (NW == 1) {
@@ -214,8 +226,12 @@ __global__ __launch_bounds__(256) void k_classify(const uint4* __restrict__ hdr,
                 }
                 // The filter: eight groups at a time, each lane's blocks loaded together, then
                 // each group's tuples. Groups and tuples are the same for every lane, so masks
-                // and salts are scalars and a test is a few vector instructions; a lane that
-                // does not need a group reads block 0 with the others and drops the outcome.
+                // and salts are scalars, four tuples to a load, and a test is ten vector
+                // instructions without a branch; a lane that does not need a group reads block 0
+                // with the others and drops the outcome. This is most of what a wide ruleset's
+                // search does: 387 tuples, 1M headers 842 us with one scalar load, a 32-bit
+                // product and a branch per tuple, 594 so, and 548 with the headers in registers
+                // (five waves per SIMD instead of four).
                 uint32_t hits = 0;
                 if constexpr (NW == 1) {
                     hits = todo[0] & ttg->nogroup[0];
@@ -223,6 +239,9 @@ __global__ __launch_bounds__(256) void k_classify(const uint4* __restrict__ hdr,
 #pragma unroll
                     for (int w = 0; w < NW; ++w) s_work[wave][w][e] = todo[w] & ttg->nogroup[w];
                 }
+                const bool every = NW > 1 && !__ballot(found);   // no lane can leave a group out
+                uint32_t k0 = 0;
+                FilterOps ops = *reinterpret_cast<const FilterOps*>(ttg->fop);
                 for (uint32_t g0 = 0; g0 < ngroups; g0 += 8u) {
                     uint2 blk[8];
                     if (STATS) ++n_rounds;
@@ -231,12 +250,14 @@ __global__ __launch_bounds__(256) void k_classify(const uint4* __restrict__ hdr,
                         blk[q] = make_uint2(0u, 0u);
                         if (g0 + q < ngroups) {
                             const FilterGroup fg = ttg->fg[g0 + q];
-                            uint32_t need = 0;
+                            uint32_t need = active;
+                            if (!every) {
+                                need = 0;
 #pragma unroll
-                            for (int w = 0; w < NW; ++w) need |= todo[w] & ttg->gmask[g0 + q][w];
+                                for (int w = 0; w < NW; ++w) need |= todo[w] & ttg->gmask[g0 + q][w];
+                            }
                             const uint32_t v = (fg.dip ? dip : sip) & fg.mask;
-                            const uint32_t at = need ? filter_block(fg.salt, v) & filter_mask : 0u;
-                            blk[q] = filter[at];
+                            blk[q] = filter[need ? filter_block(fg.salt, v, filter_shift) : 0u];
                             if (STATS) n_filter += need != 0;
                         }
                     }
@@ -245,13 +266,23 @@ __global__ __launch_bounds__(256) void k_classify(const uint4* __restrict__ hdr,
                         if (g0 + q < ngroups) {
                             const FilterGroup fg = ttg->fg[g0 + q];
                             const uint32_t ov = fg.dip ? sip : dip;
-                            for (uint32_t k = fg.begin; k < fg.end; ++k) {
-                                const FilterOp op = ttg->fop[k];
-                                const uint32_t has = filter_has(blk[q], filter_hash(op.salt, ov & op.omask));
-                                if constexpr (NW == 1) {
-                                    hits |= (has >> 31) << op.t;
-                                } else {
-                                    if (has >> 31) atomicOr(&s_work[wave][op.t >> 5][e], 1u << (op.t & 31u));
+                            // the groups' tuples follow one another; the next four are loaded
+                            // while these are tested
+                            while (k0 < fg.end) {
+                                const uint32_t m = min(fg.end - k0, (uint32_t)kOpsAtOnce);
+                                const FilterOps now = ops;
+                                k0 += m;
+                                ops = *reinterpret_cast<const FilterOps*>(ttg->fop + k0);
+#pragma unroll
+                                for (uint32_t j = 0; j < (uint32_t)kOpsAtOnce; ++j) {
+                                    if (j >= m) break;
+                                    const FilterOp op = now.op[j];
+                                    const uint32_t has =
+                                        filter_has(blk[q], dot16(ov & op.omask, hash_c, op.salt)) >> 31;
+                                    if constexpr (NW == 1)
+                                        hits |= has << (op.salt & 31u);
+                                    else
+                                        atomicOr(&s_work[wave][(op.salt & 0x1FFu) >> 5][e], has << (op.salt & 31u));
                                 }
                             }
                         }
@@ -267,11 +298,13 @@ __global__ __launch_bounds__(256) void k_classify(const uint4* __restrict__ hdr,
                         work |= m ? 1u << w : 0u;
                     }
                 }
-                ent[e] = Entry{b.prio, b.id, b.cm, work};
+                entry(e) = Entry{b.prio, b.id, b.cm, work};
             }
-            const unsigned long long has = __ballot(work != 0u);
-            if (work) queue[qn + lanes_below(has)] = (uint16_t)e;
-            qn += (uint32_t)__popcll(has);
+            if constexpr (R > 1) {
+                const unsigned long long has = __ballot(work != 0u);
+                if (work) queue[qn + lanes_below(has)] = (uint16_t)e;
+                qn += (uint32_t)__popcll(has);
+            }
         }
         wave_sync();
 
@@ -289,30 +322,36 @@ __global__ __launch_bounds__(256) void k_classify(const uint4* __restrict__ hdr,
         uint32_t ct = 0, tk = 0, k0 = 0, k1 = 0, bi = 0, left = 0;
         uint32_t sub = 0;   // sub-lists of a split bucket still to visit (bit 0 DP, SP, protocol, rest)
         uint32_t at = 0, walk = 0;   // slot or record index; steps of the slot walk
+        auto take = [&](uint32_t e) {
+            const uint4 h = header(e);
+            const Entry b = entry(e);
+            sip = h.x;
+            dip = h.y;
+            ports = h.z;
+            proto = h.w & 0xFFu;
+            bp = b.prio;
+            bid = b.id;
+            bcm = b.cm;
+            cur = NW == 1 ? b.work : 0u;
+            nz = NW == 1 ? 0u : b.work;
+        };
+        if constexpr (R == 1) {
+            e = lane;
+            take(e);
+            ps = own.work ? P_NEXT : P_IDLE;
+        }
         for (;;) {
-            const unsigned long long idle = __ballot(ps == P_IDLE);
-            if (idle && taken < qn) {
-                const uint32_t q = taken + lanes_below(idle);
-                if (ps == P_IDLE && q < qn) {
-                    e = queue[q];
-                    const uint4 h = hd[e];
-                    const Entry b = ent[e];
-                    sip = h.x;
-                    dip = h.y;
-                    ports = h.z;
-                    proto = h.w & 0xFFu;
-                    bp = b.prio;
-                    bid = b.id;
-                    bcm = b.cm;
-                    if constexpr (NW == 1) {
-                        cur = b.work;
-                    } else {
-                        cur = 0;
-                        nz = b.work;
+            if constexpr (R > 1) {
+                const unsigned long long idle = __ballot(ps == P_IDLE);
+                if (idle && taken < qn) {
+                    const uint32_t q = taken + lanes_below(idle);
+                    if (ps == P_IDLE && q < qn) {
+                        e = queue[q];
+                        take(e);
+                        ps = P_NEXT;
                     }
-                    ps = P_NEXT;
+                    taken = min(qn, taken + (uint32_t)__popcll(idle));
                 }
-                taken = min(qn, taken + (uint32_t)__popcll(idle));
             }
             if (ps == P_NEXT) {
                 ps = P_IDLE;
@@ -345,10 +384,10 @@ __global__ __launch_bounds__(256) void k_classify(const uint4* __restrict__ hdr,
                         break;
                     }
                 }
-                if (ps == P_IDLE) ent[e] = Entry{bp, bid, bcm, 0u};   // nothing left to probe
+                if (R > 1 && ps == P_IDLE) ent[e] = Entry{bp, bid, bcm, 0u};   // nothing left to probe
             }
             if (!__ballot(ps != P_IDLE)) {
-                if (taken >= qn) break;
+                if (R == 1 || taken >= qn) break;
                 continue;
             }
             if (STATS) ++n_steps;
@@ -441,15 +480,16 @@ __global__ __launch_bounds__(256) void k_classify(const uint4* __restrict__ hdr,
                     ps = P_NEXT;
                 } else {
                     ps = P_IDLE;
-                    ent[e] = Entry{bp, bid, bcm, 0u};
+                    if (R > 1) ent[e] = Entry{bp, bid, bcm, 0u};
                 }
             }
         }
+        if constexpr (R == 1) own = Entry{bp, bid, bcm, 0u};
         wave_sync();
     }
 #pragma unroll 1
     for (uint32_t e = lane; e < cnt; e += 64u) {
-        const uint32_t id = ent[e].id;
+        const uint32_t id = entry(e).id;
         if (STATS) {
             nm += id == kDead;
             if (kcand > 0 && id != kDead) top1 += s_tup[wave][e] == (out[base + e] & ((1u << CB) - 1u));
@@ -496,11 +536,12 @@ hipError_t launch_classify(const tang_ruleset_t* rs, const tang_header_t* d_hdr,
         };
         // Records per step, small batches (U = 1, 2, 4; 65,536 headers): 100,000 rules 52, 45,
         // 43 us, 1,800 rules 28, 30, 33; two sets, 4.2M headers (U = 1, 2): 100,000 rules 368
-        // and 344, 512k 259 and 265, 1,800 225 and 241. 144 tuples, 1M (U = 1, 2, 4) 230, 223,
-        // 251; 387 tuples, 1M 829, 838, 854.
-        // Wider rulesets take one set: two need 44 and 71 KB of LDS per workgroup, and the
-        // waves lost cost more than the fuller lanes give (144 tuples, 2.1M headers: 387
-        // against 476 us; 387 tuples, 1M: 884 against 977).
+        // and 344, 512k 259 and 265, 1,800 225 and 241. 144 tuples (U = 1, 2), 65,536 headers 64
+        // and 59, 2.1M 293 and 295; 387 tuples, 1M 548 and 570.
+        // Wider rulesets take one set: two need LDS for the headers and a second set of work
+        // rows, and the waves lost cost more than the fuller lanes give (with the headers in
+        // LDS in both forms, 144 tuples, 2.1M headers: 387 against 476 us; 387 tuples, 1M: 884
+        // against 977).
         if (rs->nw == 1) {
             if (stats) go(k_classify<true, 1, 2, 1>, 2);
             else if (m >= kQueueFrom) go(k_classify<false, 1, 2, 1>, 2);

@@ -136,8 +136,12 @@ constexpr uint32_t kNoGroup = 0xFFu;
 struct alignas(32) FilterGroup {
     uint32_t dip, mask, salt, begin, end, pad[3];
 };
-struct alignas(16) FilterOp {
-    uint32_t omask, salt, t, pad;
+struct alignas(8) FilterOp {
+    uint32_t omask, salt;   // the salt's low 9 bits are the tuple
+};
+constexpr int kOpsAtOnce = 4;   // FilterOps per scalar load; the table has as many to spare
+struct alignas(8) FilterOps {
+    FilterOp op[kOpsAtOnce];
 };
 // A tuple's group for a lane that tests one tuple of its own: key (kNoGroup: none) and salt.
 struct alignas(8) TupleGroup {
@@ -149,7 +153,7 @@ struct TupleTable {
     uint32_t n;                       // number of tuples
     uint32_t all_mask[kMaxWords];     // bits of all tuples
     uint32_t slot_mask;               // slots - 1
-    uint32_t filter_mask;             // filter blocks - 1
+    uint32_t filter_shift;            // 32 - log2(filter blocks)
     uint32_t nw;                      // mask words of this ruleset (1, kMaskWords or kMaxWords)
     TupleGroup tg[TANG_MAX_TUPLES];
     // smallest best key among tuples t, t + 1, ...: a probe in tuple order stops there once
@@ -160,7 +164,7 @@ struct TupleTable {
     uint32_t gmask[kMaxGroups][kMaxWords];  // tuples of each group
     uint32_t nogroup[kMaxWords];      // tuples without a group (always pass)
     FilterGroup fg[kMaxGroups];
-    FilterOp fop[TANG_MAX_TUPLES];
+    FilterOp fop[TANG_MAX_TUPLES + 2 * kOpsAtOnce];
     // prefix[k]: the k tuples of lowest best key, as mask words; rows past n are not copied
     // to the device
     uint32_t prefix[TANG_MAX_TUPLES + 1][kMaxWords];
@@ -195,17 +199,27 @@ __host__ __device__ inline uint32_t key_hash(uint32_t t, uint32_t ms, uint32_t m
 // lengths per field), where a bit per tuple took one load each. A clear bit means no
 // bucket; a set pair may be a collision, which only costs a slot walk. Placement never
 // affects answers.
-__host__ __device__ inline uint32_t filter_block(uint32_t salt, uint32_t v) {
-    uint32_t x = v ^ salt;
-    x *= 0x85EBCA6Bu;
-    x ^= x >> 15;
-    x *= 0xC2B2AE35u;
-    x ^= x >> 16;
-    return x;
+// Both hashes are sums of two 16-bit products and a salt, whose top bits count: one
+// instruction at the full rate of the vector units, where a 32-bit product takes four times
+// as long. (The key hash stays with products: with dot16 the search gained 0 to 4%, but 1,820
+// rules' headers met 25% more slots.) The constants were picked on the rulesets of synth.py,
+// 1,000 to 524,288 rules of 25, 144 and 387 tuples: within 5% as many tuples pass as with
+// independent hashes; other constants let up to three times as many pass.
+__host__ __device__ inline uint32_t dot16(uint32_t x, uint32_t c, uint32_t add) {
+#ifdef __HIP_DEVICE_COMPILE__
+    typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, x), __builtin_bit_cast(u16x2, c), add, false);
+#else
+    return (x & 0xFFFFu) * (c & 0xFFFFu) + (x >> 16) * (c >> 16) + add;
+#endif
 }
-__host__ __device__ inline uint32_t group_salt(uint32_t gkey) { return (gkey + 1u) * 0x9E3779B9u; }
-__host__ __device__ inline uint32_t filter_salt(uint32_t t) { return (t + 1u) * 0x7FEB352Du; }
-__host__ __device__ inline uint32_t filter_hash(uint32_t salt, uint32_t o) { return (o ^ salt) * 0x846CA68Bu; }
+__host__ __device__ inline uint32_t filter_block(uint32_t salt, uint32_t v, uint32_t shift) {
+    return dot16(v, 0xEAFF1A09u, salt) >> shift;
+}
+__host__ __device__ inline uint32_t group_salt(uint32_t gkey) { return (gkey + 1u) * 0xCCEA71FFu; }
+__host__ __device__ inline uint32_t filter_salt(uint32_t t) { return ((t + 1u) * 0xFD724453u & ~0x1FFu) | t; }
+constexpr uint32_t kFilterHashC = 0x4A15876Bu;
+__host__ __device__ inline uint32_t filter_hash(uint32_t salt, uint32_t o) { return dot16(o, kFilterHashC, salt); }
 // One bit in each half of the block, counted from the top: shifting each half left by its
 // position brings the bit to the sign, so a test is two shifts and an AND. Bit 31 of the
 // result: set in both halves.

@@ -220,11 +220,11 @@ TupleTable make_tuple_table(const tang_ruleset_t* rs) {
         f.salt = group_salt(tt.gkey[g]);
         f.begin = ops;
         for (uint32_t t = 0; t < n; ++t)
-            if (tt.tg[t].gkey == tt.gkey[g]) tt.fop[ops++] = FilterOp{f.dip ? tt.t[t].smask : tt.t[t].dmask, filter_salt(t), t, 0u};
+            if (tt.tg[t].gkey == tt.gkey[g]) tt.fop[ops++] = FilterOp{f.dip ? tt.t[t].smask : tt.t[t].dmask, filter_salt(t)};
         f.end = ops;
     }
     tt.slot_mask = rs->slots.empty() ? 0 : (uint32_t)rs->slots.size() - 1;
-    tt.filter_mask = rs->filter_blocks ? rs->filter_blocks - 1u : 0u;
+    tt.filter_shift = 32u - (uint32_t)__builtin_ctz(std::max(rs->filter_blocks, 2u));   // a power of two, 1024 or more
     return tt;
 }
 
