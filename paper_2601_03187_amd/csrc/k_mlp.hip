@@ -298,8 +298,8 @@ __device__ __forceinline__ Scored take_best(float (&v)[KL], int (&cl)[KL]) {
 // displaces, so ties keep the lower class; a NaN or -inf score counts as -FLT_MAX, so every
 // real class beats an empty slot and a padded class.
 template <int KS, int KL>
-__device__ __forceinline__ void keep_best(float (&v)[KL], int (&cl)[KL], float val, int c, int C) {
-    float x = c < C ? (val == val ? fmaxf(val, -FLT_MAX) : -FLT_MAX) : -INFINITY;
+__device__ __forceinline__ void keep_best(float (&v)[KL], int (&cl)[KL], float val, int c, bool real) {
+    float x = real ? fmaxf(val, -FLT_MAX) : -INFINITY;   // (the maximum drops a NaN)
     int xc = c;
 #pragma unroll
     for (int q = 0; q < KS; ++q) {
@@ -576,6 +576,17 @@ __global__ __launch_bounds__(64 * WAVES) void k_mlp(
                 }
         }
         const int ncb = OUTB == 1 ? 1 : (C + 31) / 32;
+        // Several blocks' fragments come from L2, the next tile's while this one's MFMAs run
+        // (524,288 headers, hidden 256, 387 classes: BF16 303 -> 262 us, FP8 232 -> 222; with a
+        // compare less per score and no padding test in whole blocks 245 and 180; 144 classes
+        // 174 -> 158 and 123 -> 105). Not where they cost a wave per SIMD: FP8, hidden 128 (387
+        // classes 124 us, 172 with).
+        constexpr bool AHEAD = OUTB > 1 && !(LDSM & 4) && PREC != TANG_FP32 && !(PREC == TANG_FP8 && H == 128);
+        F next[AHEAD ? KBNH : 1];
+        if constexpr (AHEAD) {
+#pragma unroll
+            for (int kb = 0; kb < KBNH; ++kb) next[kb] = ldf<false>(s3, r3, kb, lane, sbase, win);
+        }
 #pragma unroll 1
         for (int cb = 0; cb < ncb; ++cb) {
             if constexpr (OUTB > 1) {
@@ -583,19 +594,32 @@ __global__ __launch_bounds__(64 * WAVES) void k_mlp(
                 for (int mt = 0; mt < 2; ++mt) {
 #pragma unroll
                     for (int nt = 0; nt < NT; ++nt) z[mt][nt] = (f4){0, 0, 0, 0};
+                    const int t = 2 * cb + mt;
+                    if (16 * t >= C) continue;   // a tile of padding alone
+                    F cur[KBNH];
+                    if constexpr (AHEAD) {
+                        const int ahead = min(t + 1, 2 * ncb - 1) * KBNH;
+#pragma unroll
+                        for (int kb = 0; kb < KBNH; ++kb) {
+                            cur[kb] = next[kb];
+                            next[kb] = ldf<false>(s3, r3, ahead + kb, lane, sbase, win);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
 #pragma unroll
                     for (int kb = 0; kb < KBNH; ++kb) {
-                        const F A = ldf<(LDSM & 4) != 0>(s3, r3, (2 * cb + mt) * KBNH + kb, lane, sbase, win);
+                        if constexpr (!AHEAD) cur[kb] = ldf<false>(s3, r3, t * KBNH + kb, lane, sbase, win);
 #pragma unroll
-                        for (int nt = 0; nt < NT; ++nt) z[mt][nt] = mma(A, a1[kb][nt], z[mt][nt]);
+                        for (int nt = 0; nt < NT; ++nt) z[mt][nt] = mma(cur[kb], a1[kb][nt], z[mt][nt]);
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
             // scores; the running top-k keeps topk slots (1, 2, or 4 for 3 and 4; a uniform
-            // branch per block picks the count)
-            auto scores = [&](auto slots) {
+            // branch per block picks the count, another whether the block has padding)
+            auto scores = [&](auto slots, auto padding) {
                 constexpr int KS = decltype(slots)::value;
+                constexpr bool PAD = decltype(padding)::value;
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt) {
                     const uint32_t pkt = pbase + nt * 16 + col;
@@ -610,15 +634,24 @@ __global__ __launch_bounds__(64 * WAVES) void k_mlp(
                                 v[nt][4 * mt + r] = (c < C && val == val) ? val : -INFINITY;
                                 cl[nt][4 * mt + r] = c;
                             } else {
-                                keep_best<KS>(v[nt], cl[nt], val, c, C);
+                                keep_best<KS>(v[nt], cl[nt], val, c, !PAD || c < C);
                             }
                         }
                     }
                 }
             };
-            if (OUTB > 1 && a.topk == 1) scores(std::integral_constant<int, 1>{});
-            else if (OUTB > 1 && a.topk == 2) scores(std::integral_constant<int, 2>{});
-            else scores(std::integral_constant<int, KL>{});
+            using Yes = std::true_type;
+            using No = std::false_type;
+            if constexpr (OUTB == 1) {
+                scores(std::integral_constant<int, KL>{}, Yes{});
+            } else if (a.topk == 1) {
+                if (32 * cb + 32 <= C) scores(std::integral_constant<int, 1>{}, No{});
+                else scores(std::integral_constant<int, 1>{}, Yes{});
+            } else if (a.topk == 2) {
+                scores(std::integral_constant<int, 2>{}, Yes{});
+            } else {
+                scores(std::integral_constant<int, KL>{}, Yes{});
+            }
         }
         // top-k with ties to the lower tuple index
 #pragma unroll
@@ -876,7 +909,7 @@ __global__ __launch_bounds__(512, OCC) void k_mlp_split(
                         const int c = 16 * ct + 4 * (int)g + q;
                         const float val = (big[nt][q] + small[nt][q]) + b3[q];
                         if (logits && pkt < n && c < C) logits[(size_t)pkt * C + c] = val;
-                        keep_best<KS>(v[nt], cl[nt], val, c, C);
+                        keep_best<KS>(v[nt], cl[nt], val, c, c < C);
                     }
                 }
             }
@@ -1062,7 +1095,7 @@ __global__ __launch_bounds__(512) void k_mlp_small(
                         const int c = 16 * ct + 4 * (int)g + q;
                         const float val = (PREC == TANG_FP8 ? z[q] * a.deq[2] : z[q]) + b3[q];
                         if (logits && pkt < n && c < C) logits[(size_t)pkt * C + c] = val;
-                        keep_best<KS ? KS : 1>(v[nt], cl[nt], val, c, C);
+                        keep_best<KS ? KS : 1>(v[nt], cl[nt], val, c, c < C);
                     }
                 }
             }
@@ -1423,7 +1456,7 @@ hipError_t launch_mlp(const tang_ruleset_t* rs, const tang_header_t* d_hdr, size
         const bool wide = m.n_out > kOutPad;
         // BF16 and FP8, small batches: tiles of 16 headers up to 4,096 (one per CU), of 64 up to
         // 16,384 (one per CU; BF16 hidden 128 10,000 headers 6.5 us, k_mlp 8.6; FP8 387 classes
-        // 12 and 25), with hidden 256 and at most 32 classes twice that (BF16 32,768 headers
+        // 11 and 21), with hidden 256 and at most 32 classes twice that (BF16 32,768 headers
         // 17.0 and 19.1; 65,536 31.8 and 20.4). Not for BF16 hidden 256 with more classes:
         // its weights and a class tile leave no registers (10,000 headers 29 and 24).
         const uint32_t small_to = m.hidden == 256 && !wide                       ? 32768u

@@ -45,3 +45,34 @@ def test_small_form_equals_large_form_bit_for_bit(prec, hidden, space, topk):
             assert np.array_equal(sc_, cand[at]), n
     finally:
         T.tang_ruleset_destroy(rs)
+
+
+@pytest.mark.parametrize("C", [33, 48, 49, 64, 65])
+@pytest.mark.parametrize("hidden", [128, 256])
+@pytest.mark.parametrize("prec", ["bf16", "fp8"])
+def test_class_tile_edges(prec, hidden, C):
+    """Class counts at the edges of the 16-class tiles and 32-class blocks, large form: the
+    candidates are the best of the scores, ties to the lower class, and the scores are within
+    the type's rounding of the oracle's (the median header within 2^-8, as above)."""
+    torch_cuda()
+    rules = synth.make_rules(6000, seed=113, all_lengths=True)
+    pair = 33 * rules["sip_len"].astype(np.int64) + rules["dip_len"]
+    rules = rules[np.isin(pair, np.unique(pair)[:C])]
+    rs = T.tang_ruleset_create(0, rules)
+    try:
+        assert T.tang_ruleset_num_tuples(rs) == C
+        Ws, bs = train.random_weights(C, hidden, seed=6)
+        Ws[2][C - 1] = Ws[2][C - 2]     # the last two classes tie, and beat most others
+        bs[2][C - 1] = bs[2][C - 2] = np.abs(bs[2]).max()
+        hdr = synth.make_packets(rules, 83, seed=114, frac_in=0.7)
+        sc = train.act_scales(Ws, bs, train.feature_bits_torch(hdr)) if prec == "fp8" else None
+        want = orc.mlp_forward(orc.feature_bits(hdr), Ws, bs, prec, act_scales=sc)
+        for topk in (1, 2, 4):
+            T.tang_model_load(rs, Ws, bs, prec, topk=topk, act_scales=sc)
+            logits, cand = mlp_dev(rs, hdr[np.arange(LARGE) % len(hdr)], C, topk=topk)
+            best = np.argsort(-logits[:83], axis=1, kind="stable")[:, :topk]
+            assert np.array_equal(cand[:83].reshape(83, topk), best), topk
+            assert np.array_equal(cand, cand[np.arange(LARGE) % len(hdr)])
+            assert np.median(np.abs(logits[:83] - want).max(axis=1) / np.abs(want).max(axis=1)) < 2.0 ** -8
+    finally:
+        T.tang_ruleset_destroy(rs)
