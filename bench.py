@@ -730,8 +730,8 @@ def paper_loop_small(args):
 def bench_resnet(args, rs, d_hdr, d_out, want, C):
     """The paper's own predictor size (7 chunks -> 512 -> 6 residual blocks -> C, BF16,
     random weights: speed only) on the first 4,194,304 headers of the 512k workload: the
-    predictor alone (tang_predict, HIP events) and whole classification (chunked, two
-    streams); the answers must equal the BF16 run's."""
+    predictor alone (tang_predict, HIP events) and whole classification; the answers must
+    equal the BF16 run's."""
     import numpy as np
     import torch
 
