@@ -183,8 +183,8 @@ template <> struct Bits<TANG_FP8> {
 };
 
 // One lane's A fragment `frag` of a layer: from LDS, or from global memory through a
-// buffer descriptor (lane offset in one VGPR, fragment offset as a scalar; reads past the
-// layer's size return zero instead of faulting). A fragment is stored as 64 consecutive
+// buffer descriptor (lane offset in one VGPR, fragment offset as a scalar, always inside the
+// layer: the bounds check does not cover it). A fragment is stored as 64 consecutive
 // lane slots of at most 16 bytes; the 32-byte FP8 fragment as two such planes (bytes
 // 0-15 of every lane, then bytes 16-31), so that 128-bit LDS reads stay free of bank
 // conflicts.
@@ -795,9 +795,10 @@ __global__ __launch_bounds__(512, OCC) void k_mlp_split(
         };
         u32x4 O[2][3];   // KS: the output layer's fragments, two K blocks ahead
         auto load_o = [&](int buf, int ct, int kb) {
+            const uint32_t t = class_tile((uint32_t)ct, (uint32_t)C);
 #pragma unroll
             for (int pl = 0; pl < 3; ++pl)
-                O[buf][pl] = __builtin_amdgcn_raw_buffer_load_b128(r3, lane * 16u, (((uint32_t)ct * KBH + kb) * 3u + pl) * 1024u, 0);
+                O[buf][pl] = __builtin_amdgcn_raw_buffer_load_b128(r3, lane * 16u, ((t * KBH + kb) * 3u + pl) * 1024u, 0);
         };
         {   // hidden layer
             f4 big[MT][NTW], small[MT][NTW];
@@ -891,7 +892,7 @@ __global__ __launch_bounds__(512, OCC) void k_mlp_split(
 #pragma unroll
                     for (int pl = 0; pl < 3; ++pl) a[pl] = O[kb & 1][pl];
                     if (kb + 2 < KBH) load_o(kb & 1, ct, kb + 2);
-                    else load_o(kb & 1, ct + 8, kb + 2 - KBH);   // past the last tile: zeros
+                    else load_o(kb & 1, ct + 8, kb + 2 - KBH);   // past the last tile: not used
 #pragma unroll
                     for (int nt = 0; nt < NT; ++nt) {
                         u32x4 b[3];
@@ -966,7 +967,7 @@ __global__ __launch_bounds__(512) void k_mlp_small(
         for (int kb = 0; kb < KB1; ++kb) A1[u][kb] = frag(r1, (wave * MT + u) * KB1 + kb);
     auto load3 = [&](int u, int ct) {   // class tile ct
 #pragma unroll
-        for (int kb = 0; kb < KBH; ++kb) A3[u][kb] = frag(r3, (uint32_t)ct * KBH + kb);
+        for (int kb = 0; kb < KBH; ++kb) A3[u][kb] = frag(r3, class_tile((uint32_t)ct, (uint32_t)C) * KBH + kb);
     };
     // rows of a hidden layer to the next one's B fragments: a lane's four rows are its own
     // elements of that fragment
@@ -1081,13 +1082,14 @@ __global__ __launch_bounds__(512) void k_mlp_small(
 #pragma unroll 1
             for (int ct = (int)wave; ct < (C + 15) / 16; ct += 8) {
                 const f4 b3 = *reinterpret_cast<const f4*>(sb3 + 16 * ct + 4 * g);
+                const uint32_t ahead = class_tile((uint32_t)ct + 8u, (uint32_t)C);   // past the last tile: not used
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt) {
                     f4 z = (f4){0, 0, 0, 0};
 #pragma unroll
                     for (int kb = 0; kb < KBH; ++kb) {
                         z = mma(A3[0][kb], act[1][(kb * NT + nt) * 64 + lane], z);
-                        if (nt == NT - 1) A3[0][kb] = frag(r3, (uint32_t)(ct + 8) * KBH + kb);   // past the end: zeros
+                        if (nt == NT - 1) A3[0][kb] = frag(r3, ahead * KBH + kb);
                     }
                     const uint32_t pkt = p0 + 16u * nt + r;
 #pragma unroll

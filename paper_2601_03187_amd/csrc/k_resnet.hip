@@ -102,19 +102,21 @@ __global__ __launch_bounds__(512) void k_res(const uint4* __restrict__ hdr, uint
     const uint32_t tiles = (n + TH - 1) / TH;
     for (uint32_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
         const uint32_t p0 = tile * TH;
-        // A fragments of K block kb of layer l (2 nb layers of 512 KB, 64 KB per wave)
+        // A fragments of K block kb of layer l (2 nb layers of 512 KB, 64 KB per wave); past
+        // the last layer that one's again, not used
         u32x4 A[3][4];
         auto load_a = [&](int buf, int l, int kb) {
-            const uint32_t at = ((uint32_t)l * 8u + wave) * 65536u + (uint32_t)kb * 4096u;
+            const uint32_t at = res_weight_at((uint32_t)l, wave, (uint32_t)kb, (uint32_t)nb);
 #pragma unroll
             for (int mt = 0; mt < 4; ++mt)
                 A[buf][mt] = __builtin_amdgcn_raw_buffer_load_b128(rw, lane * 16u, at + mt * 1024u, 0);
         };
         load_a(0, 0, 0);
         load_a(1, 0, 1);
-        // bias of layer l for neuron tid (zero past the last: the output layer reads its own)
+        // bias of layer l for neuron tid (past the last not used: the output layer reads its own)
         auto next_bias = [&](int l) {
-            return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rb, tid * 4u, (uint32_t)(1 + l) * (kW * 4u), 0));
+            return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                                 rb, tid * 4u, res_bias_row((uint32_t)l, (uint32_t)nb) * (kW * 4u), 0));
         };
         sbias[tid] = next_bias(0);
         // Input layer: a lane is a header, a wave 64 neurons, so weights are scalars.

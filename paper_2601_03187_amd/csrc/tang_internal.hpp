@@ -257,6 +257,23 @@ constexpr int kMaxHidden = 256;
 constexpr int kOutPad = 32;   // output classes padded to 2 MFMA tiles
 constexpr int kInPad = 128;   // 104 input bits padded to 128
 
+// Weights are loaded ahead of their use, also where a layer or a wave's class tiles have
+// ended and nothing follows: such a load takes the last stored piece again. It must not run
+// past the end: the scalar offset of a buffer load is not part of its bounds check.
+__host__ __device__ constexpr uint32_t stored(uint32_t want, uint32_t count) {
+    return want < count ? want : count - 1u;
+}
+// Plain networks: the 16-class tile of the output layer (stored in pairs) for class tile ct.
+__host__ __device__ constexpr uint32_t class_tile(uint32_t ct, uint32_t classes) {
+    return stored(ct, 2u * ((classes + 31u) / 32u));
+}
+// Residual network of nb blocks: the byte offset of wave `wave`'s K block kb (4 KB) of block
+// layer l, and the bias row (512 floats) of that layer.
+__host__ __device__ constexpr uint32_t res_weight_at(uint32_t l, uint32_t wave, uint32_t kb, uint32_t nb) {
+    return (stored(l, 2u * nb) * 8u + wave) * 65536u + kb * 4096u;
+}
+__host__ __device__ constexpr uint32_t res_bias_row(uint32_t l, uint32_t nb) { return 1u + stored(l, 2u * nb); }
+
 struct ModelDev {
     int loaded = 0;
     int kind = 0;     // 0: the plain 104 -> H -> H -> C network; 1: the residual network
