@@ -1158,20 +1158,48 @@ void planes(float w, uint16_t (&q)[3]) {
     }
 }
 
-// Whether every value the FP32 network can meet stays far from BF16's range limits, where
-// the planes would overflow or vanish: finite weights, bounded hidden outputs.
+// Whether the FP32 network stays far enough from the limits of BF16's range for its planes:
+//  - above: finite weights and outputs of at most 1e30;
+//  - below: planes and plane products under 2^-126 may vanish. A term w x of a row then misses
+//    at most 2^-125 (|x| + |w|) + 2^-123 (two planes of either factor, six products). That is
+//    nothing beside the rounding of FP32 sums if either no term that occurs can be small (the
+//    smallest non-zero magnitudes of every layer, multiplied up, stay above 2^-90), or what
+//    the scores can miss in all is below 2^-28 of the magnitude that the biases alone give them.
 bool can_split(const tang_mlp_desc_t* d, const float* const* W, const float* const* b) {
-    double in = 1.0;   // largest input of the layer
+    double in = 1.0, least = 1.0;   // largest input of the layer, smallest magnitude of one
+    bool above = true;
+    std::vector<double> miss(d->dims[0], 0.0), sure(d->dims[0], 0.0);   // of the inputs
     for (int l = 0; l < 3; ++l) {
-        double most = 0.0;
-        for (uint32_t o = 0; o < d->dims[l + 1]; ++o) {
-            double sum = std::fabs((double)b[l][o]);
-            for (uint32_t i = 0; i < d->dims[l]; ++i) sum += in * std::fabs((double)W[l][(size_t)o * d->dims[l] + i]);
+        const uint32_t n_in = d->dims[l], n_out = d->dims[l + 1];
+        double most = 0.0, w_least = 1e300, b_least = 1e300;
+        std::vector<double> miss_out(n_out), sure_out(n_out);
+        for (uint32_t o = 0; o < n_out; ++o) {
+            const double bias = std::fabs((double)b[l][o]);
+            double sum = bias, lost = 0.0, base = bias;
+            for (uint32_t i = 0; i < n_in; ++i) {
+                const double w = std::fabs((double)W[l][(size_t)o * n_in + i]);
+                sum += in * w;
+                if (w == 0.0) continue;
+                w_least = std::min(w_least, w);
+                lost += w * miss[i] + std::ldexp(in + w, -125) + std::ldexp(1.0, -123);
+                base += w * sure[i];
+            }
             if (!(sum < 1e30)) return false;   // NaN and infinities too
             most = std::max(most, sum);
+            if (bias != 0.0) b_least = std::min(b_least, bias);
+            miss_out[o] = lost;
+            sure_out[o] = base;
         }
         in = most;
+        above &= w_least >= 0x1p-90;
+        least = std::min(least * w_least, b_least);
+        above &= least >= 0x1p-90;
+        miss.swap(miss_out);
+        sure.swap(sure_out);
     }
+    if (above) return true;
+    for (size_t c = 0; c < miss.size(); ++c)
+        if (!(miss[c] <= std::ldexp(sure[c], -28))) return false;
     return true;
 }
 

@@ -77,3 +77,35 @@ def test_weights_out_of_the_planes_range(hidden):
         assert not np.isfinite(logits[:, 3]).all() and (cand < C).all()
     finally:
         T.tang_ruleset_destroy(rs)
+
+
+@pytest.mark.parametrize("layer", [1, 2])
+@pytest.mark.parametrize("hidden", [128, 256])
+def test_weights_below_the_planes_range(hidden, layer):
+    """A hidden layer scaled by 2^-116 and the next by 2^116: ordinary scores from values
+    whose planes would vanish. The error over the scores stays that of FP32 sums: a random
+    walk of K roundings, 4 sqrt(K) u at most (two planes alone would give 2^-17)."""
+    torch_cuda()
+    rules, rs, C, _, _ = _setup("narrow", hidden, 11)
+    try:
+        rng = np.random.default_rng(12)
+        dims = [104, hidden, hidden, C]
+        Ws = [(rng.uniform(0.5, 1.0, (o, i)) * rng.choice([-1, 1], (o, i)) / np.sqrt(i)).astype(np.float32)
+              for i, o in zip(dims, dims[1:])]
+        bs = [np.full(o, v, np.float32) for o, v in zip(dims[1:], (4.0, 4.0, 0.5))]   # few inputs near zero
+        small, large = np.float32(2.0 ** -116), np.float32(2.0 ** 116)
+        if layer == 1:      # the hidden layer's weights and outputs
+            Ws[1], bs[1], Ws[2] = Ws[1] * small, bs[1] * small, Ws[2] * large
+        else:               # the output layer's weights alone, its scores 2^-116 of the ordinary
+            Ws[2], bs[2] = Ws[2] * small, bs[2] * small
+        hdr = synth.make_packets(rules, 500, seed=104, frac_in=0.7)
+        T.tang_model_load(rs, Ws, bs, "fp32")
+        logits, _ = mlp_dev(rs, hdr, C)
+        a = orc.feature_bits(hdr).astype(np.float64)
+        for k in range(3):
+            a = a @ Ws[k].astype(np.float64).T + bs[k]
+            a = np.maximum(a, 0) if k < 2 else a
+        err = np.linalg.norm(logits - a) / np.linalg.norm(a)
+        assert err <= 4 * np.sqrt(104 + 2 * hidden) * U, err
+    finally:
+        T.tang_ruleset_destroy(rs)
