@@ -90,7 +90,8 @@ __device__ __forceinline__ uint64_t key64(uint32_t prio, uint32_t id) { return (
 // scalar loads, and a compare gathers the bits in which the two rules keep apart: prefix bits
 // that both fix, the protocol if both fix it, and port bounds the wrong way round, both ports
 // in one packed maximum. Bound by issue over the pairs (524,288 rules, 100 fresh: 71 us; 85
-// with a compare per bound and the boxes in LDS).
+// with a compare per bound and the boxes in LDS). Waves of dead records alone (vacated places,
+// after large deletes most of the array) compare nothing.
 template <int NW>
 __global__ __launch_bounds__(256) void k_conflict_update(Rec* __restrict__ recs,
                                                          uint32_t* __restrict__ cmask, uint32_t used,
@@ -103,6 +104,8 @@ __global__ __launch_bounds__(256) void k_conflict_update(Rec* __restrict__ recs,
     Rec me = Rec{0u, 0u, kDead, 0u, 0u, 0u, kDead, 0u};
     if (p < used) me = recs[p];
     const bool live = !(me.prio == kDead && me.id == kDead);
+    if (!__syncthreads_or(live)) return;
+    const bool wave_live = __ballot(live) != 0ull;
     const uint32_t sm = pmask(meta_sl(me.meta)), dm = pmask(meta_dl(me.meta));
     const uint32_t lo = (me.sp & 0xFFFFu) | (me.dp << 16), hi = (me.sp >> 16) | (me.dp & 0xFFFF0000u);
     const uint32_t proto = meta_proto(me.meta), pm = meta_exact(me.meta) ? 0xFFu : 0u;
@@ -117,7 +120,7 @@ __global__ __launch_bounds__(256) void k_conflict_update(Rec* __restrict__ recs,
         for (int w = 0; w < NW; ++w) qadd[threadIdx.x][w] = 0;
         __syncthreads();
 #pragma unroll 4
-        for (uint32_t k = 0; k < cnt; ++k) {
+        for (uint32_t k = 0; k < (wave_live ? cnt : 0u); ++k) {
             const FreshDev q = fresh[q0 + k];
             uint32_t apart = (me.sip ^ q.sip) & sm & q.sm;
             apart |= (me.dip ^ q.dip) & dm & q.dm;
