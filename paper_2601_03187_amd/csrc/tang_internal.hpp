@@ -362,6 +362,8 @@ struct tang_ruleset_s {
     std::vector<tang::Slot> slots;                 // host mirror of the slot table
     std::vector<tang::SplitInfo> split_info;       // summaries of the split buckets' sub-lists
     uint32_t filter_blocks = 0;                    // size of the bucket filter (device only)
+    std::vector<uint32_t> touched_in;              // last batch that touched a bucket, and the
+    uint32_t batch = 0;                            // number of the present one
     uint32_t rec_used = 0, rec_cap = 0;
     uint32_t nw = 1;   // conflict-mask words per rule (fixed at build: words_for(tuples))
 

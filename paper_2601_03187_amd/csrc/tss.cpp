@@ -2,7 +2,6 @@
 // deletion (Sec. 5.2.1), and the device deltas they produce.
 #include <algorithm>
 #include <numeric>
-#include <unordered_set>
 
 #include "tang_internal.hpp"
 
@@ -289,6 +288,7 @@ int build_host(tang_ruleset_t* rs, const tang_rule_t* rules, size_t n) {
     rs->rec_used = off;
     rs->rec_cap = off + std::max<uint32_t>(65536u, off / 4);
     rebuild_slots(rs);
+    rs->touched_in.assign(rs->buckets.size(), 0u);
     return TANG_OK;
 }
 
@@ -649,6 +649,21 @@ int flush_or_fail(tang_ruleset_t* rs, const std::vector<uint32_t>& dirty,
     return TANG_OK;
 }
 
+// The buckets that a batch of an update touches, each once: a bucket carries the number of
+// the last batch that did (a set of them takes twice the time of a whole large batch).
+void begin_batch(tang_ruleset_t* rs) {
+    if (++rs->batch == 0) {
+        std::fill(rs->touched_in.begin(), rs->touched_in.end(), 0u);
+        rs->batch = 1;
+    }
+}
+bool first_touch(tang_ruleset_t* rs, uint32_t b) {
+    if (b >= rs->touched_in.size()) rs->touched_in.resize(rs->buckets.size() + rs->buckets.size() / 2, 0u);
+    if (rs->touched_in[b] == rs->batch) return false;
+    rs->touched_in[b] = rs->batch;
+    return true;
+}
+
 }  // namespace
 
 int apply_insert(tang_ruleset_t* rs, const tang_rule_t* rules, size_t n) {
@@ -690,7 +705,7 @@ int apply_insert(tang_ruleset_t* rs, const tang_rule_t* rules, size_t n) {
                                          std::to_string(kMaxBucketLen) + " rules");
     }
     std::vector<uint32_t> dirty, fresh;
-    std::unordered_set<uint32_t> mark;
+    begin_batch(rs);
     size_t nb_before = rs->buckets.size();
     for (size_t i = 0; i < n; ++i) {
         tang_rule_t r = normalise(rules[i]);
@@ -719,7 +734,7 @@ int apply_insert(tang_ruleset_t* rs, const tang_rule_t* rules, size_t n) {
         std::vector<uint32_t> changed{b};
         if (b == mb && mem.size() > kSplitAt) changed = split_bucket(rs, mb);
         for (uint32_t c : changed)
-            if (mark.insert(c).second) dirty.push_back(c);
+            if (first_touch(rs, c)) dirty.push_back(c);
         fresh.push_back(h);
     }
     // new buckets need slots; grow the table when it would pass half full
@@ -749,7 +764,7 @@ int apply_delete(tang_ruleset_t* rs, const uint32_t* ids, size_t n) {
             return fail(TANG_ENOTFOUND, "rule id " + std::to_string(ids[i]) + " is not live");
     }
     std::vector<uint32_t> dirty;
-    std::unordered_set<uint32_t> mark;
+    begin_batch(rs);
     for (size_t i = 0; i < n; ++i) {
         uint32_t h = rs->id2h[ids[i]];
         auto& hr = rs->rules[h];
@@ -759,7 +774,7 @@ int apply_delete(tang_ruleset_t* rs, const uint32_t* ids, size_t n) {
         rs->id2h.erase(ids[i]);
         rs->n_live--;
         if (rs->sigs[hr.tuple] != std::make_pair(hr.r.sip_len, hr.r.dip_len)) rs->n_coarse--;
-        if (mark.insert(hr.bucket).second) dirty.push_back(hr.bucket);
+        if (first_touch(rs, hr.bucket)) dirty.push_back(hr.bucket);
     }
     return flush_or_fail(rs, dirty, {}, false);
 }
