@@ -133,7 +133,7 @@ static void free_device(tang_ruleset_t* rs) {
     if (rs->upd_host) (void)hipHostFree(rs->upd_host);
     if (rs->upd_dev) (void)dev_release(rs->upd_dev);
     rs->upd_host = rs->upd_dev = nullptr;
-    rs->upd_host_cap = rs->upd_dev_cap = 0;
+    rs->upd_dev_cap = 0;
     if (rs->d_back) (void)dev_release(rs->d_back);
     rs->d_back = nullptr;
     if (rs->d_filter) (void)dev_release(rs->d_filter);

@@ -254,6 +254,10 @@ struct StatsDev {
 };
 constexpr int kStatCopies = 64;
 
+// Updates' staging (see tang_ruleset_s): 1,000 rules take 300 KB of the pinned part.
+constexpr size_t kUpdHost = (size_t)1 << 20;
+constexpr size_t kUpdDevMin = (size_t)2 << 20, kUpdDevKeep = (size_t)16 << 20;
+
 // Rule box used by the conflict-mask kernels (key order), 32 B.
 struct alignas(16) BoxDev {
     uint32_t slo, shi, dlo, dhi, sp, dp, pt, pos;  // pt = proto | exact << 8 | tuple << 16
@@ -376,12 +380,13 @@ struct tang_ruleset_s {
     tang::TupleTable* d_tt = nullptr;
     tang::StatsDev* d_stats = nullptr;
     hipStream_t upd_stream = nullptr;
-    // Updates' staging, kept up to 16 MB each and released with the ruleset: pinned host memory
-    // that a batch is packed into, and the device block it is copied to (with scratch behind
-    // it). One update runs at a time and ends synchronised, so both are free again.
+    // Updates' staging, released with the ruleset: pinned host memory (kUpdHost) that a batch
+    // is packed into, and the device block that it is copied to (with scratch behind it; kept
+    // up to kUpdDevKeep). One update runs at a time and ends synchronised, so both are free
+    // again.
     void* upd_host = nullptr;
     void* upd_dev = nullptr;
-    size_t upd_host_cap = 0, upd_dev_cap = 0;
+    size_t upd_dev_cap = 0;
     tang::ModelDev model;
     std::mutex stats_mu;
     uint64_t version = 0;   // bumped by every change that captured launches depend on

@@ -288,7 +288,7 @@ int build_host(tang_ruleset_t* rs, const tang_rule_t* rules, size_t n) {
     rs->rec_used = off;
     rs->rec_cap = off + std::max<uint32_t>(65536u, off / 4);
     rebuild_slots(rs);
-    rs->touched_in.assign(rs->buckets.size(), 0u);
+    rs->touched_in.assign(rs->buckets.size() + rs->buckets.size() / 4 + 1024, 0u);
     return TANG_OK;
 }
 
@@ -327,25 +327,15 @@ static hipError_t upload_slots(const tang_ruleset_t* rs, SlotDev* d_slots, uint3
     return e;
 }
 
-// Makes room for a batch of an update; the least serves ordinary ones (100 rules take 30 KB).
-static hipError_t grow_staging(tang_ruleset_t* rs, size_t host_bytes, size_t dev_bytes) {
-    hipError_t e = hipSuccess;
-    if (host_bytes > rs->upd_host_cap) {
-        if (rs->upd_host) e = hipHostFree(rs->upd_host);
-        rs->upd_host = nullptr;
-        rs->upd_host_cap = 0;
-        const size_t cap = std::max<size_t>(host_bytes + host_bytes / 2, 1u << 18);
-        if (e == hipSuccess) e = hipHostMalloc(&rs->upd_host, cap, hipHostMallocDefault);
-        if (e == hipSuccess) rs->upd_host_cap = cap;
-    }
-    if (e == hipSuccess && dev_bytes > rs->upd_dev_cap) {
-        if (rs->upd_dev) e = dev_release(rs->upd_dev);
-        rs->upd_dev = nullptr;
-        rs->upd_dev_cap = 0;
-        const size_t cap = std::max<size_t>(dev_bytes + dev_bytes / 2, 1u << 18);
-        if (e == hipSuccess) e = dev_alloc(&rs->upd_dev, cap);
-        if (e == hipSuccess) rs->upd_dev_cap = cap;
-    }
+// Makes room for a batch of an update in the device block.
+static hipError_t grow_block(tang_ruleset_t* rs, size_t bytes) {
+    if (bytes <= rs->upd_dev_cap) return hipSuccess;
+    hipError_t e = dev_release(rs->upd_dev);
+    rs->upd_dev = nullptr;
+    rs->upd_dev_cap = 0;
+    const size_t cap = std::max<size_t>(bytes + bytes / 2, kUpdDevMin);
+    if (e == hipSuccess) e = dev_alloc(&rs->upd_dev, cap);
+    if (e == hipSuccess) rs->upd_dev_cap = cap;
     return e;
 }
 
@@ -365,7 +355,9 @@ int upload_all(tang_ruleset_t* rs) {
     }
     TANG_HIP(dev_alloc(&rs->d_tt, sizeof(TupleTable)));
     TANG_HIP(dev_alloc(&rs->d_stats, kStatCopies * sizeof(StatsDev)));
-    TANG_HIP(grow_staging(rs, 1, 1));   // here rather than in the first update
+    // here rather than in the first update
+    TANG_HIP(hipHostMalloc(&rs->upd_host, kUpdHost, hipHostMallocDefault));
+    TANG_HIP(grow_block(rs, 1));
 
     std::vector<Rec> recs(rs->rec_cap, dead_rec());
     for (uint32_t h = 0; h < rs->rules.size(); ++h)
@@ -412,7 +404,7 @@ int upload_all(tang_ruleset_t* rs) {
 
 namespace {
 
-// Arrays laid out one after another (16-byte aligned) in a staging block.
+// Arrays laid out one after another (16-byte aligned) in the device block.
 struct Packer {
     struct Part {
         const void* p;
@@ -430,27 +422,27 @@ struct Packer {
     size_t add(const std::vector<T>& v) {
         return add(v.data(), v.size() * sizeof(T));
     }
-    void write(void* to) const {
+    // To `dev`, through the pinned staging in one copy where they fit; a large batch goes
+    // straight from its arrays (new pinned memory costs the host 0.4 ms a MB in page faults).
+    hipError_t copy(char* dev, char* pinned, hipStream_t s) const {
+        if (size <= kUpdHost) {
+            for (const Part& x : parts)
+                if (x.bytes) std::memcpy(pinned + x.at, x.p, x.bytes);
+            return size ? hipMemcpyAsync(dev, pinned, size, hipMemcpyHostToDevice, s) : hipSuccess;
+        }
+        hipError_t e = hipSuccess;
         for (const Part& x : parts)
-            if (x.bytes) std::memcpy(static_cast<char*>(to) + x.at, x.p, x.bytes);
+            if (e == hipSuccess && x.bytes) e = hipMemcpyAsync(dev + x.at, x.p, x.bytes, hipMemcpyHostToDevice, s);
+        return e;
     }
 };
 
-// Staging that a batch larger than the ordinary left behind is given back.
-hipError_t trim_staging(tang_ruleset_t* rs) {
-    constexpr size_t kKeep = 16u << 20;
-    hipError_t e = hipSuccess;
-    if (rs->upd_host_cap > kKeep) {
-        e = hipHostFree(rs->upd_host);
-        rs->upd_host = nullptr;
-        rs->upd_host_cap = 0;
-    }
-    if (rs->upd_dev_cap > kKeep) {
-        const hipError_t e2 = dev_release(rs->upd_dev);
-        if (e == hipSuccess) e = e2;
-        rs->upd_dev = nullptr;
-        rs->upd_dev_cap = 0;
-    }
+// A block that a batch larger than the ordinary left behind is given back.
+hipError_t trim_block(tang_ruleset_t* rs) {
+    if (rs->upd_dev_cap <= kUpdDevKeep) return hipSuccess;
+    const hipError_t e = dev_release(rs->upd_dev);
+    rs->upd_dev = nullptr;
+    rs->upd_dev_cap = 0;
     return e;
 }
 
@@ -572,24 +564,24 @@ int flush(tang_ruleset_t* rs, const std::vector<uint32_t>& dirty, const std::vec
     }
     const TupleTable tt = make_tuple_table(rs);
 
-    // The batch packed into the staging block, one copy; device-only scratch behind it.
+    // The batch in the device block, with scratch behind it; the tuple table has a place of
+    // its own, and goes through the end of the staging if there is room.
     Packer pk;
     const size_t o_src = pk.add(src), o_dst = pk.add(dst), o_new = pk.add(newrecs), o_fresh = pk.add(fdev),
                  o_idx = pk.add(touched_slots), o_val = pk.add(vals), o_sidx = pk.add(split_slots),
                  o_info = pk.add(split_info);
-    const size_t packed = pk.size, o_tt = pk.add(&tt, tuple_table_bytes(tt)), host_bytes = pk.size;
-    const size_t o_stage = (packed + 255) & ~(size_t)255, o_mstage = o_stage + dst.size() * sizeof(Rec);
-    const size_t dev_bytes = o_mstage + (rs->nw > 1 ? dst.size() * rs->nw * sizeof(uint32_t) : 0);
-    hipError_t e = grow_staging(rs, host_bytes, dev_bytes);
+    const size_t o_stage = (pk.size + 255) & ~(size_t)255, o_mstage = o_stage + dst.size() * sizeof(Rec);
+    hipError_t e = grow_block(rs, o_mstage + (rs->nw > 1 ? dst.size() * rs->nw * sizeof(uint32_t) : 0));
     char* const d = static_cast<char*>(rs->upd_dev);
     auto at = [&](size_t off) { return reinterpret_cast<uint32_t*>(d + off); };
+    const size_t tt_bytes = tuple_table_bytes(tt);
+    const void* tt_from = &tt;
     if (e == hipSuccess) {
-        pk.write(rs->upd_host);
-        if (packed) e = hipMemcpyAsync(d, rs->upd_host, packed, hipMemcpyHostToDevice, s);
+        char* const pinned = static_cast<char*>(rs->upd_host);
+        e = pk.copy(d, pinned, s);
+        if (pk.size + tt_bytes <= kUpdHost) tt_from = std::memcpy(pinned + pk.size, &tt, tt_bytes);
     }
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(rs->d_tt, static_cast<char*>(rs->upd_host) + o_tt, tuple_table_bytes(tt),
-                           hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(rs->d_tt, tt_from, tt_bytes, hipMemcpyHostToDevice, s);
     if (e == hipSuccess)
         e = launch_move_records(rs->d_recs, (const Rec*)(d + o_new), at(o_src), at(o_dst), (uint32_t)dst.size(),
                                 (Rec*)(d + o_stage), rs->d_back, s);
@@ -628,7 +620,7 @@ int flush(tang_ruleset_t* rs, const std::vector<uint32_t>& dirty, const std::vec
                                   (uint32_t)split_slots.size(), s);
     }
     hipError_t e2 = hipStreamSynchronize(s);
-    if (e2 == hipSuccess) e2 = trim_staging(rs);
+    if (e2 == hipSuccess) e2 = trim_block(rs);
     if (e != hipSuccess) return hip_fail(e, "update flush");
     if (e2 != hipSuccess) return hip_fail(e2, "update flush sync");
     return TANG_OK;

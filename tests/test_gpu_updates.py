@@ -167,3 +167,30 @@ def test_inserted_masks_equal_bruteforce(space, n_new):
             assert T.tang_ruleset_conflict_mask(rs, int(rules[k]["id"])) == int(want[k]), (k, k >= 900)
     finally:
         T.tang_ruleset_destroy(rs)
+
+
+@pytest.mark.parametrize("wide", [False, True])
+def test_batches_on_both_sides_of_the_staging(wide):
+    """Batches that fit the pinned staging, that go straight from their arrays, and that
+    leave a device block too large to keep, with small ones in between: answers equal the
+    oracle's after each insert and each delete."""
+    torch_cuda()
+    rules = synth.make_rules(2000, seed=407, wide=wide)
+    rs = T.tang_ruleset_create(0, rules)
+    every, live = rules, np.ones(len(rules), bool)
+    rng = np.random.default_rng(8)
+    try:
+        for k, n in enumerate((5, 2_000, 3_500, 5_000, 70_000, 5, 4_000)):
+            ins = synth.make_rules(n, seed=408 + k, wide=wide)
+            ins["id"] = 100_000 * (k + 1) + np.arange(n)
+            ins["priority"] = rng.integers(0, 2000, n)
+            T.tang_insert(rs, ins)
+            every, live = np.concatenate([every, ins]), np.concatenate([live, np.ones(n, bool)])
+            hdr = synth.make_packets(every[live], 1500, seed=420 + k, frac_in=0.9)
+            assert np.array_equal(classify_dev(rs, hdr), orc.classify(every, hdr, live=live)), n
+            gone = ins["id"][: max(1, 3 * n // 4)]
+            T.tang_delete(rs, gone)
+            live &= ~np.isin(every["id"], gone)
+            assert np.array_equal(classify_dev(rs, hdr), orc.classify(every, hdr, live=live)), -n
+    finally:
+        T.tang_ruleset_destroy(rs)
