@@ -315,40 +315,62 @@ __device__ __forceinline__ void keep_best(float (&v)[KL], int (&cl)[KL], float v
 }
 
 // Where a header's classes are spread over 8 waves: each wave's top-k of its classes to LDS
-// ([wave][header][KS]), then one thread per header picks from the eight lists.
+// ([wave][header][KS]), then eight lanes per header pick from the eight lists, a lane holding
+// one. (One lane per header that read all of them for each pick took longer than the layers:
+// 65,536 headers, hidden 128, 144 classes, FP32, top-4 126 us and 70; 16,384, BF16, 29 and 15.)
+//
+// The best of the sorted lists (keep_best) in the lanes that differ from this one in the bits
+// from `first` to `last`, ties to the lower class; the lane that holds it drops it.
+template <int KS>
+__device__ __forceinline__ Scored pop_best(float (&v)[KS], int (&cl)[KS], int first, int last) {
+    float bv = v[0];
+    int bc = cl[0];
+#pragma unroll
+    for (int o = first; o <= last; o <<= 1) {
+        const float ov = __shfl_xor(bv, o, 64);
+        const int oc = __shfl_xor(bc, o, 64);
+        if (ov > bv || (ov == bv && oc < bc)) { bv = ov; bc = oc; }
+    }
+    const bool mine = bc == cl[0];   // a class is in one list
+#pragma unroll
+    for (int j = 0; j + 1 < KS; ++j) {
+        v[j] = mine ? v[j + 1] : v[j];
+        cl[j] = mine ? cl[j + 1] : cl[j];
+    }
+    v[KS - 1] = mine ? -INFINITY : v[KS - 1];
+    cl[KS - 1] = mine ? kNoClass : cl[KS - 1];
+    return {bv, bc};
+}
 template <int NT, int KS>
 __device__ __forceinline__ void put_tops(u32x2* tops, float (&v)[NT][KS], int (&cl)[NT][KS], uint32_t wave,
                                          uint32_t g, uint32_t r, int topk) {
+    for (int k = 0; k < topk; ++k)
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-        for (int k = 0; k < topk; ++k) {
-            const Scored b = take_best<KS>(v[nt], cl[nt]);
+        for (int nt = 0; nt < NT; ++nt) {
+            const Scored b = pop_best<KS>(v[nt], cl[nt], 16, 32);
             if (g == 0) tops[(wave * 16u * NT + 16u * nt + r) * KS + k] = (u32x2){__float_as_uint(b.first), (uint32_t)b.second};
         }
 }
 template <int KS>
-__device__ __forceinline__ void merge_tops(const u32x2* tops, uint32_t headers, uint32_t h, int topk, int C,
-                                           uint32_t pkt, uint32_t* cand, uint16_t* cand16) {
-    uint32_t packed = 0;
-    float lv = INFINITY;
-    int lc = -1;
-    for (int k = 0; k < topk; ++k) {
-        float bv = -INFINITY;
-        int bc = kNoClass;
-        for (uint32_t w = 0; w < 8u; ++w)
-            for (int j = 0; j < topk; ++j) {
-                const u32x2 t = tops[(w * headers + h) * KS + j];
-                const float tv = __uint_as_float(t[0]);
-                const int tc = (int)t[1];
-                const bool left = tv < lv || (tv == lv && tc > lc);   // not picked yet
-                if (left && (tv > bv || (tv == bv && tc < bc))) { bv = tv; bc = tc; }
-            }
-        lv = bv;
-        lc = bc;
-        packed |= (uint32_t)bc << (cand_bits(C) * k);
-        if (cand16) cand16[(size_t)pkt * topk + k] = (uint16_t)bc;
+__device__ __forceinline__ void merge_tops(const u32x2* tops, uint32_t headers, uint32_t tid, int topk, int C,
+                                           uint32_t p0, uint32_t n, uint32_t* cand, uint16_t* cand16) {
+    const uint32_t h = tid >> 3, w = tid & 7u;
+    if (h >= headers) return;   // uniform over a wave
+    float v[KS];
+    int cl[KS];
+#pragma unroll
+    for (int j = 0; j < KS; ++j) {
+        const u32x2 t = j < topk ? tops[(w * headers + h) * KS + j] : (u32x2){__float_as_uint(-INFINITY), (uint32_t)kNoClass};
+        v[j] = __uint_as_float(t[0]);
+        cl[j] = (int)t[1];
     }
-    if (cand) cand[pkt] = packed;
+    uint32_t packed = 0;
+    for (int k = 0; k < topk; ++k) {
+        const int bc = pop_best<KS>(v, cl, 1, 4).second;
+        packed |= (uint32_t)bc << (cand_bits(C) * k);
+        if (cand16 && w == 0 && p0 + h < n) cand16[(size_t)(p0 + h) * topk + k] = (uint16_t)bc;
+    }
+    if (cand && w == 0 && p0 + h < n) cand[p0 + h] = packed;
 }
 
 // OUTB: most blocks of 32 output classes (1, or 16 for up to 512 tuples; the W3 fragments
@@ -918,7 +940,7 @@ __global__ __launch_bounds__(512, OCC) void k_mlp_split(
             u32x2* const tops = act8;   // over the activations
             put_tops<NT, KS>(tops, v, cl, wave, g, r, topk);
             lds_barrier();
-            if (tid < TH && p0 + tid < n) merge_tops<KS>(tops, TH, tid, topk, C, p0 + tid, cand, cand16);
+            merge_tops<KS>(tops, TH, tid, topk, C, p0, n, cand, cand16);
         }
         load_a(r1, 0, wn * MT, 4, 0);
         lds_barrier();   // the next tile's input layer overwrites the activations
@@ -1103,7 +1125,7 @@ __global__ __launch_bounds__(512) void k_mlp_small(
             }
             put_tops<NT, KS ? KS : 1>(tops, v, cl, wave, g, r, a.topk);
             lds_barrier();
-            if (tid < TH && p0 + tid < n) merge_tops<KS ? KS : 1>(tops, TH, tid, a.topk, C, p0 + tid, cand, cand16);
+            merge_tops<KS ? KS : 1>(tops, TH, tid, a.topk, C, p0, n, cand, cand16);
         }
         // the next tile's first layer writes act[0], read before the last barrier, and its
         // second act[1] after another one
@@ -1500,12 +1522,14 @@ hipError_t launch_mlp(const tang_ruleset_t* rs, const tang_header_t* d_hdr, size
         // 524,288 headers, hidden 256: 713 us, 750 with 48 and four waves, 703 with 96, which
         // takes 36 against 26 for 10,000).
         if (m.split) {
-            const bool one = m.topk == 1;
+            const bool one = m.topk == 1, two = m.topk == 2;
             if (m.hidden == 128 && wide && one) e = launch_split<128, 4, 2, 1>(m, h, k, c, lg, c8, s, d_live);
+            else if (m.hidden == 128 && wide && two) e = launch_split<128, 4, 2, 2>(m, h, k, c, lg, c8, s, d_live);
             else if (m.hidden == 128 && wide) e = launch_split<128, 4, 2, 4>(m, h, k, c, lg, c8, s, d_live);
             else if (m.hidden == 128 && k <= 16384) e = launch_split<128, 4, 4>(m, h, k, c, lg, c8, s, d_live);
             else if (m.hidden == 128) e = launch_split<128, 6, 4>(m, h, k, c, lg, c8, s, d_live);
             else if (wide && one) e = launch_split<256, 4, 2, 1>(m, h, k, c, lg, c8, s, d_live);
+            else if (wide && two) e = launch_split<256, 4, 2, 2>(m, h, k, c, lg, c8, s, d_live);
             else if (wide) e = launch_split<256, 4, 2, 4>(m, h, k, c, lg, c8, s, d_live);
             else if (k <= 8192) e = launch_split<256, 2, 4>(m, h, k, c, lg, c8, s, d_live);
             else if (k < (1u << 18)) e = launch_split<256, 3, 4>(m, h, k, c, lg, c8, s, d_live);

@@ -76,3 +76,35 @@ def test_class_tile_edges(prec, hidden, C):
             assert np.median(np.abs(logits[:83] - want).max(axis=1) / np.abs(want).max(axis=1)) < 2.0 ** -8
     finally:
         T.tang_ruleset_destroy(rs)
+
+
+@pytest.mark.parametrize("topk", [2, 3, 4])
+@pytest.mark.parametrize("hidden", [128, 256])
+@pytest.mark.parametrize("prec", ["fp32", "bf16", "fp8"])
+def test_best_classes_of_all_waves(prec, hidden, topk):
+    """Many classes, spread over the waves: the candidates are the best of the scores whatever
+    waves hold them, ties to the lower class (four classes of different tiles that tie, above
+    most others), a NaN score last."""
+    torch_cuda()
+    rules = synth.make_rules(6000, seed=115, wide=True)
+    rs = T.tang_ruleset_create(0, rules)
+    try:
+        C = T.tang_ruleset_num_tuples(rs)
+        assert C > 128
+        Ws, bs = train.random_weights(C, hidden, seed=8)
+        for c in (60, 77, C - 1):
+            Ws[2][c] = Ws[2][5]
+            bs[2][c] = bs[2][5]
+        bs[2][[5, 60, 77, C - 1]] = np.sort(np.abs(bs[2]))[-3]
+        hdr = synth.make_packets(rules, 131, seed=116, frac_in=0.7)
+        sc = train.act_scales(Ws, bs, train.feature_bits_torch(hdr)) if prec == "fp8" else None
+        bs[2][90] = np.nan
+        T.tang_model_load(rs, Ws, bs, prec, topk=topk, act_scales=sc)
+        for n in (1, 16, 131, 4099):
+            at = np.arange(n) % len(hdr)
+            logits, cand = mlp_dev(rs, hdr[at], C, topk=topk)
+            known = np.where(np.isnan(logits), -np.inf, logits)
+            assert np.isnan(logits[:, 90]).all()
+            assert np.array_equal(cand, np.argsort(-known, axis=1, kind="stable")[:, :topk]), n
+    finally:
+        T.tang_ruleset_destroy(rs)
