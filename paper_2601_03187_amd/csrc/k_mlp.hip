@@ -815,7 +815,12 @@ __global__ __launch_bounds__(512, OCC) void k_mlp_split(
 #pragma unroll
             for (int pl = 0; pl < 3; ++pl) b[pl] = act[((pl * KBH + kb) * NT + nt) * 64 + lane];
         };
-        u32x4 O[2][3];   // KS: the output layer's fragments, two K blocks ahead
+        // KS: the wave's turns over the class tiles, and the output layer's fragments, two K
+        // blocks ahead
+        const int ct16 = (C + 15) / 16;
+        const uint32_t n_turns = turns(wave, (uint32_t)ct16, NT);
+        auto turn_at = [&](uint32_t i) { return (int)turn_tile(i, wave, (uint32_t)ct16, NT); };
+        u32x4 O[2][3];
         auto load_o = [&](int buf, int ct, int kb) {
             const uint32_t t = class_tile((uint32_t)ct, (uint32_t)C);
 #pragma unroll
@@ -845,8 +850,8 @@ __global__ __launch_bounds__(512, OCC) void k_mlp_split(
                 __builtin_amdgcn_sched_barrier(0);
             }
             if constexpr (KS != 0) {
-                load_o(0, (int)wave, 0);
-                load_o(1, (int)wave, 1);
+                load_o(0, turn_at(0u), 0);
+                load_o(1, turn_at(0u), 1);
             }
             lds_barrier();   // every wave has read the layer's input
 #pragma unroll
@@ -856,7 +861,8 @@ __global__ __launch_bounds__(512, OCC) void k_mlp_split(
         }
         lds_barrier();
         // Output layer in blocks of 32 classes: with one block, wave w takes header column w;
-        // with more, 16-class tiles w, w + 8, .. for all headers, and the waves' top-k lists are
+        // with more, 16-class tiles w, w + 8, .. for all headers while there are eight of them,
+        // then a header column of a tile that is left (turn_tile), and the waves' top-k lists are
         // merged through LDS.
         if constexpr (KS == 0) {
             if (wave < (uint32_t)NT) {
@@ -903,20 +909,21 @@ __global__ __launch_bounds__(512, OCC) void k_mlp_split(
                     v[nt][q] = -INFINITY;
                     cl[nt][q] = kNoClass;
                 }
-#pragma unroll 1
-            for (int ct = (int)wave; ct < (C + 15) / 16; ct += 8) {
+            // one turn: class tile ct for the header columns from FROM to TO
+            auto turn = [&](auto from, auto to, int ct, int ct_next) {
+                constexpr int FROM = decltype(from)::value, TO = decltype(to)::value;
                 f4 big[NT], small[NT];
 #pragma unroll
-                for (int nt = 0; nt < NT; ++nt) big[nt] = small[nt] = (f4){0, 0, 0, 0};
+                for (int nt = FROM; nt < TO; ++nt) big[nt] = small[nt] = (f4){0, 0, 0, 0};
 #pragma unroll
                 for (int kb = 0; kb < KBH; ++kb) {
                     u32x4 a[3];
 #pragma unroll
                     for (int pl = 0; pl < 3; ++pl) a[pl] = O[kb & 1][pl];
                     if (kb + 2 < KBH) load_o(kb & 1, ct, kb + 2);
-                    else load_o(kb & 1, ct + 8, kb + 2 - KBH);   // past the last tile: not used
+                    else load_o(kb & 1, ct_next, kb + 2 - KBH);   // past the last turn: not used
 #pragma unroll
-                    for (int nt = 0; nt < NT; ++nt) {
+                    for (int nt = FROM; nt < TO; ++nt) {
                         u32x4 b[3];
                         acts(kb, nt, b);
                         six(a, b, big[nt], small[nt]);
@@ -925,7 +932,7 @@ __global__ __launch_bounds__(512, OCC) void k_mlp_split(
                 }
                 const f4 b3 = *reinterpret_cast<const f4*>(sbias + 2 * H + 16 * ct + 4 * g);
 #pragma unroll
-                for (int nt = 0; nt < NT; ++nt) {
+                for (int nt = FROM; nt < TO; ++nt) {
                     const uint32_t pkt = p0 + 16u * nt + r;
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
@@ -935,6 +942,20 @@ __global__ __launch_bounds__(512, OCC) void k_mlp_split(
                         keep_best<KS>(v[nt], cl[nt], val, c, c < C);
                     }
                 }
+            };
+#pragma unroll 1
+            for (uint32_t i = 0; i < n_turns; ++i) {
+                const int ct = turn_at(i), ct_next = turn_at(i + 1u);
+                if (i < (uint32_t)ct16 / 8u) {
+                    turn(std::integral_constant<int, 0>{}, std::integral_constant<int, NT>{}, ct, ct_next);
+                    continue;
+                }
+                const uint32_t col = turn_column(i, wave, (uint32_t)ct16, NT);
+                static_assert(KS == 0 || NT == 4, "a case per header column");
+                if (col == 0u) turn(std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{}, ct, ct_next);
+                else if (col == 1u) turn(std::integral_constant<int, 1>{}, std::integral_constant<int, 2>{}, ct, ct_next);
+                else if (col == 2u) turn(std::integral_constant<int, 2>{}, std::integral_constant<int, 3>{}, ct, ct_next);
+                else turn(std::integral_constant<int, 3>{}, std::integral_constant<int, 4>{}, ct, ct_next);
             }
             lds_barrier();
             u32x2* const tops = act8;   // over the activations
@@ -1519,13 +1540,15 @@ hipError_t launch_mlp(const tang_ruleset_t* rs, const tang_header_t* d_hdr, size
         // headers 13 us with 32 per tile, 15 with 48, 22 with 96; 131,072 headers 149, 131 and
         // 134; 1,048,576 974, 857 and 826. Hidden 128, 10,000 headers 9.5 us with 64, 11.3
         // with 96; 1,048,576 359 and 318. More than 32 classes: 64 per tile (144 classes,
-        // 524,288 headers, hidden 256: 713 us, 750 with 48 and four waves, 703 with 96, which
-        // takes 36 against 26 for 10,000).
+        // 524,288 headers, hidden 256, whole class tiles to a wave: 713 us, 750 with 48 and four
+        // waves, 703 with 96, which takes 36 against 26 for 10,000; by turns 603). Hidden 128
+        // takes four waves (262,144 headers, top-1 155 us with two and 124, top-2 185 and 138,
+        // top-4 247 and 191; 16,384 headers, top-4 18 and 22).
         if (m.split) {
             const bool one = m.topk == 1, two = m.topk == 2;
-            if (m.hidden == 128 && wide && one) e = launch_split<128, 4, 2, 1>(m, h, k, c, lg, c8, s, d_live);
-            else if (m.hidden == 128 && wide && two) e = launch_split<128, 4, 2, 2>(m, h, k, c, lg, c8, s, d_live);
-            else if (m.hidden == 128 && wide) e = launch_split<128, 4, 2, 4>(m, h, k, c, lg, c8, s, d_live);
+            if (m.hidden == 128 && wide && one) e = launch_split<128, 4, 4, 1>(m, h, k, c, lg, c8, s, d_live);
+            else if (m.hidden == 128 && wide && two) e = launch_split<128, 4, 4, 2>(m, h, k, c, lg, c8, s, d_live);
+            else if (m.hidden == 128 && wide) e = launch_split<128, 4, 4, 4>(m, h, k, c, lg, c8, s, d_live);
             else if (m.hidden == 128 && k <= 16384) e = launch_split<128, 4, 4>(m, h, k, c, lg, c8, s, d_live);
             else if (m.hidden == 128) e = launch_split<128, 6, 4>(m, h, k, c, lg, c8, s, d_live);
             else if (wide && one) e = launch_split<256, 4, 2, 1>(m, h, k, c, lg, c8, s, d_live);

@@ -286,6 +286,20 @@ __host__ __device__ constexpr uint32_t stored(uint32_t want, uint32_t count) {
 __host__ __device__ constexpr uint32_t class_tile(uint32_t ct, uint32_t classes) {
     return stored(ct, 2u * ((classes + 31u) / 32u));
 }
+// The class tile of a wave's i-th turn when eight waves share `tiles` class tiles for `columns`
+// header columns: whole rounds of eight tiles for all columns, then the tiles left, a wave
+// taking one column of one (turn_column) per turn.
+__host__ __device__ constexpr uint32_t turn_tile(uint32_t i, uint32_t wave, uint32_t tiles, uint32_t columns) {
+    const uint32_t rounds = tiles / 8u;
+    return i < rounds ? wave + 8u * i : 8u * rounds + (wave + 8u * (i - rounds)) / columns;
+}
+__host__ __device__ constexpr uint32_t turn_column(uint32_t i, uint32_t wave, uint32_t tiles, uint32_t columns) {
+    return (wave + 8u * (i - tiles / 8u)) % columns;
+}
+// Turns of a wave: its rounds, and its share of the columns of the tiles left.
+__host__ __device__ constexpr uint32_t turns(uint32_t wave, uint32_t tiles, uint32_t columns) {
+    return tiles / 8u + (tiles % 8u * columns + 7u - wave) / 8u;
+}
 // Residual network of nb blocks: the byte offset of wave `wave`'s K block kb (4 KB) of block
 // layer l, and the bias row (512 floats) of that layer.
 __host__ __device__ constexpr uint32_t res_weight_at(uint32_t l, uint32_t wave, uint32_t kb, uint32_t nb) {

@@ -12,6 +12,9 @@ BODY = """
 extern "C" unsigned weight_at(unsigned l, unsigned wave, unsigned kb, unsigned nb) { return res_weight_at(l, wave, kb, nb); }
 extern "C" unsigned bias_row(unsigned l, unsigned nb) { return res_bias_row(l, nb); }
 extern "C" unsigned tile_of(unsigned ct, unsigned classes) { return class_tile(ct, classes); }
+extern "C" unsigned turn_count(unsigned w, unsigned tiles, unsigned cols) { return turns(w, tiles, cols); }
+extern "C" unsigned turn_of(unsigned i, unsigned w, unsigned tiles, unsigned cols) { return turn_tile(i, w, tiles, cols); }
+extern "C" unsigned column_of(unsigned i, unsigned w, unsigned tiles, unsigned cols) { return turn_column(i, w, tiles, cols); }
 """
 
 
@@ -51,3 +54,22 @@ def test_plain_network_class_tiles(lib, C):
             named.append(ct)                           # loaded during the tile before
         assert all(0 <= lib.tile_of(t, C) < stored for t in named), (wave, named)
     assert sorted(visited) == list(np.arange(-(-C // 16)))
+
+
+@pytest.mark.parametrize("C", [33, 48, 49, 64, 65, 112, 113, 128, 129, 144, 256, 257, 387, 512])
+def test_turns_over_the_class_tiles(lib, C):
+    """Eight waves that share class tiles by turns (four header columns): every tile meets every
+    column once, no wave has two turns more than another, and the tile named ahead is stored."""
+    tiles, cols, stored = -(-C // 16), 4, 2 * -(-C // 32)
+    seen, count = [], []
+    for wave in range(8):
+        n = lib.turn_count(wave, tiles, cols)
+        count.append(n)
+        for i in range(n + 1):
+            tile = lib.turn_of(i, wave, tiles, cols)
+            assert 0 <= lib.tile_of(tile, C) < stored
+            if i < n:
+                assert tile < tiles
+                seen += [(tile, c) for c in (range(cols) if i < tiles // 8 else [lib.column_of(i, wave, tiles, cols)])]
+    assert sorted(seen) == [(t, c) for t in range(tiles) for c in range(cols)]
+    assert max(count) - min(count) <= 1
