@@ -102,7 +102,8 @@ typedef struct tang_stats_s {
     uint64_t fallbacks;   /* nothing matched in the predicted tuples */
     uint64_t no_match;    /* packets with no matching rule at all */
     uint64_t filter_checks;  /* bucket-filter blocks read */
-    uint64_t wave_steps;     /* per 64 packets: 64 x the probe-loop steps of their wave */
+    uint64_t wave_steps;     /* per packet: probe-loop steps of its wave (64 packets, or 128
+                                from 524,288 packets and up to 32 tuples) */
     uint64_t wave_rounds;    /* per packet: filter batches (8 groups) of its wave */
 } tang_stats_t;
 

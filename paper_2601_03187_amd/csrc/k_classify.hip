@@ -245,7 +245,7 @@ __global__ __launch_bounds__(256) void k_classify(const uint4* __restrict__ hdr,
                 FilterOps ops = *reinterpret_cast<const FilterOps*>(ttg->fop);
                 for (uint32_t g0 = 0; g0 < ngroups; g0 += 8u) {
                     uint2 blk[8];
-                    if (STATS) ++n_rounds;
+                    if (STATS) n_rounds += active;
 #pragma unroll
                     for (uint32_t q = 0; q < 8u; ++q) {
                         blk[q] = make_uint2(0u, 0u);
@@ -541,11 +541,11 @@ __global__ __launch_bounds__(256) void k_classify(const uint4* __restrict__ hdr,
     if (STATS) {
         // wave sums -> block sums in LDS -> one set of atomics per block, spread over
         // kStatCopies counter copies (summed on the host) to avoid one hot address.
-        // Steps and rounds are a wave's own counts, shared out over 64 headers.
+        // Steps are the wave's own count, once for each of its headers.
         constexpr int NS = 10;
         __shared__ unsigned long long s_red[4][NS];
         unsigned long long v[NS] = {lane == 0 ? cnt : 0u, n_probe, n_slots, n_recs, top1, fb, nm, n_filter,
-                                    n_steps, n_rounds};
+                                    lane == 0 ? (unsigned long long)cnt * n_steps : 0u, n_rounds};
 #pragma unroll
         for (int q = 0; q < NS; ++q) v[q] = wave_sum(v[q]);
         if (lane == 0)
@@ -585,9 +585,13 @@ hipError_t launch_classify(const tang_ruleset_t* rs, const tang_header_t* d_hdr,
         // LDS in both forms, 144 tuples, 2.1M headers: 387 against 476 us; 387 tuples, 1M: 884
         // against 977).
         if (rs->nw == 1) {
-            if (stats) go(k_classify<true, 1, 2, 1>, 2);
-            else if (m >= kQueueFrom) go(k_classify<false, 1, 2, 1>, 2);
-            else go(k_classify<false, 1, 1, 2>, 1);
+            if (m >= kQueueFrom) {
+                if (stats) go(k_classify<true, 1, 2, 1>, 2);
+                else go(k_classify<false, 1, 2, 1>, 2);
+            } else {
+                if (stats) go(k_classify<true, 1, 1, 2>, 1);
+                else go(k_classify<false, 1, 1, 2>, 1);
+            }
         } else if (rs->nw == kMaskWords) {
             if (stats) go(k_classify<true, kMaskWords, 1, 2>, 1);
             else go(k_classify<false, kMaskWords, 1, 2>, 1);

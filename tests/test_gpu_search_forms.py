@@ -207,3 +207,29 @@ def test_queued_form_scans_long_lists_as_fast():
         assert best[1] < 1.2 * best[0], best
     finally:
         T.tang_ruleset_destroy(rs)
+
+
+def test_counters_follow_the_form_that_runs():
+    """Copies of one header that one slot answers: per packet, each counter is the same for
+    whole, ragged and queued batches, and a packet's wave takes the steps of one header, or of
+    two where a wave holds 128."""
+    torch_cuda()
+    rules = synth.make_rules(2000, seed=121)
+    k = int(np.flatnonzero((rules["sip_len"] == 32) & (rules["dip_len"] == 32))[0])
+    hdr = synth.sample_inside(rules[k:k + 1], np.random.default_rng(1))
+    rs = T.tang_ruleset_create(0, rules)
+    try:
+        per = {}
+        for n in (64, 65, 100, 129, QUEUE_FROM - 1, QUEUE_FROM):
+            got, st = classify_dev(rs, np.repeat(hdr, n), stats=True)
+            assert (got == got[0]).all() and st["packets"] == n
+            assert all(st[f] % n == 0 for f in ("probes", "slots", "records", "filter_checks", "wave_steps", "wave_rounds")), n
+            per[n] = {f: st[f] // n for f in ("probes", "slots", "records", "filter_checks", "wave_rounds", "wave_steps")}
+        one = per[64]
+        assert one["wave_steps"] >= one["slots"] > 0 and one["wave_rounds"] > 0
+        for n in (65, 100, 129, QUEUE_FROM - 1):
+            assert per[n] == one, n
+        queued = dict(one, wave_steps=2 * one["wave_steps"])
+        assert per[QUEUE_FROM] == queued
+    finally:
+        T.tang_ruleset_destroy(rs)
