@@ -972,9 +972,9 @@ __global__ __launch_bounds__(512, OCC) void k_mlp_split(
 // BF16 and FP8 for small batches. k_mlp gives a wave whole headers and stages 100 to 150 KB of
 // weights per workgroup first, which a batch of a few tiles waits for. Here the workgroup's 8
 // waves split the neurons: wave w computes H/8 of them in both hidden layers for 16 NT
-// headers, holds its share of those weights in registers (loaded at once, at the start) and
+// headers, loads its share of those weights from L2 straight into registers and
 // exchanges activations through LDS. Fragments, K order and epilogues are k_mlp's, so the
-// scores are the same bit for bit.
+// scores are the same bit for bit. One workgroup per tile.
 // KS: 0 with at most 32 classes, else the top-k slots kept (wave w takes the 16-class tiles
 // w, w + 8, .. and the waves' lists are merged through LDS).
 // What bounds it: the chain of loads and layers, not the matrix units. Predictor call, k_mlp
@@ -993,8 +993,7 @@ __global__ __launch_bounds__(512) void k_mlp_small(
     __shared__ F act[2][KBH * NT * 64];   // first and second hidden layer, B fragments
     __shared__ u32x2 tops[KS ? 8 * TH * KS : 1];
     if (live) n = min(n, *live);
-    const uint32_t tiles = (n + TH - 1) / TH;
-    if (blockIdx.x >= tiles) return;
+    if (blockIdx.x * TH >= n) return;
     const uint32_t tid = threadIdx.x, lane = tid & 63u, g = lane >> 4, r = lane & 15u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int C = a.n_out;
@@ -1033,124 +1032,116 @@ __global__ __launch_bounds__(512) void k_mlp_small(
         b1[u] = *reinterpret_cast<const f4*>(bias + 16 * (wave * MT + u) + 4 * g);
         b2[u] = *reinterpret_cast<const f4*>(bias + H + 16 * (wave * MT + u) + 4 * g);
     }
-    bool first = true;
-    for (uint32_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
-        const uint32_t p0 = tile * TH;
-        uint4 hv[NT];
+    const uint32_t p0 = blockIdx.x * TH;
+    uint4 hv[NT];
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            const uint32_t p = p0 + nt * 16 + r;
-            hv[nt] = p < n ? hdr[p] : make_uint4(0u, 0u, 0u, 0u);
+    for (int nt = 0; nt < NT; ++nt) {
+        const uint32_t p = p0 + nt * 16 + r;
+        hv[nt] = p < n ? hdr[p] : make_uint4(0u, 0u, 0u, 0u);
+    }
+#pragma unroll
+    for (int u = 0; u < MT; ++u)
+#pragma unroll
+        for (int kb = 0; kb < KBH; ++kb) A2[u][kb] = frag(r2, (wave * MT + u) * KBH + kb);
+    if constexpr (KS == 0) {
+        load3(0, 0);
+        load3(1, 1);
+    } else {
+        load3(0, (int)wave);
+    }
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+        f4 acc[MT];
+#pragma unroll
+        for (int u = 0; u < MT; ++u) acc[u] = b1[u];
+#pragma unroll
+        for (int kb = 0; kb < KB1; ++kb) {
+            const F x = Bits<PREC>::make(hv[nt], kb, g);
+#pragma unroll
+            for (int u = 0; u < MT; ++u) acc[u] = mma(A1[u][kb], x, acc[u]);
         }
-        if (first) {
 #pragma unroll
-            for (int u = 0; u < MT; ++u)
+        for (int u = 0; u < MT; ++u) store(act[0], u, nt, acc[u], a.rq[0], a.rb[0]);
+    }
+    lds_barrier();
 #pragma unroll
-                for (int kb = 0; kb < KBH; ++kb) A2[u][kb] = frag(r2, (wave * MT + u) * KBH + kb);
-            if constexpr (KS == 0) {
-                load3(0, 0);
-                load3(1, 1);
-            }
-            first = false;
+    for (int nt = 0; nt < NT; ++nt) {
+        f4 acc[MT];
+#pragma unroll
+        for (int u = 0; u < MT; ++u) acc[u] = b2[u];
+#pragma unroll
+        for (int kb = 0; kb < KBH; ++kb) {
+            const F x = act[0][(kb * NT + nt) * 64 + lane];
+#pragma unroll
+            for (int u = 0; u < MT; ++u) acc[u] = mma(A2[u][kb], x, acc[u]);
         }
-        if constexpr (KS != 0) load3(0, (int)wave);
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            f4 acc[MT];
+        for (int u = 0; u < MT; ++u) store(act[1], u, nt, acc[u], a.rq[1], a.rb[1]);
+    }
+    lds_barrier();
+    const float* sb3 = bias + 2 * H;
+    if constexpr (KS == 0) {
+        if (wave < (uint32_t)NT) {
+            const uint32_t pkt = p0 + 16u * wave + r;
+            float v[8];
+            int cl[8];
 #pragma unroll
-            for (int u = 0; u < MT; ++u) acc[u] = b1[u];
+            for (int u = 0; u < 2; ++u) {
+                f4 z = (f4){0, 0, 0, 0};
 #pragma unroll
-            for (int kb = 0; kb < KB1; ++kb) {
-                const F x = Bits<PREC>::make(hv[nt], kb, g);
+                for (int kb = 0; kb < KBH; ++kb) z = mma(A3[u][kb], act[1][(kb * NT + wave) * 64 + lane], z);
 #pragma unroll
-                for (int u = 0; u < MT; ++u) acc[u] = mma(A1[u][kb], x, acc[u]);
-            }
-#pragma unroll
-            for (int u = 0; u < MT; ++u) store(act[0], u, nt, acc[u], a.rq[0], a.rb[0]);
-        }
-        lds_barrier();
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            f4 acc[MT];
-#pragma unroll
-            for (int u = 0; u < MT; ++u) acc[u] = b2[u];
-#pragma unroll
-            for (int kb = 0; kb < KBH; ++kb) {
-                const F x = act[0][(kb * NT + nt) * 64 + lane];
-#pragma unroll
-                for (int u = 0; u < MT; ++u) acc[u] = mma(A2[u][kb], x, acc[u]);
-            }
-#pragma unroll
-            for (int u = 0; u < MT; ++u) store(act[1], u, nt, acc[u], a.rq[1], a.rb[1]);
-        }
-        lds_barrier();
-        const float* sb3 = bias + 2 * H;
-        if constexpr (KS == 0) {
-            if (wave < (uint32_t)NT) {
-                const uint32_t pkt = p0 + 16u * wave + r;
-                float v[8];
-                int cl[8];
-#pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    f4 z = (f4){0, 0, 0, 0};
-#pragma unroll
-                    for (int kb = 0; kb < KBH; ++kb) z = mma(A3[u][kb], act[1][(kb * NT + wave) * 64 + lane], z);
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int c = 16 * u + 4 * (int)g + q;
-                        const float val = (PREC == TANG_FP8 ? z[q] * a.deq[2] : z[q]) + sb3[c];
-                        if (logits && pkt < n && c < C) logits[(size_t)pkt * C + c] = val;
-                        v[4 * u + q] = (c < C && val == val) ? val : -INFINITY;
-                        cl[4 * u + q] = c;
-                    }
+                for (int q = 0; q < 4; ++q) {
+                    const int c = 16 * u + 4 * (int)g + q;
+                    const float val = (PREC == TANG_FP8 ? z[q] * a.deq[2] : z[q]) + sb3[c];
+                    if (logits && pkt < n && c < C) logits[(size_t)pkt * C + c] = val;
+                    v[4 * u + q] = (c < C && val == val) ? val : -INFINITY;
+                    cl[4 * u + q] = c;
                 }
-                uint32_t packed = 0;
-                for (int k = 0; k < a.topk; ++k) {
-                    const int bc = take_best<8>(v, cl).second;
-                    packed |= (uint32_t)bc << (8 * k);
-                    if (cand16 && g == 0 && pkt < n) cand16[(size_t)pkt * a.topk + k] = (uint16_t)bc;
-                }
-                if (cand && g == 0 && pkt < n) cand[pkt] = packed;
             }
-        } else {
-            float v[NT][KS ? KS : 1];
-            int cl[NT][KS ? KS : 1];
+            uint32_t packed = 0;
+            for (int k = 0; k < a.topk; ++k) {
+                const int bc = take_best<8>(v, cl).second;
+                packed |= (uint32_t)bc << (8 * k);
+                if (cand16 && g == 0 && pkt < n) cand16[(size_t)pkt * a.topk + k] = (uint16_t)bc;
+            }
+            if (cand && g == 0 && pkt < n) cand[pkt] = packed;
+        }
+    } else {
+        float v[NT][KS ? KS : 1];
+        int cl[NT][KS ? KS : 1];
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
+        for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-                for (int q = 0; q < KS; ++q) {
-                    v[nt][q] = -INFINITY;
-                    cl[nt][q] = kNoClass;
-                }
+            for (int q = 0; q < KS; ++q) {
+                v[nt][q] = -INFINITY;
+                cl[nt][q] = kNoClass;
+            }
 #pragma unroll 1
-            for (int ct = (int)wave; ct < (C + 15) / 16; ct += 8) {
-                const f4 b3 = *reinterpret_cast<const f4*>(sb3 + 16 * ct + 4 * g);
-                const uint32_t ahead = class_tile((uint32_t)ct + 8u, (uint32_t)C);   // past the last tile: not used
+        for (int ct = (int)wave; ct < (C + 15) / 16; ct += 8) {
+            const f4 b3 = *reinterpret_cast<const f4*>(sb3 + 16 * ct + 4 * g);
+            const uint32_t ahead = class_tile((uint32_t)ct + 8u, (uint32_t)C);   // past the last tile: not used
 #pragma unroll
-                for (int nt = 0; nt < NT; ++nt) {
-                    f4 z = (f4){0, 0, 0, 0};
+            for (int nt = 0; nt < NT; ++nt) {
+                f4 z = (f4){0, 0, 0, 0};
 #pragma unroll
-                    for (int kb = 0; kb < KBH; ++kb) {
-                        z = mma(A3[0][kb], act[1][(kb * NT + nt) * 64 + lane], z);
-                        if (nt == NT - 1) A3[0][kb] = frag(r3, ahead * KBH + kb);
-                    }
-                    const uint32_t pkt = p0 + 16u * nt + r;
+                for (int kb = 0; kb < KBH; ++kb) {
+                    z = mma(A3[0][kb], act[1][(kb * NT + nt) * 64 + lane], z);
+                    if (nt == NT - 1) A3[0][kb] = frag(r3, ahead * KBH + kb);
+                }
+                const uint32_t pkt = p0 + 16u * nt + r;
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int c = 16 * ct + 4 * (int)g + q;
-                        const float val = (PREC == TANG_FP8 ? z[q] * a.deq[2] : z[q]) + b3[q];
-                        if (logits && pkt < n && c < C) logits[(size_t)pkt * C + c] = val;
-                        keep_best<KS ? KS : 1>(v[nt], cl[nt], val, c, c < C);
-                    }
+                for (int q = 0; q < 4; ++q) {
+                    const int c = 16 * ct + 4 * (int)g + q;
+                    const float val = (PREC == TANG_FP8 ? z[q] * a.deq[2] : z[q]) + b3[q];
+                    if (logits && pkt < n && c < C) logits[(size_t)pkt * C + c] = val;
+                    keep_best<KS ? KS : 1>(v[nt], cl[nt], val, c, c < C);
                 }
             }
-            put_tops<NT, KS ? KS : 1>(tops, v, cl, wave, g, r, a.topk);
-            lds_barrier();
-            merge_tops<KS ? KS : 1>(tops, TH, tid, a.topk, C, p0, n, cand, cand16);
         }
-        // the next tile's first layer writes act[0], read before the last barrier, and its
-        // second act[1] after another one
-        if constexpr (KS != 0) lds_barrier();
+        put_tops<NT, KS ? KS : 1>(tops, v, cl, wave, g, r, a.topk);
+        lds_barrier();
+        merge_tops<KS ? KS : 1>(tops, TH, tid, a.topk, C, p0, n, cand, cand16);
     }
 }
 

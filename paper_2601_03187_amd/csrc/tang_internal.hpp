@@ -131,10 +131,10 @@ struct TupleDev {
 constexpr int kMaxGroups = 64;
 constexpr uint32_t kNoGroup = 0xFFu;
 // A group and its tuples as the filter reads them (one scalar load each): the group's own
-// field (dip: 0 SIP, 1 DIP) and its mask and salt, and its range of FilterOps; a tuple's
-// mask on the other field and its salt.
-struct alignas(32) FilterGroup {
-    uint32_t dip, mask, salt, begin, end, pad[3];
+// field (dip: 0 SIP, 1 DIP) and its mask and salt, and the end of its FilterOps (they begin
+// where the group before ends); a tuple's mask on the other field and its salt.
+struct alignas(16) FilterGroup {
+    uint32_t dip, mask, salt, end;
 };
 struct alignas(8) FilterOp {
     uint32_t omask, salt;   // the salt's low 9 bits are the tuple

@@ -217,7 +217,6 @@ TupleTable make_tuple_table(const tang_ruleset_t* rs) {
         f.dip = tt.gkey[g] >> 6;
         f.mask = pmask(tt.gkey[g] & 63u);
         f.salt = group_salt(tt.gkey[g]);
-        f.begin = ops;
         for (uint32_t t = 0; t < n; ++t)
             if (tt.tg[t].gkey == tt.gkey[g]) tt.fop[ops++] = FilterOp{f.dip ? tt.t[t].smask : tt.t[t].dmask, filter_salt(t)};
         f.end = ops;
