@@ -254,9 +254,9 @@ struct StatsDev {
 };
 constexpr int kStatCopies = 64;
 
-// Updates' staging (see tang_ruleset_s): 1,000 rules take 300 KB of the pinned part.
-constexpr size_t kUpdHost = (size_t)1 << 20;
-constexpr size_t kUpdDevMin = (size_t)2 << 20, kUpdDevKeep = (size_t)16 << 20;
+// Updates' staging (see tang_ruleset_s): 800 rules fill the pinned part.
+constexpr size_t kUpdHost = (size_t)256 << 10;
+constexpr size_t kUpdDevMin = (size_t)512 << 10, kUpdDevKeep = (size_t)16 << 20;
 
 // Rule box used by the conflict-mask kernels (key order), 32 B.
 struct alignas(16) BoxDev {
