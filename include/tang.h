@@ -194,7 +194,8 @@ int tang_model_unload(tang_ruleset_t* rs);
  * W[1 + 2k] and W[2 + 2k] (block k's two layers) width x width, W[last] C x width.
  * Precision: BF16 only (the input layer is computed in FP32; every later layer's weights
  * and inputs are rounded to bfloat16, nearest-even; FP32 accumulation and biases).
- * Deep copy; replaces any loaded model. The library also allocates a 192 MB workspace.
+ * Deep copy; replaces any loaded model. The library also allocates 192 MB of device memory
+ * with it, a workspace that the present kernel does not use.
  * Errors: EINVAL (width != 512, n_blocks outside 1..16, n_out != C, topk outside
  * 1..min(4, C), precision not BF16, NULL pointers), ENOMEM, EDEVICE.
  */

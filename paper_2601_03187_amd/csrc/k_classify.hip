@@ -27,12 +27,16 @@ namespace {
 constexpr uint32_t kNoTuple = 0xFFFFFFFFu;
 // Sets of 64 headers per wave, rulesets of at most 32 tuples: two, through a queue, from this
 // many headers on, one below. More sets keep a wave's lanes busy longer, fewer make more waves
-// (one set and two: 100,000 rules, 600,000 headers 99 and 112 us, 1,048,576 141 and 151,
-// 4,194,304 436 and 362; 512k rules with 25% wildcard-heavy rules 92 and 77, 139 and 114, 471
-// and 355). Four sets need 36 KB of LDS and leave four waves per SIMD: 1,800 rules, 4.2M
-// headers 316 us against 265 with two.
+// (one set and two: 100,000 rules, 600,000 headers 52 and 55 us, 1,048,576 76 and 77,
+// 4,194,304 233 and 212; 512k rules with 25% wildcard-heavy rules 79 and 71, 120 and 106, 405
+// and 324). Four sets need 36 KB of LDS and leave four waves per SIMD: 1,800 rules, 4.2M
+// headers 143 us against 125 with two, 600,000 headers 36 against 28.
 constexpr uint32_t kQueueFrom = 1u << 19;
-constexpr uint32_t kScan = 4, kScanTry = 8;   // records of a list at once; steps between looks
+// Long lists are passed over kScan records at a time (4.2M headers, 512k rules in one /8: 3 and
+// 4 records 394 and 384 us, 4 and 8 391 and 375; 65,536 rules, 25% wildcard-heavy: 291 and 296,
+// 294 and 321), looked for every kScanTry steps (1,800 rules in short lists: every step 209 us,
+// every eighth 203, not at all 195).
+constexpr uint32_t kScan = 4, kScanTry = 8;
 
 __device__ __forceinline__ bool kless(uint32_t p1, uint32_t i1, uint32_t p2, uint32_t i2) {
     return p1 < p2 || (p1 == p2 && i1 < i2);
@@ -68,10 +72,10 @@ struct alignas(16) Entry {
 // per wave. U: records of a list per step: a small batch lasts as long as its longest list
 // scan, so more records in flight pay there, until the registers cost waves.
 //
-// What bounds it (25 tuples, 512k rules, no predictor, 4.2M Zipf headers: 258 us): vector
-// issue, about 225 us of it, and random 128-byte lines beside it: the card serves 265 G
+// What bounds it (25 tuples, 512k rules, no predictor, 4.2M Zipf headers: 267 us): vector
+// issue, about 190 us of it, and random 128-byte lines beside it: the card serves 265 G
 // random accesses/s that hit an L2 and 60 G that miss it, and a header needs about 7.5 and
-// 1.1 of them, together 195 us. One header per lane with a slot table, its records and the
+// 1.1 of them, together 193 us. One header per lane with a slot table, its records and the
 // filter each on lines of their own (8.6 and 2.0 accesses) took 396 us, 93% of it vector
 // issue: the wave ran its probe loop as long as its busiest lane needed, 25 steps where a
 // header needs 3.1 on average.
@@ -231,8 +235,9 @@ __global__ __launch_bounds__(256) void k_classify(const uint4* __restrict__ hdr,
                 // instructions without a branch; a lane that does not need a group reads block 0
                 // with the others and drops the outcome. This is most of what a wide ruleset's
                 // search does: 387 tuples, 1M headers 842 us with one scalar load, a 32-bit
-                // product and a branch per tuple, 594 so, and 548 with the headers in registers
-                // (five waves per SIMD instead of four).
+                // product and a branch per tuple, 594 so (548 with the headers in registers, five
+                // waves per SIMD instead of four; 484 with long lists passed over and the
+                // filter's present hashes).
                 uint32_t hits = 0;
                 if constexpr (NW == 1) {
                     hits = todo[0] & ttg->nogroup[0];
@@ -576,14 +581,14 @@ hipError_t launch_classify(const tang_ruleset_t* rs, const tang_header_t* d_hdr,
                                reinterpret_cast<const uint2*>(rs->d_filter), rs->d_tt, kcand, rs->d_stats,
                                d_live);
         };
-        // Records per step, small batches (U = 1, 2, 4; 65,536 headers): 100,000 rules 52, 45,
-        // 43 us, 1,800 rules 28, 30, 33; two sets, 4.2M headers (U = 1, 2): 100,000 rules 368
-        // and 344, 512k 259 and 265, 1,800 225 and 241. 144 tuples (U = 1, 2), 65,536 headers 64
-        // and 59, 2.1M 293 and 295; 387 tuples, 1M 548 and 570.
+        // Records per step (U = 1 and 2), 65,536 headers: 100,000 rules 27 and 23 us, 512k with
+        // 25% wildcard-heavy rules 31 and 33, 1,800 rules 13 and 15; two sets, 4.2M headers: 100,000
+        // rules 212 and 211, 512k 254 and 274, 1,800 125 and 137. 144 tuples, 65,536 headers 39 and
+        // 38, 2.1M 253 and 260; 387 tuples, 1M 491 and 514.
         // Wider rulesets take one set: two need LDS for the headers and a second set of work
         // rows, and the waves lost cost more than the fuller lanes give (with the headers in
-        // LDS in both forms, 144 tuples, 2.1M headers: 387 against 476 us; 387 tuples, 1M: 884
-        // against 977).
+        // LDS in both forms and records taken one by one, 144 tuples, 2.1M headers: 387 against
+        // 476 us; 387 tuples, 1M: 884 against 977).
         if (rs->nw == 1) {
             if (m >= kQueueFrom) {
                 if (stats) go(k_classify<true, 1, 2, 1>, 2);

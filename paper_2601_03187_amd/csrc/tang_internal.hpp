@@ -33,7 +33,7 @@ constexpr uint32_t kMaxBucketLen = (1u << kTlShift) - 1u;
 
 // Long buckets are split. A bucket that would hold more than kSplitAt rules keeps its
 // slot only as a marker (len 0, off = kSplit | bucket index); its rules move to four
-// sub-lists stored in the same table under keys (tuple | kind << 8, bucket index, value):
+// sub-lists stored in the same table under keys (tuple | kind << 9, bucket index, value):
 //   kSubDp    rules with an exact DP, value = that DP
 //   kSubSp    rules with an exact SP (DP not exact), value = that SP
 //   kSubProto rules with an exact protocol and no exact port, value = the protocol
@@ -64,11 +64,11 @@ inline int max_topk(int n_tuples) {
     return k < n_tuples ? k : n_tuples;
 }
 
-// Rec (32 B): one rule as the bucket scan reads it, hot half first. The scan reads the
-// first 16 bytes of each record (one load): ports, priority and the protocol/length
-// word decide a match for a rule held by its own tuple. The second half is read only
-// for a match (its id and conflict mask), a priority tie (the id breaks it), or a rule
-// held by a coarser tuple than its own signature (its prefixes must be checked).
+// Rec (32 B): one rule as the bucket scan reads it, hot half first: ports, priority and the
+// protocol/length word, which decide a match for a rule held by its own tuple. The second
+// half matters for a match (its id and conflict mask), a priority tie (the id breaks it), or
+// a rule held by a coarser tuple than its own signature (its prefixes must be checked). A
+// step of the search loads both halves; long lists are passed over by their first ones.
 //   sp, dp   : lo | hi << 16 (inclusive)
 //   prio     : priority; (prio, id) is the key, kDead in both marks a vacated record
 //   meta     : proto (bits 0-7) | exact-proto (8) | prefix check (9) | sip_len (10-15)
