@@ -417,30 +417,40 @@ __global__ __launch_bounds__(256) void k_classify(const uint4* __restrict__ hdr,
                         ((uint32_t)(meta_exact(b.w) == 0) | (uint32_t)(proto == meta_proto(b.w)))) != 0u;
             };
             // Where most of the wave's busy lanes are in long lists, they first pass over records
-            // that cannot matter, kScan at a time, by their first halves; the record where a lane
-            // stops goes through a step. Looked for every kScanTry steps, and in each step while
-            // it holds. Lists of a record or two do not pay for it (1,800 rules, 4.2M headers 196 us
-            // without and 200 with); where headers meet long lists it is most of the time (25
-            // tuples and one list of 4,000 rules that half of the headers go through, 524,288
-            // headers 4.96 and 1.13 ms; 512k rules in one /8 301 and 116 us). One word of tuples: at
-            // the step's end (before its loads 200 becomes 203); more: before its loads (387 tuples,
-            // 1M headers 564, at the end 624).
+            // that cannot matter, kScan at a time, by their first halves (and the one where a lane
+            // stops by its own prefixes, if a coarser tuple holds it); the record where a lane
+            // stops for good goes through a step. Looked for every kScanTry steps, and every
+            // second while it holds. Lists of a record or two do not pay for it (1,800 rules, 4.2M
+            // headers 196 us without and 200 with); where headers meet long lists it is most of the
+            // time (25 tuples and one list of 4,000 rules that half of the headers go through,
+            // 524,288 headers 4.96 and 1.16 ms; 512k rules in one /8 301 and 115 us; 65,536 rules and
+            // 17,000 more held by coarser tuples, with the BF16 predictor, 1M headers 1,480 and 1,510
+            // Mpps, 1,210 where every step looked and coarse-held records stopped it; every third
+            // step 1,530, but the 4,000 rules take 1.49 ms). One word of tuples: at the step's end
+            // (before its loads 200 becomes 203); more: before its loads (387 tuples, 1M headers
+            // 564, at the end 624).
             auto pass_over = [&]() {
                 if (--try_scan != 0) return;
                 try_scan = kScanTry;
                 bool scan = ps == P_REC && left > kScan;
                 while (3u * (uint32_t)__popcll(__ballot(scan)) > 2u * (uint32_t)__popcll(__ballot(ps != P_IDLE))) {
-                    try_scan = 1;
+                    try_scan = 2;
                     if (scan) {
                         const uint4* const p = reinterpret_cast<const uint4*>(recs + at);
                         uint4 h[kScan];
 #pragma unroll
                         for (uint32_t j = 0; j < kScan; ++j) h[j] = p[2u * j];
-                        uint32_t past = 0;
+                        uint32_t past = 0, at_meta = 0;   // meta of the record where it stops
                         bool on = true;
 #pragma unroll
                         for (uint32_t j = 0; j < kScan; ++j) {
+                            at_meta = on ? h[j].w : at_meta;
                             on &= !fits(h[j]) & (h[j].z < bp);
+                            past += on ? 1u : 0u;
+                        }
+                        if (!on && meta_check(at_meta)) {   // held by a coarser tuple: its own prefixes
+                            const uint4 b = p[2u * past], c = p[2u * past + 1u];
+                            on = (b.z < bp) & ((((sip ^ c.x) & pmask(meta_sl(at_meta))) | ((dip ^ c.y) & pmask(meta_dl(at_meta)))) != 0u);
                             past += on ? 1u : 0u;
                         }
                         if (STATS) n_recs += past;

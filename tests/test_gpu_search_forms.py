@@ -233,3 +233,41 @@ def test_counters_follow_the_form_that_runs():
         assert per[QUEUE_FROM] == queued
     finally:
         T.tang_ruleset_destroy(rs)
+
+
+@pytest.mark.parametrize("space", ["narrow", "wide"])
+def test_long_lists_of_coarse_rules_equal_oracle(space):
+    """Lists whose rules a coarser tuple holds (inserted with lengths that no tuple has), most
+    of them kept apart by their own prefixes alone, ports and protocol open: each header's
+    answer at its place in the list, in both forms of the narrow search."""
+    torch_cuda()
+    rules = synth.make_rules(2000, seed=131, wide=space == "wide")
+    n = 390
+    late = synth.make_rules(n, seed=132, ordering="literal")
+    rng = np.random.default_rng(5)
+    late["sip_len"], late["dip_len"] = rng.integers(9, 12, n), rng.integers(4, 8, n)
+    for f, base in (("sip", 0x0A000000), ("dip", 0)):
+        keep = -(1 << (32 - late[f + "_len"].astype(np.int64)))
+        late[f] = (base | rng.integers(0, 1 << 24 if base else 1 << 32, n)) & keep
+    late["proto"] = late["proto_mask"] = 0
+    for f in ("sp", "dp"):
+        late[f + "_lo"], late[f + "_hi"] = 0, np.where(rng.random(n) < 0.7, 65535, 30_000)
+    late["priority"] = rng.integers(0, 300, n)              # ties too
+    late["id"] = 70_000 + np.arange(n)
+    every = np.concatenate([rules, late])
+    hdr = np.concatenate([synth.sample_inside(late[rng.integers(0, n, 1500)], rng),
+                          synth.make_packets(rules, 500, seed=133, frac_in=0.5)])
+    hdr = hdr[rng.permutation(len(hdr))]
+    rs = T.tang_ruleset_create(0, rules)
+    try:
+        T.tang_insert(rs, late)
+        assert T.tang_ruleset_coarse_rules(rs) > n // 2
+        want = orc.classify(every, hdr)
+        assert len(np.unique(want)) > 50
+        assert np.array_equal(classify_dev(rs, hdr), want)
+        if space == "narrow":
+            many = QUEUE_FROM + 77
+            reps = -(-many // len(hdr))
+            assert np.array_equal(classify_dev(rs, np.tile(hdr, reps)[:many]), np.tile(want, reps)[:many])
+    finally:
+        T.tang_ruleset_destroy(rs)
