@@ -383,8 +383,8 @@ def main():
                             "overhead": "bucket-filter blocks (8 B each) and the predictor's "
                                         "candidate word (4 B), not counted in bytes_per_pkt",
                             "what_binds": "issue, not HBM: the whole-batch search keeps the "
-                                          "texture data units about 95% busy and issues VALU "
-                                          "in about 83% of its cycles (derived shares in "
+                                          "texture data units about 96% busy and issues VALU "
+                                          "in about 86% of its cycles (derived shares in "
                                           "profiles/k_classify_c3_512k_zipf_16m.txt)"}}
     tr = measured_traffic("k_classify", wl)
     if tr:
